@@ -321,8 +321,8 @@ const char* mrt_last_error(void);
  * step loops.  kind: 0 forward steps, 1 adjoint steps, 2 recompute steps,
  * 3 tangent-linear steps, 4 continuous-adjoint steps.
  * mrt_timing_read synchronises on the recorded events and returns the
- * summed milliseconds and the number of kernel launches since the last
- * reset. */
+ * summed milliseconds and the number of time steps since the last reset (a
+ * D2Q9 launch takes several, a D3Q19 launch one). */
 int mrt_timing_enable(int32_t on);
 int mrt_timing_reset(void);
 int mrt_timing_read(int32_t kind, double* ms /* host */,

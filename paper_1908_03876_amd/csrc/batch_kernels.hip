@@ -167,11 +167,17 @@ __device__ __forceinline__ void forward_sweep_tiles(const BatchArgs<T>& a, const
     const TileNode<T> A = tile_of(a, t);
     if (!A.ok) continue;
     const ModelCoef<T> m = uniform_load(a.coef + A.k);
-    T fa[9], ga[9], ca = T(0);
-    forward_gather<T, true, FIRST>(A.g, A.n, m, src ? src + 18 * A.fo : nullptr,
-                                   a.u0 + A.fo, a.v0 + A.fo, a.ctrl + A.fo, fa, ga, ca);
-    forward_collide_store<T, false>(A.g, A.n, m, fa, ga, ca, dst + 18 * A.fo,
-                                    rec ? rec + 3 * A.fo : nullptr, 0u);
+    T fu[9], fv[9], r[5];
+    const T* s = src ? src + 18 * A.fo : nullptr;
+    pull_species<kAny, FIRST>(A.g, A.n, m.u, s, a.u0 + A.fo, fu);
+    pull_species<kAny, FIRST>(A.g, A.n, m.v, s ? s + 9 * A.g.plane : nullptr, a.v0 + A.fo, fv);
+    const size_t idx = A.n.r0 + A.n.x;
+    const T c = a.ctrl[A.fo + idx];
+    forward_collide<T, kVarFirst>(m, fu, fv, nullptr, c, r, nullptr, FIRST);
+    if (rec) store_record<kAny, kVarFirst, true>(A.g, A.n, rec + 3 * A.fo, r);
+    T* d = dst + 18 * A.fo;
+    store_species<kAny, false, false, true>(A.g, A.n, fu, d, 0u);
+    store_species<kAny, false, false, true>(A.g, A.n, fv, d + 9 * A.g.plane, 0u);
   }
 }
 
@@ -182,10 +188,21 @@ __device__ __forceinline__ void adjoint_sweep_tiles(const BatchArgs<T>& a, const
     const TileNode<T> A = tile_of(a, t);
     if (!A.ok) continue;
     const ModelCoef<T> m = uniform_load(a.coef + A.k);
-    adjoint_node<T, true, false, FIRST, false>(
-        A.g, A.n, m, src ? src + 18 * A.fo : nullptr,
-        dst ? dst + 18 * A.fo : nullptr, a.seed_u + A.fo, nullptr, rec + 3 * A.fo,
-        a.gacc + A.fo, nullptr, nullptr);
+    T nu[9], nv[9];
+    adjoint_gather<kAny, false, kVarFirst, FIRST, T>(A.g, A.n, src ? src + 18 * A.fo : nullptr,
+                                        a.seed_u + A.fo, nullptr, 0u, nu, nv, nullptr);
+    const size_t idx = A.n.r0 + A.n.x;
+    T r[5];
+    load_record<kAny, kVarFirst>(A.g, A.n, rec + 3 * A.fo, r);
+    const double share =
+        double(adjoint_collide<T, false, kVarFirst>(m, nu, nv, nullptr, r, nullptr, FIRST, false));
+    double* ga = a.gacc + A.fo + idx;
+    *ga = FIRST ? share : *ga + share;
+    if (dst) {
+      T* d = dst + 18 * A.fo;
+      store_species<kAny, false, true, true>(A.g, A.n, nu, d, 0u);
+      store_species<kAny, false, true, true>(A.g, A.n, nv, d + 9 * A.g.plane, 0u);
+    }
   }
 }
 
@@ -264,7 +281,7 @@ __global__ __launch_bounds__(256) void batch_finalize_kernel(BatchArgs<T> a, con
     NodeIdx n;
     if (!tile_node(tl, a.tile_w, g, n)) continue;
     const size_t fo = a.foff[k];
-    finalize_node<T, true, false>(g, n, src + 18 * fo, nullptr, a.uN + fo, a.vN + fo);
+    finalize_node<T>(g, n, src + 18 * fo, nullptr, a.uN + fo, a.vN + fo);
   }
 }
 

@@ -250,7 +250,7 @@ struct SpanGuard {
     (void)hipEventRecord(span.a, s);
     active = true;
   }
-  void count() { ++span.launches; }
+  void count(int steps) { span.launches += steps; }
   ~SpanGuard() {
     if (!active) return;
     (void)hipEventRecord(span.b, s);
@@ -369,6 +369,7 @@ struct mrt_tape {
   const void* f_u0 = nullptr;
   const void* f_v0 = nullptr;
   const void* f_ctrl = nullptr;
+  const void* last_state = nullptr;  // state after step N-1 of the last forward or recomputation
   std::vector<void*> allocs;
 };
 
@@ -465,49 +466,64 @@ int last_launch_error() {
   return MRT_OK;
 }
 
+int variant(const mrt_tape* t) { return t->ns == 3 ? 4 : (t->so2 ? 2 : (t->impl ? 3 : 1)); }
+
+// The previous step's kinetics (explicit second-order source) of the forward
+// sweep, k = 0, 1.  A store-all tape runs its sweeps one after the other, so
+// each has the other's buffer as its second one and can take several steps a
+// launch; elsewhere a sweep has one buffer and one step a launch.
+bool lag_pair(const mrt_tape* t) { return t->mode == 1; }
+void* lag_of(const mrt_tape* t, int k) { return k && lag_pair(t) ? t->alag : t->lag; }
+void* alag_of(const mrt_tape* t, int k) { return k && lag_pair(t) ? t->lag : t->alag; }
+bool one_step(const mrt_tape* t) { return t->so2 && !lag_pair(t); }
+
 // Forward steps [n0, n1) starting from `src` (null = equilibrium of u0, v0).
-// The output of step n goes to ckpt[(n+1)/K] when that step closes a
-// segment (checkpointed mode, forward pass), else to a ping-pong buffer.
+// Several steps run in one launch; the output of its last step n goes to
+// ckpt[(n+1)/K] when that step closes a segment (checkpointed mode, forward
+// pass), else to the ping-pong buffer that src is not.
 // Returns the buffer holding the last written state through *last.
 //
-// Second-order source: the kinetics of the previous step live in t->lag;
-// a step that closes a segment also saves them beside its checkpoint, and
-// a recomputation that starts from checkpoint `seg` (restore_lag) first
-// restores them.
+// Second-order source: the kinetics of the previous step live in t->lag; a
+// launch that closes a segment writes them beside its checkpoint, and one that
+// starts there reads them from it.
 template <typename T>
 int run_forward_steps(mrt_tape* t, const mrt::ModelCoef<T>& m,
                       const mrt::Geometry& g, int n0, int n1, const T* src,
                       const T* u0, const T* v0, const T* ctrl, bool record,
                       bool write_ckpt, int kind, hipStream_t s,
-                      const T** last, bool restore_lag = false, const T* w0 = nullptr) {
+                      const T** last, const T* w0 = nullptr) {
   SpanGuard span(kind, s);
   const int seg = n0 / t->K;
-  if (t->so2 && restore_lag && n0 > 0)
-    HIP_TRY(hipMemcpyAsync(t->lag, t->ckpt_lag[seg], 2 * t->plane * t->elem,
-                           hipMemcpyDeviceToDevice, s));
-  for (int n = n0; n < n1; ++n) {
+  // the kinetics that go with src: a checkpoint's, or the buffer in use
+  const T* lag = static_cast<const T*>(t->lag);
+  if (t->so2 && n0 > 0 && n0 % t->K == 0) lag = static_cast<const T*>(t->ckpt_lag[seg]);
+  for (int n = n0; n < n1;) {
+    // a launch ends where a checkpoint is due
+    const int seg_end = t->mode == 2 ? std::min(n1, (n / t->K + 1) * t->K) : n1;
     mrt::FwdLaunch<T> a;
     a.src = src;
     a.u0 = u0;
     a.v0 = v0;
     a.ctrl = ctrl;
     a.rec = record ? slot<T>(t, n - seg * t->K) : nullptr;
-    a.variant = t->ns == 3 ? 4 : (t->so2 ? 2 : (t->impl ? 3 : 1));
-    a.lag = t->so2 ? static_cast<T*>(t->lag) : nullptr;
+    a.rec_stride = t->rec_slot_bytes / sizeof(T);
+    a.variant = variant(t);
+    a.lag = lag;
     a.w0 = w0;
-    T* dst = static_cast<T*>(t->buf[n & 1]);
-    const bool closes = write_ckpt && t->mode == 2 && (n + 1) % t->K == 0 && n + 1 < t->nsteps;
-    if (closes) dst = static_cast<T*>(t->ckpt[(n + 1) / t->K]);
+    const mrt::StepPlan p = mrt::plan_steps(g, sizeof(T), a.variant, seg_end - n, one_step(t));
+    n += p.steps;
+    const bool closes = write_ckpt && t->mode == 2 && n % t->K == 0 && n < t->nsteps;
+    T* dst = static_cast<T*>(closes ? t->ckpt[n / t->K] : t->buf[src == t->buf[0] ? 1 : 0]);
     a.dst = dst;
-    mrt::launch_forward_step<T>(g, m, a, s);
-    span.count();
+    a.lag_out = static_cast<T*>(closes ? t->ckpt_lag[n / t->K] : lag_of(t, lag == t->lag ? 1 : 0));
+    mrt::launch_forward<T>(g, m, a, p, s);
+    span.count(p.steps);
     int rc = last_launch_error();
     if (rc) return rc;
-    if (closes && t->so2)
-      HIP_TRY(hipMemcpyAsync(t->ckpt_lag[(n + 1) / t->K], t->lag, 2 * t->plane * t->elem,
-                             hipMemcpyDeviceToDevice, s));
     src = dst;
+    lag = a.lag_out;
   }
+  if (n1 == t->nsteps) t->last_state = src;
   *last = src;
   return MRT_OK;
 }
@@ -532,12 +548,12 @@ int forward_impl(const mrt_problem* p, mrt_tape* t, const void* u0,
   const T* tw0 = static_cast<const T*>(p->nspecies == 3 ? p->w0 : nullptr);
   if (rec_start > 0) {
     rc = run_forward_steps<T>(t, m, g, 0, rec_start, nullptr, tu0, tv0, tc,
-                              false, true, 0, s, &cur, false, tw0);
+                              false, true, 0, s, &cur, tw0);
     if (rc) return rc;
   }
   if (rec_start < N) {
     rc = run_forward_steps<T>(t, m, g, rec_start, N, cur, tu0, tv0, tc, true,
-                              true, 0, s, &cur, false, tw0);
+                              true, 0, s, &cur, tw0);
     if (rc) return rc;
   }
   mrt::launch_finalize<T>(g, cur, static_cast<T*>(state), static_cast<T*>(uN),
@@ -563,8 +579,8 @@ int adjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0,
   const T* tu0 = static_cast<const T*>(u0);
   const T* tv0 = static_cast<const T*>(v0);
   const T* tc = static_cast<const T*>(control);
-  const bool want0 = adj_u0 != nullptr || adj_v0 != nullptr;
   const T* asrc = nullptr;
+  const T* mu = static_cast<const T*>(t->alag);
   for (int seg = t->nseg - 1; seg >= 0; --seg) {
     const int n0 = seg * K, n1 = std::min(N, n0 + K);
     if (t->rec_seg != seg) {
@@ -574,7 +590,7 @@ int adjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0,
       const T* dummy = nullptr;
       t->rec_seg = -1;
       int rc = run_forward_steps<T>(t, m, g, n0, n1, src, tu0, tv0, tc, true,
-                                    false, 2, s, &dummy, true,
+                                    false, 2, s, &dummy,
                                     static_cast<const T*>(p->nspecies == 3 ? p->w0 : nullptr));
       if (rc) return rc;
       t->rec_seg = seg;
@@ -582,12 +598,11 @@ int adjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0,
     const T* su = static_cast<const T*>(seed_u);
     const T* sv = static_cast<const T*>(seed_v);
     if (t->impl && seg == t->nseg - 1) {
-      // the cost sees Theta^N, a function of the sums of the last state,
-      // which buf[(N-1) & 1] holds (the last step never closes a segment,
-      // and the last segment was the most recent one run or recomputed)
+      // the cost sees Theta^N, a function of the sums of the last state (the
+      // last segment was the most recent one run or recomputed)
       T* tu = static_cast<T*>(t->tseed);
       T* tv = tu + t->plane;
-      mrt::launch_implicit_terminal<T>(g, m, static_cast<const T*>(t->buf[(N - 1) & 1]), tc,
+      mrt::launch_implicit_terminal<T>(g, m, static_cast<const T*>(t->last_state), tc,
                                        su, sv, tu, tv, gacc, s);
       int rc = last_launch_error();
       if (rc) return rc;
@@ -595,23 +610,26 @@ int adjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0,
       sv = tv;
     }
     SpanGuard span(1, s);
-    for (int n = n1 - 1; n >= n0; --n) {
+    for (int n = n1 - 1; n >= n0;) {
       mrt::AdjLaunch<T> a;
       a.src = asrc;
-      a.first = n == N - 1;
-      a.last = (n == 0 && want0) ? 1 : 0;
-      a.dst = n == 0 ? nullptr : static_cast<T*>(t->abuf[n & 1]);
       a.seed_u = su;
       a.seed_v = sv;
-      a.variant = t->ns == 3 ? 4 : (t->so2 ? 2 : (t->impl ? 3 : 1));
+      a.variant = variant(t);
       a.rec = slot<T>(t, n - n0);
+      a.rec_stride = t->rec_slot_bytes / sizeof(T);
       a.g = gacc;
-      a.adj_u0 = static_cast<T*>(adj_u0);
-      a.adj_v0 = static_cast<T*>(adj_v0);
-      a.mu = t->so2 ? static_cast<T*>(t->alag) : nullptr;
-      a.step0 = n == 0 ? 1 : 0;
-      mrt::launch_adjoint_step<T>(g, m, a, s);
-      span.count();
+      a.mu = mu;
+      mu = a.mu_out = static_cast<T*>(alag_of(t, mu == t->alag ? 1 : 0));
+      a.step = n;
+      const mrt::StepPlan plan = mrt::plan_steps(g, sizeof(T), a.variant, n - n0 + 1, one_step(t));
+      n -= plan.steps;
+      const bool ends = n < 0;
+      a.dst = ends ? nullptr : static_cast<T*>(t->abuf[asrc == t->abuf[0] ? 1 : 0]);
+      a.adj_u0 = ends ? static_cast<T*>(adj_u0) : nullptr;
+      a.adj_v0 = ends ? static_cast<T*>(adj_v0) : nullptr;
+      mrt::launch_adjoint<T>(g, m, a, plan, s);
+      span.count(plan.steps);
       int rc = last_launch_error();
       if (rc) return rc;
       asrc = a.dst;
@@ -634,6 +652,7 @@ int tlm_impl(const mrt_problem* p, mrt_tape* t, const void* u0, const void* v0,
   const T* tv0 = static_cast<const T*>(v0);
   const T* tc = static_cast<const T*>(control);
   const T* dsrc = nullptr;
+  const T* dlag = static_cast<const T*>(t->alag);
   for (int seg = 0; seg < t->nseg; ++seg) {
     const int n0 = seg * K, n1 = std::min(N, n0 + K);
     if (t->rec_seg != seg) {
@@ -641,32 +660,36 @@ int tlm_impl(const mrt_problem* p, mrt_tape* t, const void* u0, const void* v0,
       const T* dummy = nullptr;
       t->rec_seg = -1;
       int rc = run_forward_steps<T>(t, m, g, n0, n1, src, tu0, tv0, tc, true, false, 2, s,
-                                    &dummy, true,
+                                    &dummy,
                                     static_cast<const T*>(p->nspecies == 3 ? p->w0 : nullptr));
       if (rc) return rc;
       t->rec_seg = seg;
     }
     SpanGuard span(3, s);
-    for (int n = n0; n < n1; ++n) {
+    for (int n = n0; n < n1;) {
       mrt::TlmLaunch<T> a;
       a.src = dsrc;
-      a.dst = static_cast<T*>(t->abuf[n & 1]);
+      a.dst = static_cast<T*>(t->abuf[dsrc == t->abuf[0] ? 1 : 0]);
       a.du0 = static_cast<const T*>(du0);
       a.dv0 = static_cast<const T*>(dv0);
       a.dc = static_cast<const T*>(dc);
       a.rec = slot<T>(t, n - n0);
-      a.variant = t->ns == 3 ? 4 : (t->so2 ? 2 : (t->impl ? 3 : 1));
-      a.dlag = t->so2 ? static_cast<T*>(t->alag) : nullptr;
-      mrt::launch_tlm_step<T>(g, m, a, s);
-      span.count();
+      a.rec_stride = t->rec_slot_bytes / sizeof(T);
+      a.variant = variant(t);
+      a.dlag = dlag;
+      dlag = a.dlag_out = static_cast<T*>(alag_of(t, dlag == t->alag ? 1 : 0));
+      const mrt::StepPlan plan = mrt::plan_steps(g, sizeof(T), a.variant, n1 - n, one_step(t));
+      mrt::launch_tlm<T>(g, m, a, plan, s);
+      span.count(plan.steps);
       int rc = last_launch_error();
       if (rc) return rc;
+      n += plan.steps;
       dsrc = a.dst;
     }
   }
   if (t->impl)
-    // the last segment ran last, so buf[(N-1) & 1] holds the forward's last state
-    mrt::launch_implicit_tlm_final<T>(g, m, static_cast<const T*>(t->buf[(N - 1) & 1]), dsrc,
+    // the last segment ran last
+    mrt::launch_implicit_tlm_final<T>(g, m, static_cast<const T*>(t->last_state), dsrc,
                                       tc, static_cast<const T*>(dc), static_cast<T*>(duN),
                                       static_cast<T*>(dvN), s);
   else
@@ -694,23 +717,25 @@ int cadjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0, const void*
       const T* dummy = nullptr;
       t->rec_seg = -1;
       int rc = run_forward_steps<T>(t, m, g, n0, n1, cs, tu0, tv0, tc, true, false, 2, s,
-                                    &dummy, true);
+                                    &dummy);
       if (rc) return rc;
       t->rec_seg = seg;
     }
     SpanGuard span(4, s);
-    for (int n = n1 - 1; n >= n0; --n) {
+    for (int n = n1 - 1; n >= n0;) {
       mrt::CadjLaunch<T> a;
       a.src = src;
-      a.dst = static_cast<T*>(t->abuf[n & 1]);
+      a.dst = static_cast<T*>(t->abuf[src == t->abuf[0] ? 1 : 0]);
       a.seed_u = static_cast<const T*>(seed_u);
       a.rec = slot<T>(t, n - n0);
+      a.rec_stride = t->rec_slot_bytes / sizeof(T);
       a.g = gacc;
-      a.first = n == N - 1;
-      mrt::launch_cadj_step<T>(g, m, cc, a, s);
-      span.count();
+      const mrt::StepPlan plan = mrt::plan_steps(g, sizeof(T), 1, n - n0 + 1, false);
+      mrt::launch_cadj<T>(g, m, cc, a, plan, s);
+      span.count(plan.steps);
       int rc = last_launch_error();
       if (rc) return rc;
+      n -= plan.steps;
       src = a.dst;
     }
   }

@@ -90,25 +90,57 @@ __device__ __forceinline__ unsigned link_of(const Geometry& g, unsigned flag,
   return flag ? unsigned(g.link[idx]) : 0u;
 }
 
-// Offset (within a plane) of node x - e_i for i = 0..8 (periodic wrap).
-__device__ __forceinline__ size_t pull_off(const NodeIdx& n, int i) {
+// How the lanes of a wavefront lie, and so how an element is addressed:
+// kRow, one row (a scalar row base and a 32-bit lane offset); kSmall, several
+// rows of a plane below 4 GiB (a scalar plane base and a 32-bit lane offset);
+// kAny, several rows of any plane (a 64-bit address per lane).
+enum Lanes { kRow, kSmall, kAny };
+
+template <Lanes A, typename T>
+__device__ __forceinline__ T* element(T* plane, size_t row, int col) {
+  if (A == kRow)
+    return (T*)((char*)(plane + row) + unsigned(col) * unsigned(sizeof(T)));
+  if (A == kSmall)
+    return (T*)((char*)plane + (unsigned(row) + unsigned(col)) * unsigned(sizeof(T)));
+  return plane + row + col;
+}
+
+// Element of a plane at node x - e_i for i = 0..8 (periodic wrap).
+template <Lanes A, typename T>
+__device__ __forceinline__ T* pull_at(T* plane, const NodeIdx& n, int i) {
   switch (i) {
-    case 0: return n.r0 + n.x;
-    case 1: return n.r0 + n.xm;   // e1 = (1,0)
-    case 2: return n.rm + n.x;    // e2 = (0,1)
-    case 3: return n.r0 + n.xp;   // e3 = (-1,0)
-    case 4: return n.rp + n.x;    // e4 = (0,-1)
-    case 5: return n.rm + n.xm;   // e5 = (1,1)
-    case 6: return n.rm + n.xp;   // e6 = (-1,1)
-    case 7: return n.rp + n.xp;   // e7 = (-1,-1)
-    default: return n.rp + n.xm;  // e8 = (1,-1)
+    case 0: return element<A>(plane, n.r0, n.x);
+    case 1: return element<A>(plane, n.r0, n.xm);  // e1 = (1,0)
+    case 2: return element<A>(plane, n.rm, n.x);   // e2 = (0,1)
+    case 3: return element<A>(plane, n.r0, n.xp);  // e3 = (-1,0)
+    case 4: return element<A>(plane, n.rp, n.x);   // e4 = (0,-1)
+    case 5: return element<A>(plane, n.rm, n.xm);  // e5 = (1,1)
+    case 6: return element<A>(plane, n.rm, n.xp);  // e6 = (-1,1)
+    case 7: return element<A>(plane, n.rp, n.xp);  // e7 = (-1,-1)
+    default: return element<A>(plane, n.rp, n.xm); // e8 = (1,-1)
   }
 }
 
-// Offset of node x + e_i = x - e_opp(i).
-__device__ __forceinline__ size_t push_off(const NodeIdx& n, int i) {
-  return pull_off(n, opp(i));
+// At node x + e_i = x - e_opp(i).
+template <Lanes A, typename T>
+__device__ __forceinline__ T* push_at(T* plane, const NodeIdx& n, int i) {
+  return pull_at<A>(plane, n, opp(i));
 }
+
+// At the node itself.
+template <Lanes A, typename T>
+__device__ __forceinline__ T* own_at(T* plane, const NodeIdx& n) {
+  return element<A>(plane, n.r0, n.x);
+}
+
+// Walls.  The pull reads plane i at x - e_i without a test: where that
+// neighbour is solid, its (otherwise unused) slot holds the node's own
+// reflected population, parked there by the step before; where it lies
+// outside a non-periodic lattice, the address wraps to the opposite edge,
+// whose population of that direction leaves the lattice and is read by
+// nobody, so its slot takes the reflected one.  The adjoint gathers plane i
+// at x + e_i in the same way.  A node's link word has bit 0 set if it is
+// solid and bit i if x - e_i is solid or outside a non-periodic lattice.
 
 // Is x - e_i outside the lattice (meaningful for non-periodic lattices)?
 __device__ __forceinline__ bool pull_outside(const NodeIdx& n, int i) {
@@ -130,35 +162,29 @@ __device__ __forceinline__ bool push_outside(const NodeIdx& n, int i) {
   return pull_outside(n, opp(i));
 }
 
-// Source of the population that node x pulls in direction i: plane i at
-// x - e_i.  A solid in-domain neighbour needs no test: its slot holds the
-// reflected population written by the previous step's wall stores.  Only
-// at the edge of a non-periodic lattice does the node take its own
-// opposite population (halfway bounce-back).
-template <bool PERIODIC>
-__device__ __forceinline__ size_t pull_src(const NodeIdx& n, int i,
-                                           size_t plane) {
-  if (!PERIODIC && pull_outside(n, i))
-    return size_t(opp(i)) * plane + n.r0 + n.x;
-  return size_t(i) * plane + pull_off(n, i);
+// a b + c d with one rounding for a b and the sum and one for c d.  Written
+// out where a sum of two products may be contracted either way, so that every
+// kernel that contains the expression computes the same bits.
+__device__ __forceinline__ float dot2(float a, float b, float c, float d) {
+  return __builtin_fmaf(a, b, c * d);
+}
+__device__ __forceinline__ double dot2(double a, double b, double c, double d) {
+  return __builtin_fma(a, b, c * d);
 }
 
-// Adjoint gather source: plane i at x + e_i (transpose of the pull), or the
-// node's own opposite value at the edge of a non-periodic lattice.
-template <bool PERIODIC>
-__device__ __forceinline__ size_t gather_src(const NodeIdx& n, int i,
-                                             size_t plane) {
-  if (!PERIODIC && push_outside(n, i))
-    return size_t(opp(i)) * plane + n.r0 + n.x;
-  return size_t(i) * plane + push_off(n, i);
+// w . f with the lattice weights.
+template <typename T>
+__device__ __forceinline__ T weighted(const T f[9]) {
+  return dot2(T(4.0 / 9.0), f[0], T(1.0 / 9.0), f[1] + f[2] + f[3] + f[4]) +
+         T(1.0 / 36.0) * (f[5] + f[6] + f[7] + f[8]);
 }
 
 // Relaxation in moment space: f <- f - M0^-1 Pi (M0 f - m_eq(theta)).
-// With theta = 0 and the K block transposed this is f <- f - C^T f
-// (C^T = M0^-1 Pi^T M0 since Pi only couples moments of equal row norm),
-// without the conserved zeroth-moment part.  Returns the scaled amounts
+// Without the equilibrium (EQ false) and with the K block transposed this is
+// f <- f - C^T f (C^T = M0^-1 Pi^T M0 since Pi only couples moments of equal
+// row norm), without the conserved zeroth-moment part.  Returns the scaled amounts
 // (a1, a2) of the e and epsilon moments for the adjoint equilibrium term.
-template <typename T>
+template <bool EQ, typename T>
 __device__ __forceinline__ void relax(T f[9], T theta,
                                       const SpeciesCoef<T>& c, T& a1o,
                                       T& a2o) {
@@ -174,10 +200,10 @@ __device__ __forceinline__ void relax(T f[9], T theta,
   const T m6 = T(-2) * (f[2] - f[4]) + dy;          // q_y
   const T m7 = f[1] - f[2] + f[3] - f[4];           // p_xx
   const T m8 = f[5] - f[6] + f[7] - f[8];           // p_xy
-  const T a1 = c.s1 * (m1 - c.e_eq * theta);
-  const T a2 = c.s2 * (m2 - c.eps_eq * theta);
-  const T a3 = c.k00 * m3 + c.k01 * m5;
-  const T a5 = c.k10 * m3 + c.k11 * m5;
+  const T a1 = c.s1 * (EQ ? m1 - c.e_eq * theta : m1);
+  const T a2 = c.s2 * (EQ ? m2 - c.eps_eq * theta : m2);
+  const T a3 = dot2(c.k00, m3, c.k01, m5);
+  const T a5 = dot2(c.k10, m3, c.k11, m5);
   const T a4 = c.s3 * m4;
   const T a6 = c.s4 * m6;
   const T a7 = c.s5 * m7;
@@ -199,41 +225,24 @@ __device__ __forceinline__ void relax(T f[9], T theta,
 
 // --------------------------------------------------------------- forward
 
-// Pre-collision populations of node n: the pull from src (with wall slots),
-// or the equilibrium initialisation phi_i = w_i Theta_0 (phieq, zero flux)
-// on the first step.  Also returns the node's control value, so that every
-// load of a node update can be issued before any of its stores.
-template <typename T, bool PERIODIC, bool FIRST>
-__device__ __forceinline__ void forward_gather(const Geometry& g, const NodeIdx& n,
-                                               const ModelCoef<T>& m, const T* __restrict__ src,
-                                               const T* __restrict__ u0, const T* __restrict__ v0,
-                                               const T* __restrict__ ctrl, T fu[9], T fv[9],
-                                               T& c) {
-  const size_t idx = n.r0 + n.x;
+// Pre-collision populations of one species at node n: the pull from its
+// planes in src, or (FIRST) the equilibrium initialisation phi_i = w_i
+// Theta_0 (phieq, zero flux; a null theta0 is zero).
+template <Lanes A, bool FIRST, typename T>
+__device__ __forceinline__ void pull_species(const Geometry& g, const NodeIdx& n,
+                                             const SpeciesCoef<T>& c, const T* __restrict__ src,
+                                             const T* __restrict__ theta0, T f[9]) {
   if (FIRST) {
-    const T a = u0[idx], b = v0[idx];
-    fu[0] = m.u.w_rest * a;
-    fv[0] = m.v.w_rest * b;
+    const T a = theta0 ? *own_at<A>(theta0, n) : T(0);
+    f[0] = c.w_rest * a;
 #pragma unroll
-    for (int i = 1; i < 5; ++i) {
-      fu[i] = m.u.w_axis * a;
-      fv[i] = m.v.w_axis * b;
-    }
+    for (int i = 1; i < 5; ++i) f[i] = c.w_axis * a;
 #pragma unroll
-    for (int i = 5; i < 9; ++i) {
-      fu[i] = m.u.w_diag * a;
-      fv[i] = m.v.w_diag * b;
-    }
+    for (int i = 5; i < 9; ++i) f[i] = c.w_diag * a;
   } else {
-    const T* sv = src + 9 * g.plane;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      const size_t o = pull_src<PERIODIC>(n, i, g.plane);
-      fu[i] = src[o];
-      fv[i] = sv[o];
-    }
+    for (int i = 0; i < 9; ++i) f[i] = *pull_at<A>(src + size_t(i) * g.plane, n, i);
   }
-  c = ctrl[idx];
 }
 
 // Sources tau S_i + tau w_i Phi (S, PhiS) with tau = 1, 1/Cs^2 = 3: the
@@ -261,31 +270,42 @@ __device__ __forceinline__ void add_sources(T fu[9], T fv[9], T phu, T ax, T ay,
   for (int i = 5; i < 9; ++i) fv[i] += q36;
 }
 
-// Post-collision state of a fluid node: non-temporal stores (the state does
-// not fit the caches and is next read one whole sweep later) and the wall
-// slots: a population phi*_i streaming into the solid node x + e_i is
-// reflected; it is parked in that node's slot of plane opp(i), where the
-// next step's pull in direction opp(i) at x reads it.
-template <typename T, bool MASKED>
-__device__ __forceinline__ void store_state(const Geometry& g, const NodeIdx& n,
-                                            const T fu[9], const T fv[9],
-                                            T* __restrict__ dst, unsigned lm) {
-  const size_t idx = n.r0 + n.x;
-  T* dv = dst + 9 * g.plane;
+// Non-temporal (NT) or ordinary store.  Non-temporal ones suit values of whole
+// 64-byte chunks that are next read a sweep later; a part of a chunk goes to
+// memory by itself, at the cost of a read-modify-write there.
+template <bool NT, typename T>
+__device__ __forceinline__ void put(T* p, T v) {
+  if (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+// Stores of one species' populations at a fluid node (its 9 planes at dst),
+// with the wall slots.  Forward: a population phi*_i streaming into a wall
+// at x + e_i is reflected; it is parked in that node's slot of plane
+// opp(i), where the next step's pull in direction opp(i) at x reads it.
+// Adjoint (ADJ): the next gather in direction i at x reads plane i at the
+// wall x + e_i and must find lambda_opp(i)(x).  A population whose slot a
+// node across a non-periodic lattice uses (it leaves the lattice there; in
+// the adjoint, plane i at x is gathered by x - e_i) is not stored itself.
+template <Lanes A, bool WALLS, bool ADJ, bool NT = false, typename T>
+__device__ __forceinline__ void store_species(const Geometry& g, const NodeIdx& n, const T f[9],
+                                              T* __restrict__ dst, unsigned lm) {
+  if (WALLS && !g.periodic && (n.ex0 || n.ex1 || n.ey0 || n.ey1)) {
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    __builtin_nontemporal_store(fu[i], &dst[size_t(i) * g.plane + idx]);
-    __builtin_nontemporal_store(fv[i], &dv[size_t(i) * g.plane + idx]);
+    for (int i = 0; i < 9; ++i)
+      if (!(ADJ ? pull_outside(n, i) : push_outside(n, i)))
+        *own_at<A>(dst + size_t(i) * g.plane, n) = f[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) put<NT>(own_at<A>(dst + size_t(i) * g.plane, n), f[i]);
   }
-  if (MASKED && (lm & 0x1FEu)) {
+  if (WALLS && (lm & 0x1FEu)) {
 #pragma unroll
-    for (int i = 1; i < 9; ++i) {
-      if ((lm >> opp(i)) & 1u) {
-        const size_t o = size_t(opp(i)) * g.plane + push_off(n, i);
-        dst[o] = fu[i];
-        dv[o] = fv[i];
-      }
-    }
+    for (int i = 1; i < 9; ++i)
+      if ((lm >> opp(i)) & 1u)
+        *push_at<A>(dst + size_t(ADJ ? i : opp(i)) * g.plane, n, i) = f[ADJ ? opp(i) : i];
   }
 }
 
@@ -313,42 +333,6 @@ __device__ __forceinline__ void implicit_solve(const ModelCoef<T>& m, T Gu, T Gv
 // 1); 4 three species (u, v and a repulsive signal w, first-order source).
 constexpr int kVarFirst = 1, kVarExplicit = 2, kVarImplicit = 3, kVarThree = 4;
 
-// Third species of a node: its pull from planes 18..26 of src (with wall
-// slots), or w_i w0 at the first step.
-template <typename T, bool PERIODIC, bool FIRST>
-__device__ __forceinline__ void gather_w(const Geometry& g, const NodeIdx& n,
-                                         const ModelCoef<T>& m, const T* __restrict__ src,
-                                         const T* __restrict__ w0, T fw[9]) {
-  if (FIRST) {
-    const T a = w0 ? w0[n.r0 + n.x] : T(0);
-    fw[0] = m.w.w_rest * a;
-#pragma unroll
-    for (int i = 1; i < 5; ++i) fw[i] = m.w.w_axis * a;
-#pragma unroll
-    for (int i = 5; i < 9; ++i) fw[i] = m.w.w_diag * a;
-  } else {
-    const T* sw = src + 18 * g.plane;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) fw[i] = sw[pull_src<PERIODIC>(n, i, g.plane)];
-  }
-}
-
-// Stores of the third species' post-collision values (planes 18..26 of
-// dst) with their wall slots, as store_state does for u and v.
-template <typename T, bool MASKED>
-__device__ __forceinline__ void store_w(const Geometry& g, const NodeIdx& n, const T fw[9],
-                                        T* __restrict__ dst, unsigned lm) {
-  const size_t idx = n.r0 + n.x;
-  T* dw = dst + 18 * g.plane;
-#pragma unroll
-  for (int i = 0; i < 9; ++i) __builtin_nontemporal_store(fw[i], &dw[size_t(i) * g.plane + idx]);
-  if (MASKED && (lm & 0x1FEu)) {
-#pragma unroll
-    for (int i = 1; i < 9; ++i)
-      if ((lm >> opp(i)) & 1u) dw[size_t(opp(i)) * g.plane + push_off(n, i)] = fw[i];
-  }
-}
-
 // Kinetics source tau w_i Phi on one species' populations.
 template <typename T>
 __device__ __forceinline__ void add_kinetics(T f[9], T ph) {
@@ -359,9 +343,7 @@ __device__ __forceinline__ void add_kinetics(T f[9], T ph) {
   for (int i = 5; i < 9; ++i) f[i] += ph * T(1.0 / 36.0);
 }
 
-// Collision of the gathered node values and the stores: record (u, j_v),
-// post-collision state, wall slots.  `lm` is the node's link word (0
-// without a mask).
+// Collision of a node's gathered populations, one forward step.
 //
 // LAG: second-order source term of (eq:LBEG) with kappa_t = 1, kappa_x = 0
 // by the explicit characteristic difference: tau F + (tau/2)(F - F_prev)
@@ -383,17 +365,15 @@ __device__ __forceinline__ void add_kinetics(T f[9], T ph) {
 // and 4), the chemotactic flux of u gains u Bw j_w (the repulsion
 // A_u2 grad w with grad w = -K_w j_w / (tau d_w Cs^2)), and w relaxes with
 // its own rates and receives Phi_w = a_w u - b_w w + s_w.
-template <typename T, bool MASKED, int VAR = kVarFirst>
-__device__ __forceinline__ void forward_collide_store(const Geometry& g, const NodeIdx& n,
-                                                      const ModelCoef<T>& m, T fu[9], T fv[9],
-                                                      T c, T* __restrict__ dst,
-                                                      T* __restrict__ rec, unsigned lm,
-                                                      T* __restrict__ lag = nullptr,
-                                                      bool first = false,
-                                                      T* __restrict__ fw = nullptr) {
+//
+// forward_collide does the arithmetic in registers: f in place, the record
+// (u, j_v, and j_w of three species) to r[0..4], lag (LAG) from the previous
+// step's kinetics to this step's.  `first` marks step 0.
+template <typename T, int VAR>
+__device__ __forceinline__ void forward_collide(const ModelCoef<T>& m, T fu[9], T fv[9], T fw[9],
+                                                T c, T r[5], T lag[2], bool first) {
   constexpr bool W3 = VAR == kVarThree;
   constexpr bool LAG = VAR == kVarExplicit;
-  const size_t idx = n.r0 + n.x;
   // macroscopic values (UGS) and the first moment of v
   T u = T(0), v = T(0);
 #pragma unroll
@@ -416,38 +396,30 @@ __device__ __forceinline__ void forward_collide_store(const Geometry& g, const N
     for (int i = 0; i < 9; ++i) wv += fw[i];
     kx = fw[1] - fw[3] + fw[5] - fw[6] - fw[7] + fw[8];
     ky = fw[2] - fw[4] + fw[5] + fw[6] - fw[7] - fw[8];
+    r[3] = kx;
+    r[4] = ky;
   }
-  if (rec != nullptr) {
-    // the record is read back only by the adjoint sweep, much later.  The
-    // solid lanes of a mixed wavefront store it too (zeros, read by nobody)
-    // so that the stores fill whole 64-byte chunks: a store instruction
-    // that leaves part of a chunk unwritten costs a read-modify-write
-    __builtin_nontemporal_store(u, &rec[idx]);
-    __builtin_nontemporal_store(jx, &rec[g.plane + idx]);
-    __builtin_nontemporal_store(jy, &rec[2 * g.plane + idx]);
-    if (W3) {
-      __builtin_nontemporal_store(kx, &rec[3 * g.plane + idx]);
-      __builtin_nontemporal_store(ky, &rec[4 * g.plane + idx]);
-    }
-  }
+  r[0] = u;
+  r[1] = jx;
+  r[2] = jy;
   // chemotactic source: A_u1 grad v = u * B * j_v with the local gradient
   // grad v = -K_v j_v / (tau d_v Cs^2)
-  T ax = u * (m.b00 * jx + m.b01 * jy);
-  T ay = u * (m.b10 * jx + m.b11 * jy);
+  T ax = u * dot2(m.b00, jx, m.b01, jy);
+  T ay = u * dot2(m.b10, jx, m.b11, jy);
   if (W3) {
-    ax += u * (m.bw00 * kx + m.bw01 * ky);
-    ay += u * (m.bw10 * kx + m.bw11 * ky);
+    ax += u * dot2(m.bw00, kx, m.bw01, ky);
+    ay += u * dot2(m.bw10, kx, m.bw11, ky);
   }
   const T ru = m.r_u * u * (T(1) - u);
   const T rv = m.a_uv * u - m.b_v * v;
   T phu, phv;
   if (LAG) {
-    const T lu = first ? ru : lag[idx];
-    const T lv = first ? rv : lag[g.plane + idx];
+    const T lu = first ? ru : lag[0];
+    const T lv = first ? rv : lag[1];
     phu = T(1.5) * ru - T(0.5) * lu;
     phv = T(1.5) * rv - T(0.5) * lv + c;
-    lag[idx] = ru;  // every lane, as the record
-    lag[g.plane + idx] = rv;
+    lag[0] = ru;
+    lag[1] = rv;
   } else if (VAR == kVarImplicit) {
     phu = T(0.5) * ru;
     phv = T(0.5) * (rv + c);
@@ -456,18 +428,31 @@ __device__ __forceinline__ void forward_collide_store(const Geometry& g, const N
     phv = rv + c;
   }
   T t1, t2;
-  relax(fu, u, m.u, t1, t2);
-  relax(fv, v, m.v, t1, t2);
+  relax<true>(fu, u, m.u, t1, t2);
+  relax<true>(fv, v, m.v, t1, t2);
   add_sources(fu, fv, phu, ax, ay, phv);
   if (W3) {
-    relax(fw, wv, m.w, t1, t2);
+    relax<true>(fw, wv, m.w, t1, t2);
     add_kinetics(fw, m.a_w * u - m.b_w * wv + m.s_w);
   }
-  // solid nodes of mixed wavefronts computed on zeros; they store no state
-  // (their slots hold the neighbours' wall stores)
-  if (MASKED && (lm & 1u)) return;
-  store_state<T, MASKED>(g, n, fu, fv, dst, lm);
-  if (W3) store_w<T, MASKED>(g, n, fw, dst, lm);
+}
+
+// Record of one step at a node.
+template <Lanes A, int VAR, bool NT = false, typename T>
+__device__ __forceinline__ void store_record(const Geometry& g, const NodeIdx& n,
+                                             T* __restrict__ rec, const T r[5]) {
+#pragma unroll
+  for (int k = 0; k < (VAR == kVarThree ? 5 : 3); ++k)
+    put<NT>(own_at<A>(rec + size_t(k) * g.plane, n), r[k]);
+}
+
+// Read once: non-temporal.
+template <Lanes A, int VAR, typename T>
+__device__ __forceinline__ void load_record(const Geometry& g, const NodeIdx& n,
+                                            const T* __restrict__ rec, T r[5]) {
+#pragma unroll
+  for (int k = 0; k < (VAR == kVarThree ? 5 : 3); ++k)
+    r[k] = __builtin_nontemporal_load(own_at<A>(rec + size_t(k) * g.plane, n));
 }
 
 // Tangent-linear step (sensitivity LBE, LIBEG-V) at a node: the derivative
@@ -486,20 +471,13 @@ __device__ __forceinline__ void forward_collide_store(const Geometry& g, const N
 // kVarThree: fw holds the perturbation of the third species;
 // d(u Bw j_w) = du Bw j_w + u Bw dj_w with j_w recorded, and
 // dPhi_w = a_w du - b_w dw.
-template <typename T, bool MASKED, int VAR = kVarFirst>
-__device__ __forceinline__ void tlm_collide_store(const Geometry& g, const NodeIdx& n,
-                                                  const ModelCoef<T>& m, T fu[9], T fv[9],
-                                                  T dc, const T* __restrict__ rec,
-                                                  T* __restrict__ dst, unsigned lm,
-                                                  T* __restrict__ dlag = nullptr,
-                                                  bool first = false,
-                                                  T* __restrict__ fw = nullptr) {
+// r: the recorded u, j_v (and j_w) of the step.
+template <typename T, int VAR>
+__device__ __forceinline__ void tlm_collide(const ModelCoef<T>& m, T fu[9], T fv[9], T fw[9], T dc,
+                                            const T r[5], T dlag[2], bool first) {
   constexpr bool LAG = VAR == kVarExplicit;
   constexpr bool W3 = VAR == kVarThree;
-  const size_t idx = n.r0 + n.x;
-  const T u = __builtin_nontemporal_load(&rec[idx]);
-  const T jx = __builtin_nontemporal_load(&rec[g.plane + idx]);
-  const T jy = __builtin_nontemporal_load(&rec[2 * g.plane + idx]);
+  const T u = r[0], jx = r[1], jy = r[2];
   T du = T(0), dv = T(0);
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
@@ -515,31 +493,31 @@ __device__ __forceinline__ void tlm_collide_store(const Geometry& g, const NodeI
   }
   const T djx = fv[1] - fv[3] + fv[5] - fv[6] - fv[7] + fv[8];
   const T djy = fv[2] - fv[4] + fv[5] + fv[6] - fv[7] - fv[8];
-  T dax = du * (m.b00 * jx + m.b01 * jy) + u * (m.b00 * djx + m.b01 * djy);
-  T day = du * (m.b10 * jx + m.b11 * jy) + u * (m.b10 * djx + m.b11 * djy);
+  const T fx = dot2(m.b00, jx, m.b01, jy), dfx = dot2(m.b00, djx, m.b01, djy);
+  const T fy = dot2(m.b10, jx, m.b11, jy), dfy = dot2(m.b10, djx, m.b11, djy);
+  constexpr bool IMPL = VAR == kVarImplicit;
+  T dax = IMPL ? dot2(du, fx, u, dfx) : dot2(u, dfx, du, fx);
+  T day = IMPL ? dot2(du, fy, u, dfy) : dot2(u, dfy, du, fy);
   T dw = T(0);
   if (W3) {
-    const T kx = __builtin_nontemporal_load(&rec[3 * g.plane + idx]);
-    const T ky = __builtin_nontemporal_load(&rec[4 * g.plane + idx]);
+    const T kx = r[3], ky = r[4];
 #pragma unroll
     for (int i = 0; i < 9; ++i) dw += fw[i];
     const T dkx = fw[1] - fw[3] + fw[5] - fw[6] - fw[7] + fw[8];
     const T dky = fw[2] - fw[4] + fw[5] + fw[6] - fw[7] - fw[8];
-    dax += du * (m.bw00 * kx + m.bw01 * ky) + u * (m.bw00 * dkx + m.bw01 * dky);
-    day += du * (m.bw10 * kx + m.bw11 * ky) + u * (m.bw10 * dkx + m.bw11 * dky);
+    dax += du * dot2(m.bw00, kx, m.bw01, ky) + u * dot2(m.bw00, dkx, m.bw01, dky);
+    day += du * dot2(m.bw10, kx, m.bw11, ky) + u * dot2(m.bw10, dkx, m.bw11, dky);
   }
   const T dru = m.r_u * (T(1) - T(2) * u) * du;
   const T drv = m.a_uv * du - m.b_v * dv;
   T dphu, dphv;
   if (LAG) {
-    const T lu = first ? dru : dlag[idx];
-    const T lv = first ? drv : dlag[g.plane + idx];
+    const T lu = first ? dru : dlag[0];
+    const T lv = first ? drv : dlag[1];
     dphu = T(1.5) * dru - T(0.5) * lu;
     dphv = T(1.5) * drv - T(0.5) * lv + dc;
-    if (!(MASKED && (lm & 1u))) {
-      dlag[idx] = dru;
-      dlag[g.plane + idx] = drv;
-    }
+    dlag[0] = dru;
+    dlag[1] = drv;
   } else if (VAR == kVarImplicit) {
     dphu = T(0.5) * dru;
     dphv = T(0.5) * (drv + dc);
@@ -548,16 +526,13 @@ __device__ __forceinline__ void tlm_collide_store(const Geometry& g, const NodeI
     dphv = drv + dc;
   }
   T t1, t2;
-  relax(fu, du, m.u, t1, t2);
-  relax(fv, dv, m.v, t1, t2);
+  relax<true>(fu, du, m.u, t1, t2);
+  relax<true>(fv, dv, m.v, t1, t2);
   add_sources(fu, fv, dphu, dax, day, dphv);
   if (W3) {
-    relax(fw, dw, m.w, t1, t2);
+    relax<true>(fw, dw, m.w, t1, t2);
     add_kinetics(fw, m.a_w * du - m.b_w * dw);
   }
-  if (MASKED && (lm & 1u)) return;
-  store_state<T, MASKED>(g, n, fu, fv, dst, lm);
-  if (W3) store_w<T, MASKED>(g, n, fw, dst, lm);
 }
 
 // Continuous-adjoint step (Section 3.2.2: the continuous adjoint system of
@@ -568,17 +543,12 @@ __device__ __forceinline__ void tlm_collide_store(const Geometry& g, const NodeI
 //   q_s = div(D_v grad q) - b_v q - div(chi u C^T grad p)
 // p relaxes like u and q like v; the advection and the couplings are
 // scalar sources, the cross-diffusion of q a flux source, as the
-// chemotaxis of u in the forward.  Accumulates g += tau q (pre-collision).
-template <typename T, bool MASKED, bool FIRST>
-__device__ __forceinline__ void cadj_collide_store(const Geometry& g, const NodeIdx& n,
-                                                   const ModelCoef<T>& m, const CadjCoef<T>& cc,
-                                                   T fp[9], T fq[9], const T* __restrict__ rec,
-                                                   T* __restrict__ dst, double* __restrict__ gacc,
-                                                   unsigned lm) {
-  const size_t idx = n.r0 + n.x;
-  const T u = __builtin_nontemporal_load(&rec[idx]);
-  const T jvx = __builtin_nontemporal_load(&rec[g.plane + idx]);
-  const T jvy = __builtin_nontemporal_load(&rec[2 * g.plane + idx]);
+// chemotaxis of u in the forward.  Returns tau q (pre-collision), the step's
+// share of the time integral.
+template <typename T>
+__device__ __forceinline__ T cadj_collide(const ModelCoef<T>& m, const CadjCoef<T>& cc, T fp[9],
+                                          T fq[9], const T r[5]) {
+  const T u = r[0], jvx = r[1], jvy = r[2];
   T P = T(0), Qv = T(0);
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
@@ -587,21 +557,14 @@ __device__ __forceinline__ void cadj_collide_store(const Geometry& g, const Node
   }
   const T jpx = fp[1] - fp[3] + fp[5] - fp[6] - fp[7] + fp[8];
   const T jpy = fp[2] - fp[4] + fp[5] + fp[6] - fp[7] - fp[8];
-  const bool solid = MASKED && (lm & 1u);
-  if (!solid) {
-    if (FIRST)
-      gacc[idx] = double(Qv);
-    else
-      gacc[idx] += double(Qv);
-  }
-  const T adv = jpx * (cc.m00 * jvx + cc.m01 * jvy) + jpy * (cc.m10 * jvx + cc.m11 * jvy);
-  const T php = m.r_u * (T(1) - T(2) * u) * P + m.a_uv * Qv + adv;
+  const T adv = dot2(jpx, dot2(cc.m00, jvx, cc.m01, jvy), jpy, dot2(cc.m10, jvx, cc.m11, jvy));
+  const T php = dot2(m.a_uv, Qv, m.r_u * (T(1) - T(2) * u), P) + adv;
   const T phq = -m.b_v * Qv;
-  const T aqx = u * (cc.q00 * jpx + cc.q01 * jpy);
-  const T aqy = u * (cc.q10 * jpx + cc.q11 * jpy);
+  const T aqx = u * dot2(cc.q00, jpx, cc.q01, jpy);
+  const T aqy = u * dot2(cc.q10, jpx, cc.q11, jpy);
   T t1, t2;
-  relax(fp, P, m.u, t1, t2);
-  relax(fq, Qv, m.v, t1, t2);
+  relax<true>(fp, P, m.u, t1, t2);
+  relax<true>(fq, Qv, m.v, t1, t2);
   add_sources(fp, fq, php, T(0), T(0), phq);
   // flux source of q: 3 w_i e_i . a_q
   const T x3 = aqx * T(1.0 / 3.0), y3 = aqy * T(1.0 / 3.0);
@@ -614,62 +577,20 @@ __device__ __forceinline__ void cadj_collide_store(const Geometry& g, const Node
   fq[6] += y12 - x12;
   fq[7] -= x12 + y12;
   fq[8] += x12 - y12;
-  if (solid) return;
-  store_state<T, MASKED>(g, n, fp, fq, dst, lm);
-}
-
-// One forward step (eq:LBE with S, PhiS, MF, MC) at node n.  Recording is a
-// run-time flag (rec != null), not a template parameter: the recorded and
-// the plain steps then run the same machine code, so a checkpointed
-// recomputation reproduces the recorded trajectory bit for bit.
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST, int VAR = kVarFirst>
-__device__ __forceinline__ void forward_node(
-    const Geometry& g, const NodeIdx& n, const ModelCoef<T>& m, const T* __restrict__ src, T* __restrict__ dst,
-    const T* __restrict__ u0, const T* __restrict__ v0,
-    const T* __restrict__ ctrl, T* __restrict__ rec, T* __restrict__ lag = nullptr,
-    const T* __restrict__ w0 = nullptr) {
-  unsigned lm = 0;
-  if (MASKED) {
-    const unsigned flag = wave_flag(g, n);
-    if (flag == 2u) return;  // wavefront inside a solid region
-    lm = link_of(g, flag, n.r0 + n.x);
-  }
-  // a solid node of a mixed wavefront loads nothing and collides zeros: it
-  // stores no state (its slots hold the neighbours' wall stores) but takes
-  // part in the record stores
-  const bool solid = MASKED && (lm & 1u);
-  T fu[9], fv[9], c = T(0);
-  if (solid) {
-#pragma unroll
-    for (int i = 0; i < 9; ++i) fu[i] = fv[i] = T(0);
-  } else {
-    forward_gather<T, PERIODIC, FIRST>(g, n, m, src, u0, v0, ctrl, fu, fv, c);
-  }
-  if (VAR == kVarThree) {
-    T fw[9];
-    if (solid) {
-#pragma unroll
-      for (int i = 0; i < 9; ++i) fw[i] = T(0);
-    } else {
-      gather_w<T, PERIODIC, FIRST>(g, n, m, src, w0, fw);
-    }
-    forward_collide_store<T, MASKED, VAR>(g, n, m, fu, fv, c, dst, rec, lm, lag, FIRST, fw);
-  } else {
-    forward_collide_store<T, MASKED, VAR>(g, n, m, fu, fv, c, dst, rec, lm, lag, FIRST);
-  }
+  return Qv;
 }
 
 // Terminal streaming: the state after the last step and its sums.  IMPL
 // (implicit characteristic difference): the streamed values are g; Theta^N
 // comes from the node solve and the state is phi^N = g + (tau/2) w Phi.
 // W3: the third species' populations are also streamed into the state.
-template <typename T, bool PERIODIC, bool MASKED, bool IMPL = false, bool W3 = false>
+template <typename T, bool IMPL = false, bool W3 = false>
 __device__ __forceinline__ void finalize_node(
     const Geometry& g, const NodeIdx& n, const T* __restrict__ src, T* __restrict__ state,
     T* __restrict__ uN, T* __restrict__ vN, const ModelCoef<T>* m = nullptr,
     const T* __restrict__ ctrl = nullptr) {
   const size_t idx = n.r0 + n.x;
-  const bool solid = MASKED && (link_of(g, wave_flag(g, n), idx) & 1u);
+  const bool solid = g.masked && (link_of(g, wave_flag(g, n), idx) & 1u);
   T fu[9], fv[9];
   if (solid) {
 #pragma unroll
@@ -677,9 +598,8 @@ __device__ __forceinline__ void finalize_node(
   } else {
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-      const size_t o = pull_src<PERIODIC>(n, i, g.plane);
-      fu[i] = src[o];
-      fv[i] = src[9 * g.plane + o];
+      fu[i] = *pull_at<kAny>(src + size_t(i) * g.plane, n, i);
+      fv[i] = *pull_at<kAny>(src + size_t(9 + i) * g.plane, n, i);
     }
   }
   T u = T(0), v = T(0);
@@ -707,7 +627,7 @@ __device__ __forceinline__ void finalize_node(
 #pragma unroll
       for (int i = 0; i < 9; ++i)
         state[size_t(18 + i) * g.plane + idx] =
-            solid ? T(0) : src[18 * g.plane + pull_src<PERIODIC>(n, i, g.plane)];
+            solid ? T(0) : *pull_at<kAny>(src + size_t(18 + i) * g.plane, n, i);
     }
   }
 }
@@ -737,169 +657,143 @@ __device__ __forceinline__ void finalize_node(
 // a_w, w's own through -b_w; the repulsive flux u Bw j_w adds
 // p . (Bw j_w) to u's and e_i . (u Bw^T p) to w's.
 //
-// adjoint_node = adjoint_gather + adjoint_update.
+// adjoint_gather loads, adjoint_collide does the arithmetic.
 //
-// Adjoint gather of node n (FIRST: the terminal seeds), the half of the
-// node update that loads; adjoint_update finishes it.
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST, int VAR = kVarFirst>
+// Adjoint gather of node n from the state of the step after (src), or
+// (FIRST) the terminal seeds.
+template <Lanes A, bool WALLS, int VAR, bool FIRST, typename T>
 __device__ __forceinline__ void adjoint_gather(const Geometry& g, const NodeIdx& n,
                                                const T* __restrict__ src,
                                                const T* __restrict__ seed_u,
                                                const T* __restrict__ seed_v, unsigned lm,
                                                T nu[9], T nv[9], T nw[9]) {
-  const size_t idx = n.r0 + n.x;
+  constexpr bool W3 = VAR == kVarThree;
   // reverse streaming: nu_i(x) = lambda_i(x + e_i), or lambda_opp(i)(x)
   // when x + e_i is a wall (exact transpose of the pull with bounce-back)
   if (FIRST) {
     // terminal condition lambda_i^N = seed for every i (psi(T) = dI0/dphi);
     // the seed fields carry no wall slots, so walls are tested here
+    const T own_u = *own_at<A>(seed_u, n), own_v = seed_v ? *own_at<A>(seed_v, n) : T(0);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-      const bool wall = (!PERIODIC && push_outside(n, i)) ||
-                        (MASKED && ((lm >> opp(i)) & 1u));
-      const size_t o = wall ? idx : push_off(n, i);
-      nu[i] = seed_u[o];
-      nv[i] = seed_v ? seed_v[o] : T(0);
+      const bool wall = WALLS && i > 0 && ((lm >> opp(i)) & 1u);
+      const T su = *push_at<A>(seed_u, n, i), sv = seed_v ? *push_at<A>(seed_v, n, i) : T(0);
+      nu[i] = wall ? own_u : su;
+      nv[i] = wall ? own_v : sv;
+      if (W3) nw[i] = T(0);
     }
   } else {
-    const T* sv = src + 9 * g.plane;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-      const size_t o = gather_src<PERIODIC>(n, i, g.plane);
-      nu[i] = src[o];
-      nv[i] = sv[o];
-    }
-  }
-  constexpr bool W3 = VAR == kVarThree;
-  if (W3) {
-    if (FIRST) {
-#pragma unroll
-      for (int i = 0; i < 9; ++i) nw[i] = T(0);
-    } else {
-      const T* sw = src + 18 * g.plane;
-#pragma unroll
-      for (int i = 0; i < 9; ++i)
-        nw[i] = sw[gather_src<PERIODIC>(n, i, g.plane)];
+      nu[i] = *push_at<A>(src + size_t(i) * g.plane, n, i);
+      nv[i] = *push_at<A>(src + size_t(9 + i) * g.plane, n, i);
+      if (W3) nw[i] = *push_at<A>(src + size_t(18 + i) * g.plane, n, i);
     }
   }
 }
 
-// The rest of the adjoint node update after adjoint_gather: sources,
-// collision, gradient accumulation and the stores.
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST, bool LAST, int VAR = kVarFirst>
-__device__ __forceinline__ void adjoint_update(
-    const Geometry& g, const NodeIdx& n, const ModelCoef<T>& m, T nu[9], T nv[9], T nw[9],
-    T* __restrict__ dst, const T* __restrict__ rec, double* __restrict__ gacc,
-    T* __restrict__ adj_u0, T* __restrict__ adj_v0, T* __restrict__ mu, bool step0,
-    unsigned lm) {
-  const size_t idx = n.r0 + n.x;
+// Transposed flux source: f_i += e_i . (u q).  Of the two products in u q_x +-
+// u q_y the one along x is fused where there are walls, the other without
+// (either is as near the exact value; each kind of lattice keeps its bits).
+template <bool WALLS, typename T>
+__device__ __forceinline__ void add_flux_adjoint(T f[9], T u, T qx, T qy) {
+  f[1] += u * qx;
+  f[2] += u * qy;
+  f[3] -= u * qx;
+  f[4] -= u * qy;
+  const T sum = WALLS ? dot2(u, qx, u, qy) : dot2(u, qy, u, qx);
+  const T dif = WALLS ? dot2(u, qx, -u, qy) : dot2(-u, qy, u, qx);
+  f[5] += sum;
+  f[6] -= dif;
+  f[7] -= sum;
+  f[8] += dif;
+}
+
+// The adjoint collision in registers: nu, nv (nw) in place; r is the
+// recorded u, j_v (j_w) of the step; mu (LAG) the adjoint of the stored
+// kinetics, from the step after to this one; `first` marks step N-1, `step0`
+// step 0.  Returns the step's share of the gradient, dF_v,i/dc = tau w_i
+// (the implicit form: see above).
+template <typename T, bool WALLS, int VAR>
+__device__ __forceinline__ T adjoint_collide(const ModelCoef<T>& m, T nu[9], T nv[9], T nw[9],
+                                             const T r[5], T mu[2], bool first, bool step0) {
   constexpr bool W3 = VAR == kVarThree;
-  // weighted sums: sigma = w . nu, p = (tau/Cs^2) sum_i w_i nu_u,i e_i
-  const T su_ = T(4.0 / 9.0) * nu[0] +
-                T(1.0 / 9.0) * (nu[1] + nu[2] + nu[3] + nu[4]) +
-                T(1.0 / 36.0) * (nu[5] + nu[6] + nu[7] + nu[8]);
-  const T sv_ = T(4.0 / 9.0) * nv[0] +
-                T(1.0 / 9.0) * (nv[1] + nv[2] + nv[3] + nv[4]) +
-                T(1.0 / 36.0) * (nv[5] + nv[6] + nv[7] + nv[8]);
-  const T px = T(1.0 / 3.0) * (nu[1] - nu[3]) +
-               T(1.0 / 12.0) * (nu[5] - nu[6] - nu[7] + nu[8]);
-  const T py = T(1.0 / 3.0) * (nu[2] - nu[4]) +
-               T(1.0 / 12.0) * (nu[5] + nu[6] - nu[7] - nu[8]);
   constexpr bool LAG = VAR == kVarExplicit;
   constexpr bool IMPL = VAR == kVarImplicit;
-  // gradient w.r.t. the control on v: dF_v,i/dc = tau w_i (the implicit
-  // form adds its share below)
-  if (!IMPL) {
-    if (FIRST)
-      gacc[idx] = double(sv_);
-    else
-      gacc[idx] += double(sv_);
-  }
-  // recorded forward quantities of step n
-  const T u = __builtin_nontemporal_load(&rec[idx]);
-  const T jx = __builtin_nontemporal_load(&rec[g.plane + idx]);
-  const T jy = __builtin_nontemporal_load(&rec[2 * g.plane + idx]);
-  const T bjx = m.b00 * jx + m.b01 * jy;
-  const T bjy = m.b10 * jx + m.b11 * jy;
+  // weighted sums: sigma = w . nu, p = (tau/Cs^2) sum_i w_i nu_u,i e_i
+  const T su_ = weighted(nu), sv_ = weighted(nv);
+  const T px = dot2(T(1.0 / 3.0), nu[1] - nu[3],
+                    T(1.0 / 12.0), nu[5] - nu[6] - nu[7] + nu[8]);
+  const T py = dot2(T(1.0 / 3.0), nu[2] - nu[4],
+                    T(1.0 / 12.0), nu[5] + nu[6] - nu[7] - nu[8]);
+  const T u = r[0], jx = r[1], jy = r[2];
+  const T bjx = dot2(m.b00, jx, m.b01, jy);
+  const T bjy = dot2(m.b10, jx, m.b11, jy);
   // transposed sources: d(tau S_u + tau Phi_u)/dphi_u is rank one along 1,
   // d(tau S_u)/dphi_v = (tau/Cs^2) diag(w) E u B E^T, dPhi_v/dphi = (a, -b).
   T rho_u = su_, rho_v = sv_;
   if (LAG) {
-    const T mu_u = FIRST ? T(0) : mu[idx];
-    const T mu_v = FIRST ? T(0) : mu[g.plane + idx];
+    const T mu_u = first ? T(0) : mu[0];
+    const T mu_v = first ? T(0) : mu[1];
     if (step0) {
       rho_u = su_ + mu_u;
       rho_v = sv_ + mu_v;
     } else {
       rho_u = T(1.5) * su_ + mu_u;
       rho_v = T(1.5) * sv_ + mu_v;
-      mu[idx] = T(-0.5) * su_;
-      mu[g.plane + idx] = T(-0.5) * sv_;
+      mu[0] = T(-0.5) * su_;
+      mu[1] = T(-0.5) * sv_;
     }
   }
-  const T qx = u * (m.b00 * px + m.b10 * py);
-  const T qy = u * (m.b01 * px + m.b11 * py);
-  T wu, wv;
+  const T qx = dot2(m.b00, px, m.b10, py);
+  const T qy = dot2(m.b01, px, m.b11, py);
+  T wu, wv, share = sv_;
   if (!IMPL) {
-    T cu = rho_u * m.r_u * (T(1) - T(2) * u) + px * bjx + py * bjy +
-           rho_v * m.a_uv;
+    T cu = dot2(rho_u * m.r_u, T(1) - T(2) * u, px, bjx) + py * bjy + rho_v * m.a_uv;
     const T cv = -rho_v * m.b_v;
     if (W3) {
-      const T kx = __builtin_nontemporal_load(&rec[3 * g.plane + idx]);
-      const T ky = __builtin_nontemporal_load(&rec[4 * g.plane + idx]);
-      const T sw_ = T(4.0 / 9.0) * nw[0] + T(1.0 / 9.0) * (nw[1] + nw[2] + nw[3] + nw[4]) +
-                    T(1.0 / 36.0) * (nw[5] + nw[6] + nw[7] + nw[8]);
-      cu += px * (m.bw00 * kx + m.bw01 * ky) + py * (m.bw10 * kx + m.bw11 * ky) +
+      const T kx = r[3], ky = r[4];
+      const T sw_ = weighted(nw);
+      cu += px * dot2(m.bw00, kx, m.bw01, ky) + py * dot2(m.bw10, kx, m.bw11, ky) +
             sw_ * m.a_w;
       T a1, a2;
-      relax(nw, T(0), m.wt, a1, a2);
-      const T ww = m.w.e_eq * a1 + m.w.eps_eq * a2 - sw_ * m.b_w;
-      const T rx = u * (m.bw00 * px + m.bw10 * py);
-      const T ry = u * (m.bw01 * px + m.bw11 * py);
+      relax<false>(nw, T(0), m.wt, a1, a2);
+      const T ww = dot2(m.w.eps_eq, a2, m.w.e_eq, a1) - sw_ * m.b_w;
 #pragma unroll
       for (int i = 0; i < 9; ++i) nw[i] += ww;
-      nw[1] += rx;
-      nw[2] += ry;
-      nw[3] -= rx;
-      nw[4] -= ry;
-      nw[5] += rx + ry;
-      nw[6] += ry - rx;
-      nw[7] -= rx + ry;
-      nw[8] += rx - ry;
+      add_flux_adjoint<WALLS>(nw, u, dot2(m.bw00, px, m.bw10, py), dot2(m.bw01, px, m.bw11, py));
     }
     // adjoint collision: nu - C^T nu + 1 * weq^T C^T nu  (AEDs with O = 1 weq^T)
     T a1, a2;
-    relax(nu, T(0), m.ut, a1, a2);
-    wu = m.u.e_eq * a1 + m.u.eps_eq * a2 + cu;
-    relax(nv, T(0), m.vt, a1, a2);
-    wv = m.v.e_eq * a1 + m.v.eps_eq * a2 + cv;
+    relax<false>(nu, T(0), m.ut, a1, a2);
+    wu = dot2(m.u.eps_eq, a2, m.u.e_eq, a1) + cu;
+    relax<false>(nv, T(0), m.vt, a1, a2);
+    wv = dot2(m.v.eps_eq, a2, m.v.e_eq, a1) + cv;
   } else {
     T a1, a2;
-    relax(nu, T(0), m.ut, a1, a2);
-    const T eu = m.u.e_eq * a1 + m.u.eps_eq * a2;
-    relax(nv, T(0), m.vt, a1, a2);
-    const T ev = m.v.e_eq * a1 + m.v.eps_eq * a2;
+    relax<false>(nu, T(0), m.ut, a1, a2);
+    const T eu = dot2(m.u.eps_eq, a2, m.u.e_eq, a1);
+    relax<false>(nv, T(0), m.vt, a1, a2);
+    const T ev = dot2(m.v.eps_eq, a2, m.v.e_eq, a1);
     T ku = T(0.5) * su_, kv = T(0.5) * sv_;
     if (!step0) {
       // w . A^T nu = w . (relaxed nu) + e (sum_i w_i = 1)
-      const T tu = T(4.0 / 9.0) * nu[0] + T(1.0 / 9.0) * (nu[1] + nu[2] + nu[3] + nu[4]) +
-                   T(1.0 / 36.0) * (nu[5] + nu[6] + nu[7] + nu[8]) + eu;
-      const T tv = T(4.0 / 9.0) * nv[0] + T(1.0 / 9.0) * (nv[1] + nv[2] + nv[3] + nv[4]) +
-                   T(1.0 / 36.0) * (nv[5] + nv[6] + nv[7] + nv[8]) + ev;
+      const T tu = weighted(nu) + eu;
+      const T tv = weighted(nv) + ev;
       ku = T(0.5) * (tu + su_);
       kv = T(0.5) * (tv + sv_);
     }
-    const T ubar = ku * m.r_u * (T(1) - T(2) * u) + kv * m.a_uv + px * bjx + py * bjy;
+    const T ubar = dot2(m.a_uv, kv, ku * m.r_u, T(1) - T(2) * u) + px * bjx + py * bjy;
     const T vbar = -kv * m.b_v;
-    T gu = ubar, gv = vbar, gc = kv;
+    T gu = ubar, gv = vbar;
+    share = kv;
     if (!step0) {
       const T beta = T(1) / (T(1) + T(0.5) * m.b_v);
       const T alpha = T(1) / (T(1) - T(0.5) * m.r_u * (T(1) - T(2) * u));
       gv = beta * vbar;
       gu = alpha * (ubar + T(0.5) * m.a_uv * gv);
-      gc = kv * beta;
+      share = kv * beta;
     }
-    gacc[idx] += double(gc);  // initialised by the terminal transform
     wu = eu + gu;
     wv = ev + gv;
   }
@@ -908,87 +802,15 @@ __device__ __forceinline__ void adjoint_update(
     nu[i] += wu;
     nv[i] += wv;
   }
-  nv[1] += qx;
-  nv[2] += qy;
-  nv[3] -= qx;
-  nv[4] -= qy;
-  nv[5] += qx + qy;
-  nv[6] += qy - qx;
-  nv[7] -= qx + qy;
-  nv[8] += qx - qy;
-  if (LAST) {
-    // transpose of phi_i^0 = w_i Theta_0
-    if (adj_u0)
-      adj_u0[idx] = m.u.w_rest * nu[0] +
-                    m.u.w_axis * (nu[1] + nu[2] + nu[3] + nu[4]) +
-                    m.u.w_diag * (nu[5] + nu[6] + nu[7] + nu[8]);
-    if (adj_v0)
-      adj_v0[idx] = m.v.w_rest * nv[0] +
-                    m.v.w_axis * (nv[1] + nv[2] + nv[3] + nv[4]) +
-                    m.v.w_diag * (nv[5] + nv[6] + nv[7] + nv[8]);
-  } else if (dst) {
-    T* dv = dst + 9 * g.plane;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      __builtin_nontemporal_store(nu[i], &dst[size_t(i) * g.plane + idx]);
-      __builtin_nontemporal_store(nv[i], &dv[size_t(i) * g.plane + idx]);
-    }
-    if (W3) {
-      T* dw = dst + 18 * g.plane;
-#pragma unroll
-      for (int i = 0; i < 9; ++i)
-        __builtin_nontemporal_store(nw[i], &dw[size_t(i) * g.plane + idx]);
-    }
-    if (MASKED && (lm & 0x1FEu)) {
-      // wall stores of the adjoint: the next gather in direction i at x
-      // reads plane i at the solid node x + e_i and must find lambda_opp(i)(x)
-#pragma unroll
-      for (int i = 1; i < 9; ++i) {
-        if ((lm >> opp(i)) & 1u) {
-          const size_t o = size_t(i) * g.plane + push_off(n, i);
-          dst[o] = nu[opp(i)];
-          dv[o] = nv[opp(i)];
-          if (W3) dst[18 * g.plane + o] = nw[opp(i)];
-        }
-      }
-    }
-  }
+  add_flux_adjoint<WALLS>(nv, u, qx, qy);
+  return share;
 }
 
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST, bool LAST, int VAR = kVarFirst>
-__device__ __forceinline__ void adjoint_node(
-    const Geometry& g, const NodeIdx& n, const ModelCoef<T>& m, const T* __restrict__ src, T* __restrict__ dst,
-    const T* __restrict__ seed_u, const T* __restrict__ seed_v,
-    const T* __restrict__ rec, double* __restrict__ gacc,
-    T* __restrict__ adj_u0, T* __restrict__ adj_v0, T* __restrict__ mu = nullptr,
-    bool step0 = false) {
-  const size_t idx = n.r0 + n.x;
-  unsigned lm = 0;
-  if (MASKED) {
-    const unsigned flag = wave_flag(g, n);
-    if (FIRST || LAST) {
-      // single steps: resolve solid nodes up front, they own outputs
-      lm = g.link[idx];
-      if (lm & 1u) {
-        if (FIRST) gacc[idx] = 0.0;
-        if (LAST) {
-          if (adj_u0) adj_u0[idx] = T(0);
-          if (adj_v0) adj_v0[idx] = T(0);
-        }
-        return;
-      }
-    } else {
-      if (flag == 2u) return;  // wavefront inside a solid region
-      lm = link_of(g, flag, idx);
-      // a solid node of a mixed wavefront: no update (taking part in the
-      // gradient's read-modify-write with zeros measured 4% slower)
-      if (lm & 1u) return;
-    }
-  }
-  T nu[9], nv[9], nw[9];
-  adjoint_gather<T, PERIODIC, MASKED, FIRST, VAR>(g, n, src, seed_u, seed_v, lm, nu, nv, nw);
-  adjoint_update<T, PERIODIC, MASKED, FIRST, LAST, VAR>(g, n, m, nu, nv, nw, dst, rec, gacc,
-                                                        adj_u0, adj_v0, mu, step0, lm);
+// Transpose of phi_i^0 = w_i Theta_0: the sensitivity to an initial field.
+template <typename T>
+__device__ __forceinline__ T adjoint_initial(const SpeciesCoef<T>& c, const T f[9]) {
+  return dot2(c.w_rest, f[0], c.w_axis, f[1] + f[2] + f[3] + f[4]) +
+         c.w_diag * (f[5] + f[6] + f[7] + f[8]);
 }
 
 // ------------------------------------------------------------ reductions

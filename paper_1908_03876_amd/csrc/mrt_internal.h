@@ -52,24 +52,41 @@ struct Geometry {
 void launch_build_link(const Geometry& g, int periodic, const uint8_t* mask,
                        uint16_t* link_out, uint32_t* wflag_out, hipStream_t s);
 
+// How the next time steps of a sweep run: `steps` of them in one launch, by
+// work-groups that own regions of rx x ry nodes.
+struct StepPlan {
+  int rx, ry, steps;
+};
+
+// Plan for a sweep that has `left` steps to go (elem: bytes per value; one:
+// one step a launch, for variant 2 with a single buffer of kinetics).
+StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool one);
+
+// The regions of a launch: ntx across, ntiles in all, `steps` steps each.
+struct TileGrid {
+  int steps, ntx, ntiles;
+};
+
 template <typename T>
 struct FwdLaunch {
   const T* src;      // post-collision state of step n-1, or null (first)
-  T* dst;            // post-collision state of step n (with wall slots)
+  T* dst;            // post-collision state of the last step (with wall slots)
   const T* u0;       // initial fields (first step only)
   const T* v0;
   const T* ctrl;     // control c(x)
-  T* rec;            // record slot [3][plane] (u, j_vx, j_vy) or null
+  T* rec;            // record slot [3][plane] (u, j_vx, j_vy) of step n or null
+  size_t rec_stride; // elements from one step's slot to the next one's
   int variant;       // scheme variant: 1 first-order source, 2 explicit,
                      // 3 implicit characteristic difference, 4 three species
-  T* lag;            // variant 2: kinetics of the previous step [2][plane],
-                     // overwritten with this step's
+  const T* lag;      // variant 2: kinetics of the step before n [2][plane]
+  T* lag_out;        // and of the launch's last step (another buffer, unless the
+                     // launch takes one step)
   const T* w0;       // variant 4: initial w (first step only; null = 0)
 };
 
 template <typename T>
-void launch_forward_step(const Geometry& g, const ModelCoef<T>& m,
-                         const FwdLaunch<T>& a, hipStream_t s);
+void launch_forward(const Geometry& g, const ModelCoef<T>& m, const FwdLaunch<T>& a,
+                    const StepPlan& p, hipStream_t s);
 
 // Terminal streaming: state (may be null), u^N, v^N (may be null).  With m
 // given (implicit characteristic difference), Theta^N comes from the node
@@ -96,23 +113,23 @@ void launch_implicit_tlm_final(const Geometry& g, const ModelCoef<T>& m, const T
 template <typename T>
 struct AdjLaunch {
   const T* src;      // adjoint state of step n+1, or null (terminal seed)
-  T* dst;            // adjoint state of step n, or null (last step)
+  T* dst;            // adjoint state of the launch's last step, or null (step 0)
   const T* seed_u;   // terminal condition (first step only)
   const T* seed_v;   // may be null (= 0)
   const T* rec;      // record slot of step n
-  double* g;         // gradient accumulator
-  T* adj_u0;         // dJ/du0 (last step only, may be null)
+  size_t rec_stride; // elements from one step's slot to the next one's
+  double* g;         // gradient accumulator (initialised where src is null)
+  T* adj_u0;         // dJ/du0 (null unless the launch ends at step 0)
   T* adj_v0;
-  int first;         // 1: step N-1 (reads seeds, initialises g)
-  int last;          // 1: step 0 and adj_u0/adj_v0 requested
   int variant;       // scheme variant (as FwdLaunch)
-  T* mu;             // variant 2: adjoint of the stored kinetics [2][plane]
-  int step0;         // 1: step 0
+  const T* mu;       // variant 2: adjoint of the stored kinetics [2][plane]
+  T* mu_out;         // and after the launch (as lag_out)
+  int step;          // n, the first step of the launch
 };
 
 template <typename T>
-void launch_adjoint_step(const Geometry& g, const ModelCoef<T>& m,
-                         const AdjLaunch<T>& a, hipStream_t s);
+void launch_adjoint(const Geometry& g, const ModelCoef<T>& m, const AdjLaunch<T>& a,
+                    const StepPlan& p, hipStream_t s);
 
 // Coefficients of the continuous-adjoint system (p adjoint of u, q of v):
 // advection chi (C grad v) . grad p = j_p^T M j_v and the cross-diffusion
@@ -126,33 +143,35 @@ struct CadjCoef {
 template <typename T>
 struct CadjLaunch {
   const T* src;      // continuous-adjoint state of the previous reversed step, or null
-  T* dst;            // state after this reversed step (with wall slots)
+  T* dst;            // state after the launch's last step (with wall slots)
   const T* seed_u;   // p at s = 0 (first reversed step only)
   const T* rec;      // record slot of the forward step at this time
-  double* g;         // time integral of q
-  int first;         // 1: first reversed step (initialises g)
+  size_t rec_stride; // elements from one step's slot to the next one's
+  double* g;         // time integral of q (initialised where src is null)
 };
 
 template <typename T>
-void launch_cadj_step(const Geometry& g, const ModelCoef<T>& m, const CadjCoef<T>& cc,
-                      const CadjLaunch<T>& a, hipStream_t s);
+void launch_cadj(const Geometry& g, const ModelCoef<T>& m, const CadjCoef<T>& cc,
+                 const CadjLaunch<T>& a, const StepPlan& p, hipStream_t s);
 
 template <typename T>
 struct TlmLaunch {
   const T* src;      // perturbation of step n-1 (post-collision), or null (n = 0)
-  T* dst;            // perturbation after step n (with wall slots)
+  T* dst;            // perturbation after the launch's last step (with wall slots)
   const T* du0;      // initial perturbations (n = 0 only; null = 0)
   const T* dv0;
   const T* dc;       // control perturbation (null = 0)
   const T* rec;      // record slot of step n (forward u, j_vx, j_vy)
+  size_t rec_stride; // elements from one step's slot to the next one's
   int variant;       // scheme variant (as FwdLaunch)
-  T* dlag;           // variant 2: perturbed kinetics of the previous step
+  const T* dlag;     // variant 2: perturbed kinetics of the previous step
                      // [2][plane]
+  T* dlag_out;       // and of the launch's last step (as lag_out)
 };
 
 template <typename T>
-void launch_tlm_step(const Geometry& g, const ModelCoef<T>& m, const TlmLaunch<T>& a,
-                     hipStream_t s);
+void launch_tlm(const Geometry& g, const ModelCoef<T>& m, const TlmLaunch<T>& a,
+                const StepPlan& p, hipStream_t s);
 
 // result[0] = sum over fluid nodes of x * y (double), result[4] = number of
 // non-finite products.

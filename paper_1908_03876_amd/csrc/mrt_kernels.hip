@@ -5,30 +5,31 @@
 // BC11, the relaxation matrix Pi and D = d Cs^2 tau (K^-1 - I/2)) and
 // Section 3.2.1 (LIBEG, CAE, AEDs, RFS1, CAEL, gradientLattice).
 //
-// Design (memory-bound stencil, no MFMA):
-//  * One thread per lattice node, 256-thread blocks along x; every
-//    population is read once and written once per step in SoA planes, so
-//    each wavefront issues 18 coalesced 256-byte loads and 18 stores.
-//  * The kernel stores post-collision states and pulls: node x gathers
-//    phi*_i(x - e_i) (or its own phi*_opp(i) when x - e_i is solid, halfway
-//    bounce-back).  Collision runs in registers in moment space; M0^-1 is
-//    applied as M0^T with the row norms folded into the rates.
+// Design (a stencil of about 240 vector instructions a node and step, no
+// contraction, so no MFMA):
+//  * One thread per lattice node; populations live in SoA planes, so each
+//    wavefront reads and writes whole rows of a plane.
+//  * The state between launches is post-collision, and the kernels pull:
+//    node x gathers phi*_i(x - e_i) (or its own phi*_opp(i) at a wall,
+//    halfway bounce-back).  Collision runs in registers in moment space;
+//    M0^-1 is applied as M0^T with the row norms folded into the rates.
 //  * The adjoint is a gather too: nu_i(x) = lambda_i(x + e_i), or
-//    lambda_opp(i)(x) when x + e_i is solid (exact transpose of the pull).
-//  * Work-group order is remapped so that each of the 8 XCDs walks a
-//    contiguous band of rows (its L2 keeps the shifted-row and edge lines).
-//  * State planes and the trajectory record are streamed with non-temporal
-//    stores (and non-temporal loads in the adjoint): they are touched once
-//    per sweep and would only evict the link mask, control and gradient.
-//  * Walls cost no test in the pull: a node whose population streams into
-//    a solid neighbour also parks it in that neighbour's (otherwise unused)
-//    slot of the opposite plane, where the next pull finds it.
+//    lambda_opp(i)(x) when x + e_i is a wall (exact transpose of the pull).
+//  * One step per launch is bound by HBM (the AMRT step's 172 B a node at 68%
+//    of 8 TB/s: 125 us at 2048^2); so a launch takes several steps in a region
+//    of the lattice held in registers, streaming through LDS, and reads and
+//    writes the state once for all of them (see "time-step kernels").
+//  * Regions are dealt so that each of the 8 XCDs walks a contiguous band of
+//    rows: its L2 serves the rows that neighbouring regions share.
+//  * Walls cost no test in the pull: see the wall slots in mrt_device.h.
 //  * Reductions: wave shuffles (64 lanes), LDS across waves, one partial per
 //    block, then a single-block pass in fixed order (deterministic).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "mrt_device.h"
 #include "mrt_internal.h"
@@ -40,9 +41,8 @@ using namespace dev;
 
 // -------------------------------------------------------------- link mask
 
-// bit 0: node solid; bit i (1..8): x - e_i is a solid node of the lattice
-// (wrapped when periodic; outside a non-periodic lattice is not a node and
-// is handled from the coordinates).
+// bit 0: node solid; bit i (1..8): x - e_i is solid (wrapped when periodic)
+// or outside a non-periodic lattice.
 __global__ void build_link_kernel(Geometry g, int periodic,
                                   const uint8_t* __restrict__ mask,
                                   uint16_t* __restrict__ link,
@@ -56,7 +56,10 @@ __global__ void build_link_kernel(Geometry g, int periodic,
   for (int i = 0; i < 9; ++i) {
     int xs = x - ex[i], ys = y - ey[i];
     const bool out = xs < 0 || ys < 0 || xs >= g.nx || ys >= g.ny;
-    if (out && !periodic) continue;
+    if (out && !periodic) {
+      bits |= uint16_t(1u << i);
+      continue;
+    }
     xs = (xs + g.nx) % g.nx;
     ys = (ys + g.ny) % g.ny;
     if (mask[size_t(ys) * g.pitch + xs]) bits |= uint16_t(1u << i);
@@ -69,40 +72,341 @@ __global__ void build_link_kernel(Geometry g, int periodic,
     wflag[size_t(y) * g.nsx + (x >> 6)] = fluid == 0ull ? 2u : (any != 0ull);
 }
 
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST, int VAR>
-__global__ __launch_bounds__(kBlock) void forward_step_kernel(
-    Geometry g, ModelCoef<T> m, const T* __restrict__ src, T* __restrict__ dst,
-    const T* __restrict__ u0, const T* __restrict__ v0,
-    const T* __restrict__ ctrl, T* __restrict__ rec, T* __restrict__ lag,
-    const T* __restrict__ w0) {
-  NodeIdx n;
-  if (!node_of_block(g, n)) return;
-  forward_node<T, PERIODIC, MASKED, FIRST, VAR>(g, n, m, src, dst, u0, v0, ctrl, rec, lag, w0);
+// ------------------------------------------------------- time-step kernels
+//
+// A launch advances several time steps.  A work-group owns a region of
+// RX x RY nodes, one per thread; the first step gathers from memory, the
+// steps in between exchange their populations through LDS (u and v of a
+// direction side by side, one 8- or 16-byte access each), and the last one
+// stores.  With K steps the K - 1 outer rings of the region go stale one
+// after the other: they recompute what the neighbouring regions own, so a
+// region stores the RX - 2(K-1) by RY - 2(K-1) nodes inside them, and a
+// wavefront whose rows are stale leaves the work to the others.
+//
+// The wide regions are 64 x 16 (a wavefront is one row, so rows are scalar
+// addresses) for the 72 bytes a node of two species in FP32, 1024 threads and
+// two work-groups a compute unit: 64 registers a thread, 67 to 75 KB of LDS.
+// Twice as wide nodes take 32 x 16.  Lattices of a few thousand nodes take
+// 16 x 16 regions, which spread them over the chip.  The explicit second-order
+// source also reads the previous step's kinetics of its nodes, which a
+// neighbouring region may not find overwritten: where the tape holds only one
+// buffer for them it takes one step at a time, in rows of 256 nodes (kRows).
+//
+// What bounds it: with 4 steps a launch the state's traffic falls from 144 to
+// 36 B a node and step, and the vector units, of which the rings take 30%,
+// come level with memory.  Stores are ordinary ones: a region's rows begin
+// anywhere in a 64-byte chunk, and two regions' parts of a chunk merge in L2
+// (with non-temporal stores each part went to memory by itself: 65 us a step
+// at 2048^2 instead of 55).  Measured at 2048^2, masked, FP32, in us a step:
+// forward with record 122 -> 55.8, AMRT step 125 -> 65.4 (periodic: 53.5 and
+// 53.3); at 1024^2 27 -> 13.7 and 36 -> 18.3; at 128^2 4.4 -> 1.9.
+
+template <typename T>
+struct alignas(2 * sizeof(T)) Pair {
+  T u, v;
+};
+
+template <typename T, int RX, int RY, bool W3>
+struct Exchange {
+  static constexpr int kNodes = RX * RY;
+  static constexpr int kPad = RX + 1;  // the outer ring reads past the region
+  Pair<T> uv[8 * kNodes + 2 * kPad];
+  T w[W3 ? 8 * kNodes + 2 * kPad : 1];
+};
+
+// One thread's node of a region.  Regions that reach past a lattice edge
+// wrap around it, periodic or not: across a wall nothing is taken from the
+// nodes beyond.
+struct RegionNode {
+  int x, y;
+  bool owner;  // its results are stored by this thread
+};
+
+// Regions of one row and one step.
+template <int RY>
+constexpr bool kRows = RY == 1;
+
+template <int RX, int RY>
+__device__ __forceinline__ RegionNode region_node(const Geometry& g, const TileGrid& tg,
+                                                  int tid) {
+  const int halo = kRows<RY> ? 0 : tg.steps - 1;
+  const int t = xcd_tile(blockIdx.x, tg.ntiles);
+  const int ty = t / tg.ntx, tx = t - ty * tg.ntx;
+  int dx = unsigned(tid) % RX, dy = unsigned(tid) / RX;
+  if (RX % 64 == 0) dy = __builtin_amdgcn_readfirstlane(dy);  // a wavefront is one row
+  RegionNode r;
+  r.x = tx * (RX - 2 * halo) - halo + dx;
+  r.y = ty * (RY - 2 * halo) - halo + dy;
+  r.owner = dx >= halo && dx < RX - halo && r.x < g.nx && dy >= halo && dy < RY - halo &&
+            r.y < g.ny;
+  if (kRows<RY>) return r;  // the others leave at once
+  // at most RX (RY) nodes past an edge: once around, unless the lattice is
+  // smaller than that
+  if (g.nx < RX) {
+    r.x %= g.nx;
+  } else {
+    r.x = r.x >= g.nx ? r.x - g.nx : r.x;
+  }
+  if (g.ny < RY) {
+    r.y %= g.ny;
+  } else {
+    r.y = r.y >= g.ny ? r.y - g.ny : r.y;
+  }
+  r.x = r.x < 0 ? r.x + g.nx : r.x;
+  r.y = r.y < 0 ? r.y + g.ny : r.y;
+  if (RX % 64 == 0) r.y = __builtin_amdgcn_readfirstlane(r.y);
+  return r;
 }
 
-template <typename T, bool PERIODIC, bool MASKED, bool IMPL, bool W3>
+// The node again, at the end of a launch, with the plane size it is
+// addressed by: computed afresh, so that nothing derived from it stays in
+// registers over the steps (the stores' row bases alone would not fit beside
+// the coefficients).  False: another thread stores its results.
+template <int RX, int RY>
+__device__ __forceinline__ bool node_again(Geometry& g, const TileGrid& tg, NodeIdx& n) {
+  if (kRows<RY>) return true;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid), "+s"(g.plane), "+s"(g.nx), "+s"(g.ny));
+  const RegionNode r = region_node<RX, RY>(g, tg, tid);
+  make_node(g, r.x, r.y, n);
+  return r.owner;
+}
+
+// Link word of a node; of a non-periodic lattice without a mask, from the
+// coordinates.
+template <Lanes A>
+__device__ __forceinline__ unsigned link_word(const Geometry& g, const NodeIdx& n) {
+  if (g.link) return *own_at<A>(g.link, n);
+  unsigned w = 0;
+#pragma unroll
+  for (int i = 1; i < 9; ++i) w |= pull_outside(n, i) ? 1u << i : 0u;
+  return w;
+}
+
+// Link word in a kernel of rows (a wavefront is one of the 64-node segments
+// that the flags describe): read only where the segment touches a solid node.
+// False: the wavefront lies inside a solid region.
+template <bool ROWS, Lanes A>
+__device__ __forceinline__ bool links(const Geometry& g, const NodeIdx& n, unsigned& lm) {
+  if (ROWS && g.masked) {
+    const unsigned flag = wave_flag(g, n);
+    if (flag == 2u) return false;
+    lm = flag ? unsigned(*own_at<A>(g.link, n)) : 0u;
+    return true;
+  }
+  lm = link_word<A>(g, n);
+  return true;
+}
+
+template <typename T>
+__device__ __forceinline__ void swap_(T& a, T& b) {
+  const T t = a;
+  a = b;
+  b = t;
+}
+
+// Streaming between two steps of a launch: the populations of every node go
+// to LDS (give), each node takes back those its neighbours send it, or its own
+// opposite one where the neighbour is a wall (ADJ: the transposed stream,
+// from x + e_i).
+template <typename T, int RX, int RY, bool W3>
+__device__ __forceinline__ void give(Exchange<T, RX, RY, W3>& lds, const T fu[9], const T fv[9],
+                                     const T fw[9]) {
+  constexpr int N = RX * RY, P = RX + 1;
+  __syncthreads();  // the reads of the exchange before are done
+#pragma unroll
+  for (int i = 1; i < 9; ++i) {
+    lds.uv[P + (i - 1) * N + int(threadIdx.x)] = Pair<T>{fu[i], fv[i]};
+    if (W3) lds.w[P + (i - 1) * N + int(threadIdx.x)] = fw[i];
+  }
+  __syncthreads();
+}
+
+template <bool WALLS, bool ADJ, typename T, int RX, int RY, bool W3>
+__device__ __forceinline__ void take(const Exchange<T, RX, RY, W3>& lds, T fu[9], T fv[9],
+                                     T fw[9], unsigned lm) {
+  constexpr int N = RX * RY, P = RX + 1;
+  constexpr int ex[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
+  constexpr int ey[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
+  auto one = [&](int i) {
+    const int o = P + (i - 1) * N + (ADJ ? 1 : -1) * (ex[i] + ey[i] * RX) + int(threadIdx.x);
+    const Pair<T> p = lds.uv[o];
+    fu[i] = p.u;
+    fv[i] = p.v;
+    if (W3) fw[i] = lds.w[o];
+  };
+  if (WALLS && __builtin_amdgcn_ballot_w64((lm & 0x1FEu) != 0u) != 0ull) {
+    // opposite populations change places, then those from fluid neighbours
+    // are read over them
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+      if (i < opp(i)) {
+        swap_(fu[i], fu[opp(i)]);
+        swap_(fv[i], fv[opp(i)]);
+        if (W3) swap_(fw[i], fw[opp(i)]);
+      }
+    }
+#pragma unroll
+    for (int i = 1; i < 9; ++i)
+      if (!((lm >> (ADJ ? opp(i) : i)) & 1u)) one(i);
+  } else {
+#pragma unroll
+    for (int i = 1; i < 9; ++i) one(i);
+  }
+}
+
+// Does this wavefront still hold rows that step s of a launch needs?  The
+// outer rows go stale with their rings.
+template <int RX, int RY>
+__device__ __forceinline__ bool live_rows(int s) {
+  const int lo = __builtin_amdgcn_readfirstlane(threadIdx.x / 64) * 64 / RX;
+  const int hi = lo + (RX < 64 ? 64 / RX : 1) - 1;
+  return hi >= s && lo < RY - s;
+}
+
+// A wavefront of stale rows after step s: it only meets the others at the
+// barriers of the exchanges to come.
+__device__ __forceinline__ void retire(const TileGrid& tg, int s) {
+  for (; s < tg.steps - 2; ++s) {
+    __syncthreads();
+    __syncthreads();
+  }
+}
+
+// The initial populations of a lattice with walls enter the collision as
+// rounded products: the compiler may not contract them into its sums.  (On
+// the others it may.  Either way is as near the exact value; each kind of
+// lattice keeps its bits.)
+template <bool W3, typename T>
+__device__ __forceinline__ void keep_rounded(T fu[9], T fv[9], T fw[9]) {
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    asm volatile("" : "+v"(fu[i]), "+v"(fv[i]));
+    if (W3) asm volatile("" : "+v"(fw[i]));
+  }
+}
+
+// The gradient accumulator of a thread's node over the steps of a launch: in
+// a register pair, or (IN_LDS) in LDS, where the adjoint's walls leave no
+// registers for it (they went to scratch memory: 82 us a step instead of 58
+// at 2048 x 2048).
+template <bool IN_LDS, int N>
+struct Accumulator {
+  double v;
+  __device__ __forceinline__ void set(double x) { v = x; }
+  __device__ __forceinline__ void add(double x) { v += x; }
+  __device__ __forceinline__ double get() { return v; }
+};
+template <int N>
+struct Accumulator<true, N> {
+  double* p;
+  __device__ __forceinline__ Accumulator() {
+    __shared__ double slots[N];
+    p = slots + threadIdx.x;
+  }
+  __device__ __forceinline__ void set(double x) { *p = x; }
+  __device__ __forceinline__ void add(double x) { *p += x; }
+  __device__ __forceinline__ double get() { return *p; }
+};
+
+// A node's populations take more than the 72 bytes of two species in FP32.
+template <typename T, int VAR>
+constexpr bool kWide = sizeof(T) == 8 || VAR == kVarThree;
+
+// Wavefronts per SIMD that a region kernel is compiled for.
+template <typename T, int VAR>
+constexpr int kRegionWaves = (sizeof(T) == 4 ? 8 : 4) / (VAR == kVarThree ? 2 : 1);
+
+#define MRT_REGION_BOUNDS(T, VAR, RX, RY)                            \
+  __attribute__((amdgpu_flat_work_group_size(RX * RY, RX * RY),      \
+                 amdgpu_waves_per_eu(kRegionWaves<T, VAR>)))
+
+// Forward steps n .. n + K - 1 (FIRST: n = 0, from the initial fields).
+template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
+__global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void forward_kernel(Geometry g, ModelCoef<T> m,
+                                                                 FwdLaunch<T> a, TileGrid tg) {
+  constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit;
+  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  __shared__ Exchange<T, RX, RY, W3> lds;
+  const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
+  if (kRows<RY> && !r.owner) return;
+  NodeIdx n;
+  make_node(g, r.x, r.y, n);
+  unsigned lm = 0;
+  T fu[9], fv[9], fw[9], rec[5], lag[2] = {T(0), T(0)}, c = T(0);
+  if (WALLS && !links<kRows<RY>, A>(g, n, lm)) return;
+  if (kRows<RY> && WALLS && (lm & 1u)) {
+    // a solid node loads nothing and collides zeros: it takes part in the
+    // record stores, so that these fill whole 64-byte chunks
+#pragma unroll
+    for (int i = 0; i < 9; ++i) fu[i] = fv[i] = fw[i] = T(0);
+  } else {
+    pull_species<A, FIRST>(g, n, m.u, a.src, a.u0, fu);
+    pull_species<A, FIRST>(g, n, m.v, a.src + 9 * g.plane, a.v0, fv);
+    if (W3) pull_species<A, FIRST>(g, n, m.w, a.src + 18 * g.plane, a.w0, fw);
+    c = *own_at<A>(a.ctrl, n);
+    if (LAG && !FIRST) {
+      lag[0] = *own_at<A>(a.lag, n);
+      lag[1] = *own_at<A>(a.lag + g.plane, n);
+    }
+  }
+  auto record = [&](int s) {
+    if (a.rec != nullptr && r.owner)
+      store_record<A, VAR, kRows<RY>>(g, n, a.rec + size_t(s) * a.rec_stride, rec);
+  };
+  int s = 0;
+  if (FIRST) {  // step 0 on its own: it differs for the second-order sources
+    if (WALLS) keep_rounded<W3>(fu, fv, fw);
+    forward_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, true);
+    record(0);
+    if (!kRows<RY> && tg.steps > 1) {
+      give(lds, fu, fv, fw);
+      if (!live_rows<RX, RY>(1)) return retire(tg, 0);
+      take<WALLS, false>(lds, fu, fv, fw, lm);
+    }
+    s = 1;
+  }
+  for (; s < tg.steps; ++s) {
+    forward_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, false);
+    record(s);
+    if (kRows<RY> || s + 1 == tg.steps) break;
+    give(lds, fu, fv, fw);
+    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
+    take<WALLS, false>(lds, fu, fv, fw, lm);
+  }
+  if (!node_again<RX, RY>(g, tg, n)) return;
+  if (LAG) {
+    *own_at<A>(a.lag_out, n) = lag[0];
+    *own_at<A>(a.lag_out + g.plane, n) = lag[1];
+  }
+  if (WALLS && (lm & 1u)) return;  // its slots hold the neighbours' wall stores
+  store_species<A, WALLS, false, kRows<RY>>(g, n, fu, a.dst, lm);
+  store_species<A, WALLS, false, kRows<RY>>(g, n, fv, a.dst + 9 * g.plane, lm);
+  if (W3) store_species<A, WALLS, false, kRows<RY>>(g, n, fw, a.dst + 18 * g.plane, lm);
+}
+
+template <typename T, bool IMPL, bool W3>
 __global__ __launch_bounds__(kBlock) void finalize_kernel(
     Geometry g, ModelCoef<T> m, const T* __restrict__ src, const T* __restrict__ ctrl,
     T* __restrict__ state, T* __restrict__ uN, T* __restrict__ vN) {
   NodeIdx n;
   if (!node_of_block(g, n)) return;
-  finalize_node<T, PERIODIC, MASKED, IMPL, W3>(g, n, src, state, uN, vN, &m, ctrl);
+  finalize_node<T, IMPL, W3>(g, n, src, state, uN, vN, &m, ctrl);
 }
 
 // Pull of the populations streamed into node n after the last step (zeros
 // on solid nodes) and their sums G.
-template <typename T, bool PERIODIC, bool MASKED>
+template <typename T>
 __device__ __forceinline__ bool pull_sums(const Geometry& g, const NodeIdx& n,
                                           const T* __restrict__ src, T& Gu, T& Gv) {
   const size_t idx = n.r0 + n.x;
-  if (MASKED && (link_of(g, wave_flag(g, n), idx) & 1u)) return false;
+  if (g.masked && (link_of(g, wave_flag(g, n), idx) & 1u)) return false;
   Gu = T(0);
   Gv = T(0);
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
-    const size_t o = pull_src<PERIODIC>(n, i, g.plane);
-    Gu += src[o];
-    Gv += src[9 * g.plane + o];
+    Gu += *pull_at<kAny>(src + size_t(i) * g.plane, n, i);
+    Gv += *pull_at<kAny>(src + size_t(9 + i) * g.plane, n, i);
   }
   return true;
 }
@@ -114,7 +418,7 @@ __device__ __forceinline__ bool pull_sums(const Geometry& g, const NodeIdx& n,
 // node equation at u^N.  v^N also depends on the control (weight tau/2 in
 // the node equation): the gradient accumulator starts at (tau/2) beta b.
 // Zero on solid nodes.
-template <typename T, bool PERIODIC, bool MASKED>
+template <typename T>
 __global__ __launch_bounds__(kBlock) void implicit_terminal_kernel(
     Geometry g, ModelCoef<T> m, const T* __restrict__ src, const T* __restrict__ ctrl,
     const T* __restrict__ seed_u, const T* __restrict__ seed_v, T* __restrict__ out_u,
@@ -123,7 +427,7 @@ __global__ __launch_bounds__(kBlock) void implicit_terminal_kernel(
   if (!node_of_block(g, n)) return;
   const size_t idx = n.r0 + n.x;
   T Gu, Gv;
-  if (!pull_sums<T, PERIODIC, MASKED>(g, n, src, Gu, Gv)) {
+  if (!pull_sums<T>(g, n, src, Gu, Gv)) {
     out_u[idx] = T(0);
     out_v[idx] = T(0);
     gacc[idx] = 0.0;
@@ -142,7 +446,7 @@ __global__ __launch_bounds__(kBlock) void implicit_terminal_kernel(
 // Implicit characteristic difference, end of the tangent sweep: the
 // perturbation of Theta^N from that of G^N (node equation linearised at the
 // forward's u^N, with the control perturbation).
-template <typename T, bool PERIODIC, bool MASKED>
+template <typename T>
 __global__ __launch_bounds__(kBlock) void implicit_tlm_final_kernel(
     Geometry g, ModelCoef<T> m, const T* __restrict__ fsrc, const T* __restrict__ dsrc,
     const T* __restrict__ ctrl, const T* __restrict__ dc, T* __restrict__ duN,
@@ -151,12 +455,12 @@ __global__ __launch_bounds__(kBlock) void implicit_tlm_final_kernel(
   if (!node_of_block(g, n)) return;
   const size_t idx = n.r0 + n.x;
   T Gu, Gv, dGu, dGv;
-  if (!pull_sums<T, PERIODIC, MASKED>(g, n, fsrc, Gu, Gv)) {
+  if (!pull_sums<T>(g, n, fsrc, Gu, Gv)) {
     if (duN) duN[idx] = T(0);
     if (dvN) dvN[idx] = T(0);
     return;
   }
-  pull_sums<T, PERIODIC, MASKED>(g, n, dsrc, dGu, dGv);
+  pull_sums<T>(g, n, dsrc, dGu, dGv);
   T u, v;
   implicit_solve(m, Gu, Gv, ctrl[idx], u, v);
   const T du = dGu / (T(1) - T(0.5) * m.r_u * (T(1) - T(2) * u));
@@ -165,116 +469,161 @@ __global__ __launch_bounds__(kBlock) void implicit_tlm_final_kernel(
   if (dvN) dvN[idx] = (dGv + T(0.5) * (m.a_uv * du + dcc)) / (T(1) + T(0.5) * m.b_v);
 }
 
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST, bool LAST, int VAR>
-__global__ __launch_bounds__(kBlock) void adjoint_step_kernel(
-    Geometry g, ModelCoef<T> m, const T* __restrict__ src, T* __restrict__ dst,
-    const T* __restrict__ seed_u, const T* __restrict__ seed_v,
-    const T* __restrict__ rec, double* __restrict__ gacc,
-    T* __restrict__ adj_u0, T* __restrict__ adj_v0, T* __restrict__ mu, int step0) {
+// Adjoint steps n, n - 1, ..., n - K + 1.
+template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
+__global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, ModelCoef<T> m,
+                                                            AdjLaunch<T> a, TileGrid tg) {
+  constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit, IMPL = VAR == kVarImplicit;
+  __shared__ Exchange<T, RX, RY, W3> lds;
+  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
+  if (kRows<RY> && !r.owner) return;
   NodeIdx n;
-  if (!node_of_block(g, n)) return;
-  adjoint_node<T, PERIODIC, MASKED, FIRST, LAST, VAR>(g, n, m, src, dst, seed_u, seed_v, rec,
-                                                      gacc, adj_u0, adj_v0, mu, step0 != 0);
+  make_node(g, r.x, r.y, n);
+  unsigned lm = 0;
+  T nu[9], nv[9], nw[9], rec[5], mu[2] = {T(0), T(0)};
+  Accumulator<WALLS && sizeof(T) == 4 && !kRows<RY>, RX * RY> sum;
+  const T* in = a.rec;
+  constexpr bool fresh = FIRST && !IMPL;  // the sweep's first step: g starts at zero
+  if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) return;
+  if (kRows<RY> && WALLS && !FIRST && a.step > 0 && (lm & 1u)) return;
+  adjoint_gather<A, WALLS, VAR, FIRST, T>(g, n, a.src, a.seed_u, a.seed_v, lm, nu, nv, nw);
+  load_record<A, VAR>(g, n, in, rec);
+  if (LAG && !FIRST) {
+    mu[0] = *own_at<A>(a.mu, n);
+    mu[1] = *own_at<A>(a.mu + g.plane, n);
+  }
+  sum.set(r.owner && !fresh ? *own_at<A>(a.g, n) : 0.0);
+  for (int s = 0;; ++s) {
+    sum.add(double(adjoint_collide<T, WALLS, VAR>(m, nu, nv, nw, rec, mu, FIRST && s == 0,
+                                           a.step - s == 0)));
+    if (kRows<RY> || s + 1 == tg.steps) break;
+    in -= a.rec_stride;
+    load_record<A, VAR>(g, n, in, rec);
+    give(lds, nu, nv, nw);
+    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
+    take<WALLS, true>(lds, nu, nv, nw, lm);
+  }
+  if (!node_again<RX, RY>(g, tg, n)) return;
+  const bool solid = WALLS && (lm & 1u);
+  if (solid) {
+    // a sweep's outputs are zero on solid nodes
+    if (fresh) *own_at<A>(a.g, n) = 0.0;
+    if (a.adj_u0) *own_at<A>(a.adj_u0, n) = T(0);
+    if (a.adj_v0) *own_at<A>(a.adj_v0, n) = T(0);
+    return;
+  }
+  *own_at<A>(a.g, n) = sum.get();
+  if (LAG) {
+    *own_at<A>(a.mu_out, n) = mu[0];
+    *own_at<A>(a.mu_out + g.plane, n) = mu[1];
+  }
+  if (a.adj_u0) *own_at<A>(a.adj_u0, n) = adjoint_initial(m.u, nu);
+  if (a.adj_v0) *own_at<A>(a.adj_v0, n) = adjoint_initial(m.v, nv);
+  if (a.dst == nullptr) return;
+  store_species<A, WALLS, true, kRows<RY>>(g, n, nu, a.dst, lm);
+  store_species<A, WALLS, true, kRows<RY>>(g, n, nv, a.dst + 9 * g.plane, lm);
+  if (W3) store_species<A, WALLS, true, kRows<RY>>(g, n, nw, a.dst + 18 * g.plane, lm);
 }
 
-// Tangent-linear step of step n: pulls the perturbation (or, for n = 0,
-// the equilibrium of (du0, dv0)), linearised collision at the recorded
-// (u, j_v) of step n, streaming stores as the forward.
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST, int VAR>
-__global__ __launch_bounds__(kBlock) void tlm_step_kernel(
-    Geometry g, ModelCoef<T> m, const T* __restrict__ src, T* __restrict__ dst,
-    const T* __restrict__ du0, const T* __restrict__ dv0, const T* __restrict__ dc,
-    const T* __restrict__ rec, T* __restrict__ dlag) {
+// Tangent-linear steps n .. n + K - 1: pull the perturbation (FIRST, step 0:
+// the equilibrium of (du0, dv0); the third species starts at zero),
+// linearised collision at the recorded (u, j_v), streaming as the forward.
+template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
+__global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCoef<T> m,
+                                                             TlmLaunch<T> a, TileGrid tg) {
+  constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit;
+  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  __shared__ Exchange<T, RX, RY, W3> lds;
+  const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
+  if (kRows<RY> && !r.owner) return;
   NodeIdx n;
-  if (!node_of_block(g, n)) return;
-  const size_t idx = n.r0 + n.x;
+  make_node(g, r.x, r.y, n);
   unsigned lm = 0;
-  if (MASKED) {
-    const unsigned flag = wave_flag(g, n);
-    if (flag == 2u) return;  // wavefront inside a solid region
-    lm = link_of(g, flag, idx);
-    if (lm & 1u) return;  // solid node of a mixed wavefront: stores nothing
+  T fu[9], fv[9], fw[9], rec[5], lag[2] = {T(0), T(0)}, c = T(0);
+  const T* in = a.rec;
+  if (WALLS && !links<kRows<RY>, A>(g, n, lm)) return;
+  if (kRows<RY> && WALLS && (lm & 1u)) return;
+  pull_species<A, FIRST>(g, n, m.u, a.src, a.du0, fu);
+  pull_species<A, FIRST>(g, n, m.v, a.src + 9 * g.plane, a.dv0, fv);
+  if (W3)
+    pull_species<A, FIRST>(g, n, m.w, a.src + 18 * g.plane, static_cast<const T*>(nullptr), fw);
+  load_record<A, VAR>(g, n, in, rec);
+  if (a.dc) c = *own_at<A>(a.dc, n);
+  if (LAG && !FIRST) {
+    lag[0] = *own_at<A>(a.dlag, n);
+    lag[1] = *own_at<A>(a.dlag + g.plane, n);
   }
-  T fu[9], fv[9];
+  int s = 0;
   if (FIRST) {
-    const T a = du0 ? du0[idx] : T(0), b = dv0 ? dv0[idx] : T(0);
-    fu[0] = m.u.w_rest * a;
-    fv[0] = m.v.w_rest * b;
-#pragma unroll
-    for (int i = 1; i < 5; ++i) {
-      fu[i] = m.u.w_axis * a;
-      fv[i] = m.v.w_axis * b;
+    tlm_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, true);
+    if (!kRows<RY> && tg.steps > 1) {
+      in += a.rec_stride;
+      load_record<A, VAR>(g, n, in, rec);
+      give(lds, fu, fv, fw);
+      if (!live_rows<RX, RY>(1)) return retire(tg, 0);
+      take<WALLS, false>(lds, fu, fv, fw, lm);
     }
-#pragma unroll
-    for (int i = 5; i < 9; ++i) {
-      fu[i] = m.u.w_diag * a;
-      fv[i] = m.v.w_diag * b;
-    }
-  } else {
-    const T* sv = src + 9 * g.plane;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      const size_t o = pull_src<PERIODIC>(n, i, g.plane);
-      fu[i] = src[o];
-      fv[i] = sv[o];
-    }
+    s = 1;
   }
-  const T c = dc ? dc[idx] : T(0);
-  if (VAR == kVarThree) {
-    // the third species' perturbation starts at zero (no dw0)
-    T fw[9];
-    gather_w<T, PERIODIC, FIRST>(g, n, m, src, nullptr, fw);
-    tlm_collide_store<T, MASKED, VAR>(g, n, m, fu, fv, c, rec, dst, lm, dlag, FIRST, fw);
-  } else {
-    tlm_collide_store<T, MASKED, VAR>(g, n, m, fu, fv, c, rec, dst, lm, dlag, FIRST);
+  for (; s < tg.steps; ++s) {
+    tlm_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, false);
+    if (kRows<RY> || s + 1 == tg.steps) break;
+    in += a.rec_stride;
+    load_record<A, VAR>(g, n, in, rec);
+    give(lds, fu, fv, fw);
+    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
+    take<WALLS, false>(lds, fu, fv, fw, lm);
   }
+  if (!node_again<RX, RY>(g, tg, n) || (WALLS && (lm & 1u))) return;
+  if (LAG) {
+    *own_at<A>(a.dlag_out, n) = lag[0];
+    *own_at<A>(a.dlag_out + g.plane, n) = lag[1];
+  }
+  store_species<A, WALLS, false, kRows<RY>>(g, n, fu, a.dst, lm);
+  store_species<A, WALLS, false, kRows<RY>>(g, n, fv, a.dst + 9 * g.plane, lm);
+  if (W3) store_species<A, WALLS, false, kRows<RY>>(g, n, fw, a.dst + 18 * g.plane, lm);
 }
 
-// Continuous-adjoint step: pulls the adjoint populations (or, for the first
-// reversed step, p = seed_u at equilibrium and q = 0), then
-// cadj_collide_store with the record of the forward step at this time.
-template <typename T, bool PERIODIC, bool MASKED, bool FIRST>
-__global__ __launch_bounds__(kBlock) void cadj_step_kernel(
-    Geometry g, ModelCoef<T> m, CadjCoef<T> cc, const T* __restrict__ src, T* __restrict__ dst,
-    const T* __restrict__ seed_u, const T* __restrict__ rec, double* __restrict__ gacc) {
+// Continuous-adjoint steps: pull the adjoint populations (or, at the first
+// reversed step, p = seed_u at equilibrium and q = 0) and collide with the
+// records of the forward steps n, n - 1, ... at those times.
+template <typename T, bool WALLS, int RX, int RY, bool FIRST>
+__global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, ModelCoef<T> m,
+                                                         CadjCoef<T> cc, CadjLaunch<T> a,
+                                                         TileGrid tg) {
+  __shared__ Exchange<T, RX, RY, false> lds;
+  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
+  if (kRows<RY> && !r.owner) return;
   NodeIdx n;
-  if (!node_of_block(g, n)) return;
-  const size_t idx = n.r0 + n.x;
+  make_node(g, r.x, r.y, n);
   unsigned lm = 0;
-  if (MASKED) {
-    if (FIRST) {
-      // the first step owns g on every node, solid ones included
-      lm = g.link[idx];
-      if (lm & 1u) {
-        gacc[idx] = 0.0;
-        return;
-      }
-    } else {
-      const unsigned flag = wave_flag(g, n);
-      if (flag == 2u) return;  // wavefront inside a solid region
-      lm = link_of(g, flag, idx);
-    }
+  T fp[9], fq[9], rec[5];
+  double sum = 0.0;
+  const T* in = a.rec;
+  if (WALLS) lm = link_word<A>(g, n);
+  pull_species<A, FIRST>(g, n, m.u, a.src, a.seed_u, fp);
+  pull_species<A, FIRST>(g, n, m.v, a.src + 9 * g.plane, static_cast<const T*>(nullptr), fq);
+  load_record<A, kVarFirst>(g, n, in, rec);
+  if (r.owner && !FIRST) sum = *own_at<A>(a.g, n);
+  for (int s = 0;; ++s) {
+    sum += double(cadj_collide<T>(m, cc, fp, fq, rec));
+    if (kRows<RY> || s + 1 == tg.steps) break;
+    in -= a.rec_stride;
+    load_record<A, kVarFirst>(g, n, in, rec);
+    give(lds, fp, fq, static_cast<T*>(nullptr));
+    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
+    take<WALLS, false>(lds, fp, fq, static_cast<T*>(nullptr), lm);
   }
-  T fp[9], fq[9];
-  if (FIRST) {
-    const T a = seed_u[idx];
-    fp[0] = m.u.w_rest * a;
-#pragma unroll
-    for (int i = 1; i < 5; ++i) fp[i] = m.u.w_axis * a;
-#pragma unroll
-    for (int i = 5; i < 9; ++i) fp[i] = m.u.w_diag * a;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) fq[i] = T(0);
-  } else {
-    const T* sq = src + 9 * g.plane;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      const size_t o = pull_src<PERIODIC>(n, i, g.plane);
-      fp[i] = src[o];
-      fq[i] = sq[o];
-    }
+  if (!node_again<RX, RY>(g, tg, n)) return;
+  if (WALLS && (lm & 1u)) {
+    if (FIRST) *own_at<A>(a.g, n) = 0.0;
+    return;
   }
-  cadj_collide_store<T, MASKED, FIRST>(g, n, m, cc, fp, fq, rec, dst, gacc, lm);
+  *own_at<A>(a.g, n) = sum;
+  store_species<A, WALLS, false, kRows<RY>>(g, n, fp, a.dst, lm);
+  store_species<A, WALLS, false, kRows<RY>>(g, n, fq, a.dst + 9 * g.plane, lm);
 }
 
 // Fluid test on the tape's link word (bit 0 = solid) or, for the calls that
@@ -471,30 +820,97 @@ void launch_build_link(const Geometry& g, int periodic, const uint8_t* mask,
                      mask, link_out, wflag_out);
 }
 
-template <typename T>
-void launch_forward_step(const Geometry& g, const ModelCoef<T>& m,
-                         const FwdLaunch<T>& a, hipStream_t s) {
-  const bool first = a.src == nullptr;
-  const int nb = stencil_blocks(g);
-#define MRT_FWD2(P, M, F, VR)                                                \
-  hipLaunchKernelGGL((forward_step_kernel<T, P, M, F, VR>), dim3(nb),        \
-                     dim3(kBlock), 0, s, g, m, a.src, a.dst, a.u0, a.v0,     \
-                     a.ctrl, a.rec, a.lag, a.w0)
-#define MRT_FWD(P, M, F)                                                     \
-  if (a.variant == kVarExplicit) { MRT_FWD2(P, M, F, kVarExplicit); }       \
-  else if (a.variant == kVarImplicit) { MRT_FWD2(P, M, F, kVarImplicit); }  \
-  else if (a.variant == kVarThree) { MRT_FWD2(P, M, F, kVarThree); }        \
-  else { MRT_FWD2(P, M, F, kVarFirst); }
-#define MRT_FWD_F(P, M) \
-  if (first) { MRT_FWD(P, M, true); } else { MRT_FWD(P, M, false); }
-  if (g.periodic) {
-    if (g.masked) { MRT_FWD_F(true, true); } else { MRT_FWD_F(true, false); }
+namespace {
+
+TileGrid region_grid(const Geometry& g, const StepPlan& p) {
+  TileGrid t;
+  t.steps = p.steps;
+  const int wx = p.rx - 2 * (p.steps - 1), wy = p.ry - 2 * (p.steps - 1);
+  t.ntx = (g.nx + wx - 1) / wx;
+  t.ntiles = t.ntx * ((g.ny + wy - 1) / wy);
+  return t;
+}
+
+// Calls f(integral constants walls, region width, region height) for a
+// lattice and a plan.  The regions of wide nodes are half as large.
+template <typename T, int VAR, typename F>
+void dispatch_region(const Geometry& g, const StepPlan& p, F f) {
+  using std::integral_constant;
+  constexpr bool WIDE = kWide<T, VAR>;
+  auto shape = [&](auto W) {
+    if constexpr (VAR == kVarExplicit)
+      if (p.ry == 1) return f(W, integral_constant<int, 256>(), integral_constant<int, 1>());
+    if (p.rx == 16)
+      f(W, integral_constant<int, 16>(), integral_constant<int, 16>());
+    else
+      f(W, integral_constant<int, WIDE ? 32 : 64>(), integral_constant<int, 16>());
+  };
+  if (g.masked || !g.periodic)
+    shape(std::true_type());
+  else
+    shape(std::false_type());
+}
+
+// Calls f(integral constant variant).
+template <typename F>
+void dispatch_variant(int variant, F f) {
+  using std::integral_constant;
+  if (variant == kVarExplicit)
+    f(integral_constant<int, kVarExplicit>());
+  else if (variant == kVarImplicit)
+    f(integral_constant<int, kVarImplicit>());
+  else if (variant == kVarThree)
+    f(integral_constant<int, kVarThree>());
+  else
+    f(integral_constant<int, kVarFirst>());
+}
+
+}  // namespace
+
+// A launch costs about 4 us beside its steps (the gather, the stores and the
+// gap before it), and every further step costs a ring of each region.
+// Measured in us per forward step, FP32, steps per launch in brackets:
+//   2048^2  64x16 regions  136 (1)   85 (2)   61 (3)  53.5 (4)  51 (5)  59 (6)
+//    512^2                 9.1 (1)  7.1 (2)  5.4 (3)  4.6 (4)  5.3 (5)  5.5 (6)
+//    256^2                 7.2 (1)  5.0 (2)  3.9 (3)  3.3 (4)  2.8 (5)  2.6 (6)
+//          16x16 regions   3.0 (4)  2.9 (5)  3.6 (6)
+//    128^2 64x16 2.5 (6); 16x16  2.2 (4)  1.9 (5)  2.0 (6)
+// The wide regions use the chip as long as there are more of them than
+// compute units; below that the steps' latency counts, and it is shortest in
+// small regions spread over all of the chip.
+StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool one) {
+  const bool wide = elem == 8 || variant == kVarThree;
+  const size_t nodes = size_t(g.nx) * g.ny;
+  StepPlan p;
+  p.ry = 16;
+  if (one) return {256, 1, 1};
+  if (nodes <= 160 * 160) {
+    p.rx = 16;
+    p.steps = 5;
   } else {
-    if (g.masked) { MRT_FWD_F(false, true); } else { MRT_FWD_F(false, false); }
+    p.rx = wide ? 32 : 64;
+    p.steps = nodes <= 384 * 384 ? 6 : 4;
   }
-#undef MRT_FWD_F
-#undef MRT_FWD
-#undef MRT_FWD2
+  // as many launches as that takes, their steps spread evenly
+  const int launches = (left + p.steps - 1) / p.steps;
+  p.steps = (left + launches - 1) / launches;
+  return p;
+}
+
+template <typename T>
+void launch_forward(const Geometry& g, const ModelCoef<T>& m, const FwdLaunch<T>& a,
+                    const StepPlan& p, hipStream_t s) {
+  const TileGrid t = region_grid(g, p);
+  dispatch_variant(a.variant, [&](auto V) {
+    dispatch_region<T, V()>(g, p, [&](auto W, auto RX, auto RY) {
+      if (a.src)
+        hipLaunchKernelGGL((forward_kernel<T, W(), V(), RX(), RY(), false>), dim3(t.ntiles),
+                           dim3(RX() * RY()), 0, s, g, m, a, t);
+      else
+        hipLaunchKernelGGL((forward_kernel<T, W(), V(), RX(), RY(), true>), dim3(t.ntiles),
+                           dim3(RX() * RY()), 0, s, g, m, a, t);
+    });
+  });
 }
 
 template <typename T>
@@ -503,20 +919,16 @@ void launch_finalize(const Geometry& g, const T* src, T* state, T* uN, T* vN,
   const int nb = stencil_blocks(g);
   const bool impl = m != nullptr;
   const ModelCoef<T> mc = impl ? *m : ModelCoef<T>{};
-#define MRT_FIN2(P, M, I, W)                                                 \
-  hipLaunchKernelGGL((finalize_kernel<T, P, M, I, W>), dim3(nb),             \
-                     dim3(kBlock), 0, s, g, mc, src, ctrl, state, uN, vN)
-#define MRT_FIN(P, M)                                                        \
-  if (impl) { MRT_FIN2(P, M, true, false); }                                 \
-  else if (three) { MRT_FIN2(P, M, false, true); }                           \
-  else { MRT_FIN2(P, M, false, false); }
-  if (g.periodic) {
-    if (g.masked) { MRT_FIN(true, true); } else { MRT_FIN(true, false); }
-  } else {
-    if (g.masked) { MRT_FIN(false, true); } else { MRT_FIN(false, false); }
-  }
-#undef MRT_FIN
-#undef MRT_FIN2
+  auto fin = [&](auto I, auto W) {
+    hipLaunchKernelGGL((finalize_kernel<T, I(), W()>), dim3(nb), dim3(kBlock), 0, s, g, mc, src,
+                       ctrl, state, uN, vN);
+  };
+  if (impl)
+    fin(std::true_type(), std::false_type());
+  else if (three)
+    fin(std::false_type(), std::true_type());
+  else
+    fin(std::false_type(), std::false_type());
 }
 
 template <typename T>
@@ -524,16 +936,8 @@ void launch_implicit_terminal(const Geometry& g, const ModelCoef<T>& m, const T*
                               const T* ctrl, const T* seed_u, const T* seed_v, T* out_u,
                               T* out_v, double* gacc, hipStream_t s) {
   const int nb = stencil_blocks(g);
-#define MRT_TRM(P, M)                                                        \
-  hipLaunchKernelGGL((implicit_terminal_kernel<T, P, M>), dim3(nb),          \
-                     dim3(kBlock), 0, s, g, m, src, ctrl, seed_u, seed_v,    \
-                     out_u, out_v, gacc)
-  if (g.periodic) {
-    if (g.masked) { MRT_TRM(true, true); } else { MRT_TRM(true, false); }
-  } else {
-    if (g.masked) { MRT_TRM(false, true); } else { MRT_TRM(false, false); }
-  }
-#undef MRT_TRM
+  hipLaunchKernelGGL((implicit_terminal_kernel<T>), dim3(nb), dim3(kBlock), 0, s, g, m, src, ctrl,
+                     seed_u, seed_v, out_u, out_v, gacc);
 }
 
 template <typename T>
@@ -541,45 +945,24 @@ void launch_implicit_tlm_final(const Geometry& g, const ModelCoef<T>& m, const T
                                const T* dsrc, const T* ctrl, const T* dc, T* duN, T* dvN,
                                hipStream_t s) {
   const int nb = stencil_blocks(g);
-#define MRT_ITF(P, M)                                                        \
-  hipLaunchKernelGGL((implicit_tlm_final_kernel<T, P, M>), dim3(nb),         \
-                     dim3(kBlock), 0, s, g, m, fsrc, dsrc, ctrl, dc, duN,    \
-                     dvN)
-  if (g.periodic) {
-    if (g.masked) { MRT_ITF(true, true); } else { MRT_ITF(true, false); }
-  } else {
-    if (g.masked) { MRT_ITF(false, true); } else { MRT_ITF(false, false); }
-  }
-#undef MRT_ITF
+  hipLaunchKernelGGL((implicit_tlm_final_kernel<T>), dim3(nb), dim3(kBlock), 0, s, g, m, fsrc,
+                     dsrc, ctrl, dc, duN, dvN);
 }
 
 template <typename T>
-void launch_adjoint_step(const Geometry& g, const ModelCoef<T>& m,
-                         const AdjLaunch<T>& a, hipStream_t s) {
-  const int nb = stencil_blocks(g);
-#define MRT_ADJ2(P, M, F, L, VR)                                             \
-  hipLaunchKernelGGL((adjoint_step_kernel<T, P, M, F, L, VR>), dim3(nb),     \
-                     dim3(kBlock), 0, s, g, m, a.src, a.dst, a.seed_u,       \
-                     a.seed_v, a.rec, a.g, a.adj_u0, a.adj_v0, a.mu,         \
-                     a.step0)
-#define MRT_ADJ(P, M, F, L)                                                  \
-  if (a.variant == kVarExplicit) { MRT_ADJ2(P, M, F, L, kVarExplicit); }    \
-  else if (a.variant == kVarImplicit) { MRT_ADJ2(P, M, F, L, kVarImplicit); } \
-  else if (a.variant == kVarThree) { MRT_ADJ2(P, M, F, L, kVarThree); }      \
-  else { MRT_ADJ2(P, M, F, L, kVarFirst); }
-#define MRT_ADJ_L(P, M, F) \
-  if (a.last) { MRT_ADJ(P, M, F, true); } else { MRT_ADJ(P, M, F, false); }
-#define MRT_ADJ_F(P, M) \
-  if (a.first) { MRT_ADJ_L(P, M, true); } else { MRT_ADJ_L(P, M, false); }
-  if (g.periodic) {
-    if (g.masked) { MRT_ADJ_F(true, true); } else { MRT_ADJ_F(true, false); }
-  } else {
-    if (g.masked) { MRT_ADJ_F(false, true); } else { MRT_ADJ_F(false, false); }
-  }
-#undef MRT_ADJ_F
-#undef MRT_ADJ_L
-#undef MRT_ADJ
-#undef MRT_ADJ2
+void launch_adjoint(const Geometry& g, const ModelCoef<T>& m, const AdjLaunch<T>& a,
+                    const StepPlan& p, hipStream_t s) {
+  const TileGrid t = region_grid(g, p);
+  dispatch_variant(a.variant, [&](auto V) {
+    dispatch_region<T, V()>(g, p, [&](auto W, auto RX, auto RY) {
+      if (a.src)
+        hipLaunchKernelGGL((adjoint_kernel<T, W(), V(), RX(), RY(), false>), dim3(t.ntiles),
+                           dim3(RX() * RY()), 0, s, g, m, a, t);
+      else
+        hipLaunchKernelGGL((adjoint_kernel<T, W(), V(), RX(), RY(), true>), dim3(t.ntiles),
+                           dim3(RX() * RY()), 0, s, g, m, a, t);
+    });
+  });
 }
 
 template <typename T>
@@ -668,47 +1051,33 @@ void launch_gd_step(const Geometry& g, T* ctrl, const T* grad, double zeta,
 }
 
 template <typename T>
-void launch_tlm_step(const Geometry& g, const ModelCoef<T>& m, const TlmLaunch<T>& a,
-                     hipStream_t s) {
-  const bool first = a.src == nullptr;
-  const int nb = stencil_blocks(g);
-#define MRT_TLM2(P, M, F, VR)                                                \
-  hipLaunchKernelGGL((tlm_step_kernel<T, P, M, F, VR>), dim3(nb),            \
-                     dim3(kBlock), 0, s, g, m, a.src, a.dst, a.du0, a.dv0,   \
-                     a.dc, a.rec, a.dlag)
-#define MRT_TLM(P, M, F)                                                     \
-  if (a.variant == kVarExplicit) { MRT_TLM2(P, M, F, kVarExplicit); }       \
-  else if (a.variant == kVarImplicit) { MRT_TLM2(P, M, F, kVarImplicit); }  \
-  else if (a.variant == kVarThree) { MRT_TLM2(P, M, F, kVarThree); }        \
-  else { MRT_TLM2(P, M, F, kVarFirst); }
-#define MRT_TLM_F(P, M) \
-  if (first) { MRT_TLM(P, M, true); } else { MRT_TLM(P, M, false); }
-  if (g.periodic) {
-    if (g.masked) { MRT_TLM_F(true, true); } else { MRT_TLM_F(true, false); }
-  } else {
-    if (g.masked) { MRT_TLM_F(false, true); } else { MRT_TLM_F(false, false); }
-  }
-#undef MRT_TLM_F
-#undef MRT_TLM
-#undef MRT_TLM2
+void launch_tlm(const Geometry& g, const ModelCoef<T>& m, const TlmLaunch<T>& a,
+                const StepPlan& p, hipStream_t s) {
+  const TileGrid t = region_grid(g, p);
+  dispatch_variant(a.variant, [&](auto V) {
+    dispatch_region<T, V()>(g, p, [&](auto W, auto RX, auto RY) {
+      if (a.src)
+        hipLaunchKernelGGL((tlm_kernel<T, W(), V(), RX(), RY(), false>), dim3(t.ntiles),
+                           dim3(RX() * RY()), 0, s, g, m, a, t);
+      else
+        hipLaunchKernelGGL((tlm_kernel<T, W(), V(), RX(), RY(), true>), dim3(t.ntiles),
+                           dim3(RX() * RY()), 0, s, g, m, a, t);
+    });
+  });
 }
 
 template <typename T>
-void launch_cadj_step(const Geometry& g, const ModelCoef<T>& m, const CadjCoef<T>& cc,
-                      const CadjLaunch<T>& a, hipStream_t s) {
-  const int nb = stencil_blocks(g);
-#define MRT_CADJ(P, M, F)                                                       \
-  hipLaunchKernelGGL((cadj_step_kernel<T, P, M, F>), dim3(nb), dim3(kBlock), 0,  \
-                     s, g, m, cc, a.src, a.dst, a.seed_u, a.rec, a.g)
-#define MRT_CADJ_F(P, M) \
-  if (a.first) { MRT_CADJ(P, M, true); } else { MRT_CADJ(P, M, false); }
-  if (g.periodic) {
-    if (g.masked) { MRT_CADJ_F(true, true); } else { MRT_CADJ_F(true, false); }
-  } else {
-    if (g.masked) { MRT_CADJ_F(false, true); } else { MRT_CADJ_F(false, false); }
-  }
-#undef MRT_CADJ_F
-#undef MRT_CADJ
+void launch_cadj(const Geometry& g, const ModelCoef<T>& m, const CadjCoef<T>& cc,
+                 const CadjLaunch<T>& a, const StepPlan& p, hipStream_t s) {
+  const TileGrid t = region_grid(g, p);
+  dispatch_region<T, kVarFirst>(g, p, [&](auto W, auto RX, auto RY) {
+    if (a.src)
+      hipLaunchKernelGGL((cadj_kernel<T, W(), RX(), RY(), false>), dim3(t.ntiles),
+                         dim3(RX() * RY()), 0, s, g, m, cc, a, t);
+    else
+      hipLaunchKernelGGL((cadj_kernel<T, W(), RX(), RY(), true>), dim3(t.ntiles),
+                         dim3(RX() * RY()), 0, s, g, m, cc, a, t);
+  });
 }
 
 template <typename T>
@@ -744,8 +1113,9 @@ void launch_count_fluid(const Geometry& g, double* partials, double* result,
 #define MRT_INSTANTIATE(T)                                                   \
   template void launch_dots<T>(const Geometry&, const DotPairs<T>&, double*, double*,  \
                                hipStream_t);                                          \
-  template void launch_forward_step<T>(const Geometry&, const ModelCoef<T>&, \
-                                       const FwdLaunch<T>&, hipStream_t);    \
+  template void launch_forward<T>(const Geometry&, const ModelCoef<T>&,      \
+                                  const FwdLaunch<T>&, const StepPlan&,      \
+                                  hipStream_t);                              \
   template void launch_finalize<T>(const Geometry&, const T*, T*, T*, T*,    \
                                    hipStream_t, const ModelCoef<T>*,         \
                                    const T*, bool);                          \
@@ -757,8 +1127,9 @@ void launch_count_fluid(const Geometry& g, double* partials, double* result,
                                              const ModelCoef<T>&, const T*,  \
                                              const T*, const T*, const T*,   \
                                              T*, T*, hipStream_t);           \
-  template void launch_adjoint_step<T>(const Geometry&, const ModelCoef<T>&, \
-                                       const AdjLaunch<T>&, hipStream_t);    \
+  template void launch_adjoint<T>(const Geometry&, const ModelCoef<T>&,      \
+                                  const AdjLaunch<T>&, const StepPlan&,      \
+                                  hipStream_t);                              \
   template void launch_cost_grad<T>(const Geometry&, const T*, const T*,    \
                                     const T*, const double*, T*, T*, double, \
                                     double*, double*, hipStream_t);          \
@@ -768,11 +1139,12 @@ void launch_count_fluid(const Geometry& g, double* partials, double* result,
   template void launch_gd_step<T>(const Geometry&, T*, const T*, double,     \
                                   double, double, double*, double*,          \
                                   hipStream_t);                              \
-  template void launch_cadj_step<T>(const Geometry&, const ModelCoef<T>&,    \
-                                    const CadjCoef<T>&, const CadjLaunch<T>&, \
-                                    hipStream_t);                             \
-  template void launch_tlm_step<T>(const Geometry&, const ModelCoef<T>&,     \
-                                   const TlmLaunch<T>&, hipStream_t);        \
+  template void launch_cadj<T>(const Geometry&, const ModelCoef<T>&,         \
+                               const CadjCoef<T>&, const CadjLaunch<T>&,      \
+                               const StepPlan&, hipStream_t);                \
+  template void launch_tlm<T>(const Geometry&, const ModelCoef<T>&,          \
+                              const TlmLaunch<T>&, const StepPlan&,          \
+                              hipStream_t);                                  \
   template void launch_dot<T>(const Geometry&, const T*, const T*, double*,  \
                               double*, hipStream_t);                         \
   template void launch_axpby<T>(const Geometry&, const T*, T*, double,       \

@@ -1,0 +1,51 @@
+"""Several time steps per launch: lattice sizes at the edges of the regions
+that a work-group owns, and step counts that leave uneven launches, against
+the FP64 oracle (relative L2 1e-12 in FP64; 1e-5 on fields and 1e-4 on the
+gradient in FP32)."""
+import pytest
+
+from oracle import oracle as O
+from paper_1908_03876_amd import inputs as I
+from tests.gpu_util import device_gradient, rel_l2
+from tests.test_gpu_parity import TOL, _ragged, _torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+# (nx, ny, steps): one region, its last column or row, one node more; lattices
+# narrower or lower than a region; the widths that 64-, 32- and 16-node regions
+# own with 4, 5 or 6 steps; both sides of the lines between the plans
+SIZES = [(6, 6, 5), (7, 13, 6), (16, 16, 9), (17, 5, 11), (3, 40, 4), (61, 2, 7),
+         (160, 160, 11), (161, 160, 12), (54, 498, 7), (1200, 23, 6),
+         (384, 384, 7), (386, 384, 9), (58 * 7, 390, 5), (26 * 15 + 1, 401, 4)]
+KINDS = {"periodic": (True, False), "masked": (False, True), "walls": (False, False),
+         "masked_periodic": (True, True)}
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "x".join(map(str, s)))
+def test_regions_match_oracle(size, kind, prec):
+    nx, ny, steps = size
+    p = _ragged(nx * 1000 + ny, nx, ny, steps, *KINDS[kind])
+    print(f"case {size} {kind} {prec}", flush=True)
+    ref = O.cost_gradient(p)
+    ftol, gtol = TOL[prec]
+    f = p.fluid
+    for ckpt in (-1, 3):
+        r = device_gradient(p, _torch_dtype(prec), ckpt_every=ckpt)
+        assert rel_l2(r["uN"], ref["uN"], f) <= ftol
+        assert rel_l2(r["grad"], ref["grad"], f) <= gtol
+
+
+@pytest.mark.parametrize("source,species", [(2, 2), (3, 2), (1, 3)])
+@pytest.mark.parametrize("size", [(17, 5, 11), (161, 160, 12), (391, 401, 5)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_regions_of_the_other_schemes(size, source, species):
+    nx, ny, steps = size
+    p = _ragged(nx * 1000 + ny, nx, ny, steps, False, True)
+    p = I.with_repellent(p) if species == 3 else I.slow_reaction(p, 0.1).copy(source_term=source)
+    print(f"case {size} source {source} species {species}", flush=True)
+    ref = O.cost_gradient(p)
+    r = device_gradient(p, _torch_dtype("f64"), ckpt_every=4)
+    assert rel_l2(r["uN"], ref["uN"], p.fluid) <= 1e-12
+    assert rel_l2(r["grad"], ref["grad"], p.fluid) <= 1e-12
