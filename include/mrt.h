@@ -351,7 +351,7 @@ int mrt_stream_probe(int32_t reads, int32_t writes, int32_t order, const float* 
  * together.  Each gradient iteration (forward, cost and seed, AMRT sweep,
  * gradient and norms, gradient step, for every instance; Section 3.2.1's
  * discrete optimisation loop) runs the forward pass and the adjoint pass as
- * one persistent launch each, with a grid barrier between time steps, and
+ * one persistent launch each, with a grid barrier every few time steps, and
  * can be captured once in a HIP graph and replayed.  Problems must be
  * periodic, unmasked and square with pitch == nx, and share dtype and
  * nsteps; chi, tensors, rates, reactions and alpha may differ.  The batch
@@ -370,10 +370,11 @@ enum {
   MRT_FIELD_GRAD = 6
 };
 
-/* Launch shape of the persistent kernels: tiles of tile_w x (256/tile_w)
- * nodes (tile_w 64, 128 or 256) and blocks_per_cu resident work-groups per
- * compute unit (1..max_blocks_per_cu, the occupancy limit, so that every
- * work-group of a persistent launch is resident). */
+/* Launch shape of the persistent kernels: regions of tile_w x (1024/tile_w)
+ * nodes (tile_w 64, 128 or 256; the passes over the last state and the
+ * gradient take tiles of tile_w x (256/tile_w)) and blocks_per_cu resident
+ * work-groups per compute unit (1..max_blocks_per_cu, the occupancy limit, so
+ * that every work-group of a persistent launch is resident). */
 typedef struct mrt_batch_tiles {
   int32_t tile_w;
   int32_t blocks_per_cu;

@@ -11,14 +11,29 @@
 
 namespace mrt {
 
-// One work tile: tile_w x (256 / tile_w) nodes of instance k at (x0, y0).
-// One tile of the sweep: instance k, its first row and column, and the
-// instance's size and field offset (so that a tile needs one table load).
+// A piece of instance k that begins at (x0, y0), with the instance's size and
+// field offset (so that it needs one table load): a tile of tile_w x
+// (256 / tile_w) nodes of the one-pass kernels, or the nodes that a region of
+// the sweeps owns.
 struct BatchTile {
   int k, y0, x0, L;
   unsigned long long fo;
   unsigned long long pad;
 };
+
+// Steps that the sweeps take between two grid barriers, by the width of their
+// regions (width x 1024 / width nodes, of which batch_steps - 1 on each side
+// are recomputed): as many as leave a region two rows or more.
+__host__ __device__ constexpr int batch_steps(int width) {
+  return width == 64 ? 4 : width == 128 ? 3 : 2;
+}
+
+// Steps of the next launch (or barrier) of `left`, when as few launches as
+// `most` steps each allow share them evenly.
+__host__ __device__ inline int even_steps(int left, int most) {
+  const int launches = (left + most - 1) / most;
+  return (left + launches - 1) / launches;
+}
 
 // Two-level grid barrier, each word on its own 128-byte line: blocks arrive
 // at the counter of their group (block id mod 8, the XCD they run on), the
@@ -42,8 +57,9 @@ constexpr int kBatchSlots = 8;
 
 template <typename T>
 struct BatchArgs {
-  const BatchTile* tiles;
-  int ntiles, tile_w;
+  const BatchTile* tiles;    // of the one-pass kernels
+  const BatchTile* regions;  // of the sweeps
+  int ntiles, nregions, tile_w;
   const ModelCoef<T>* coef;  // [count]
   const int* L;              // [count] lattice side
   const size_t* foff;        // [count] offset of instance k's fields

@@ -2,10 +2,16 @@
 // launch (periodic square lattices, each with its own coefficients).
 //
 // The forward pass and the adjoint pass are each ONE persistent launch: the
-// work-groups stay resident, walk a tile table that covers every instance,
-// and meet at a grid barrier between time steps.  The per-node arithmetic is
-// the single-lattice code (mrt_device.h), so a batched instance computes the
-// same numbers as a single run.
+// work-groups stay resident, walk a table of regions that covers every
+// instance, take several time steps in each region (mrt_region.h) and meet at
+// a grid barrier before the next steps.  The per-node arithmetic is the
+// single-lattice code, so a batched instance computes the same numbers as a
+// single run.
+//
+// One step a barrier was bound by HBM (148 to 172 B a node and step at 63 to
+// 68% of 8 TB/s) and by the barrier itself (12 us).  Four steps a barrier,
+// 16 instances of 128^2 to 1024^2, N = 100, FP32: forward pass 16.6 -> 6.9
+// ms, adjoint pass with the recomputation 31.0 -> 14.7 ms.
 //
 // The grid barrier spins with a time limit.  A wait that exceeds it (which
 // can only happen if the work-groups are not all resident) sets a sticky
@@ -14,8 +20,12 @@
 // the error.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "batch_internal.h"
 #include "mrt_device.h"
+#include "mrt_region.h"
 
 namespace mrt {
 namespace {
@@ -107,33 +117,10 @@ __device__ __forceinline__ Geometry inst_geom(int L) {
   return g;
 }
 
-// Node of this thread in tile t; false if outside its lattice.
-__device__ __forceinline__ bool tile_node(const BatchTile& tl, int tile_w,
-                                          const Geometry& g, NodeIdx& n) {
-  const int x = tl.x0 + int(threadIdx.x) % tile_w;
-  const int y = tl.y0 + int(threadIdx.x) / tile_w;
-  if (x >= g.nx || y >= g.ny) return false;
-  make_node(g, x, y, n);
-  return true;
-}
-
-// Recording is a run-time pointer here as in the single-lattice kernels:
-// no call site is specialised on it, so the recorded forward and the
-// recomputation compute identical values.
-// Node of tile t for this thread: instance offset, geometry, coefficients.
-template <typename T>
-struct TileNode {
-  bool ok;
-  size_t fo;
-  Geometry g;
-  NodeIdx n;
-  int k;
-};
-
-// The tile table and the per-instance coefficients are read-only for the
+// The region table and the per-instance coefficients are read-only for the
 // whole launch and are indexed by wave-uniform values, so they are read
 // through the constant address space: scalar loads into SGPRs, instead of
-// a dozen vector loads per wavefront and tile that the compiler would issue
+// a dozen vector loads per wavefront and region that the compiler would issue
 // for a pointer held in the by-value argument struct.
 template <typename U>
 __device__ __forceinline__ U uniform_load(const U* p) {
@@ -145,111 +132,145 @@ __device__ __forceinline__ U uniform_load(const U* p) {
 #endif
 }
 
-template <typename T>
-__device__ __forceinline__ TileNode<T> tile_of(const BatchArgs<T>& a, int t) {
-  TileNode<T> r;
-  const BatchTile tl = uniform_load(a.tiles + t);
+// Region t for this thread: instance, its field offset and geometry, the
+// thread's node (regions wrap around their lattice).
+struct BatchNode {
+  bool owner;
+  int k;
+  size_t fo;
+  Geometry g;
+  NodeIdx n;
+};
+
+template <int RX, int RY>
+__device__ __forceinline__ BatchNode node_of_region(const BatchTile* regions, int t) {
+  constexpr int halo = batch_steps(RX) - 1;
+  const BatchTile tl = uniform_load(regions + t);
+  BatchNode r;
   r.k = __builtin_amdgcn_readfirstlane(tl.k);
   r.g = inst_geom(__builtin_amdgcn_readfirstlane(tl.L));
-  r.ok = tile_node(tl, a.tile_w, r.g, r.n);
   r.fo = size_t(tl.fo);
+  const int dx = threadIdx.x % RX, dy = __builtin_amdgcn_readfirstlane(threadIdx.x / RX);
+  const int L = r.g.nx;
+  int x = tl.x0 - halo + dx, y = tl.y0 - halo + dy;
+  r.owner = dx >= halo && dx < RX - halo && x < L && dy >= halo && dy < RY - halo && y < L;
+  x = L < RX ? x % L : (x >= L ? x - L : x);
+  y = L < RY ? y % L : (y >= L ? y - L : y);
+  x = x < 0 ? x + L : x;
+  y = y < 0 ? y + L : y;
+  make_node(r.g, x, __builtin_amdgcn_readfirstlane(y), r.n);
   return r;
 }
 
-// Forward and adjoint sweeps over this block's tiles, one tile at a time,
-// each tile's descriptor and coefficients in SGPRs.  Holding two tiles'
-// loads in registers (paired, or the next tile's gathers issued before the
-// current collision) measured slower over a gradient iteration.
-template <typename T, bool FIRST>
-__device__ __forceinline__ void forward_sweep_tiles(const BatchArgs<T>& a, const T* src, T* dst,
-                                    T* rec) {
-  for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const TileNode<T> A = tile_of(a, t);
-    if (!A.ok) continue;
-    const ModelCoef<T> m = uniform_load(a.coef + A.k);
-    T fu[9], fv[9], r[5];
-    const T* s = src ? src + 18 * A.fo : nullptr;
-    pull_species<kAny, FIRST>(A.g, A.n, m.u, s, a.u0 + A.fo, fu);
-    pull_species<kAny, FIRST>(A.g, A.n, m.v, s ? s + 9 * A.g.plane : nullptr, a.v0 + A.fo, fv);
-    const size_t idx = A.n.r0 + A.n.x;
-    const T c = a.ctrl[A.fo + idx];
-    forward_collide<T, kVarFirst>(m, fu, fv, nullptr, c, r, nullptr, FIRST);
-    if (rec) store_record<kAny, kVarFirst, true>(A.g, A.n, rec + 3 * A.fo, r);
-    T* d = dst + 18 * A.fo;
-    store_species<kAny, false, false, true>(A.g, A.n, fu, d, 0u);
-    store_species<kAny, false, false, true>(A.g, A.n, fv, d + 9 * A.g.plane, 0u);
-  }
+// The regions that this work-group takes, in order: f(t).  Work-groups are
+// dealt to the 8 XCDs round-robin; those of one XCD walk a contiguous eighth
+// of the table side by side, so that neighbouring regions, which read each
+// other's rings, share an L2.
+template <typename F>
+__device__ __forceinline__ void each_region(int ntiles, F f) {
+  const int groups = gridDim.x < unsigned(kXcds) ? gridDim.x : kXcds;
+  const int xcd = blockIdx.x % groups, members = (gridDim.x - xcd + groups - 1) / groups;
+  const int t0 = int(long(ntiles) * xcd / groups), t1 = int(long(ntiles) * (xcd + 1) / groups);
+  for (int t = t0 + blockIdx.x / groups; t < t1; t += members) f(t);
 }
 
-template <typename T, bool FIRST>
-__device__ __forceinline__ void adjoint_sweep_tiles(const BatchArgs<T>& a, const T* src, T* dst,
-                                    const T* rec) {
-  for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const TileNode<T> A = tile_of(a, t);
-    if (!A.ok) continue;
-    const ModelCoef<T> m = uniform_load(a.coef + A.k);
+// `count` forward (adjoint) steps of every instance over this block's regions.
+template <typename T, int RX, int RY, bool FIRST>
+__device__ __forceinline__ void forward_sweep(Exchange<T, RX, RY, false>& lds,
+                                              const BatchArgs<T>& a, const T* src, T* dst,
+                                              T* rec, int count) {
+  each_region(a.nregions, [&](int t) {
+    const BatchNode r = node_of_region<RX, RY>(a.regions, t);
+    const ModelCoef<T> m = uniform_load(a.coef + r.k);
+    T fu[9], fv[9];
+    const T* s = src + 18 * r.fo;
+    pull_species<kRow, FIRST>(r.g, r.n, m.u, s, a.u0 + r.fo, fu);
+    pull_species<kRow, FIRST>(r.g, r.n, m.v, s + 9 * r.g.plane, a.v0 + r.fo, fv);
+    const T c = *own_at<kRow>(a.ctrl + r.fo, r.n);
+    T* const nil = nullptr;
+    if (!forward_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, 0u, m, c, r.owner, fu, fv,
+                                                      nil, nil, rec ? rec + 3 * r.fo : nil,
+                                                      a.rec_elems, {count, batch_steps(RX) - 1}))
+      return;
+    if (!r.owner) return;
+    T* d = dst + 18 * r.fo;
+    store_species<kRow, false, false>(r.g, r.n, fu, d, 0u);
+    store_species<kRow, false, false>(r.g, r.n, fv, d + 9 * r.g.plane, 0u);
+  });
+}
+
+template <typename T, int RX, int RY, bool FIRST>
+__device__ __forceinline__ void adjoint_sweep(Exchange<T, RX, RY, false>& lds,
+                                              const BatchArgs<T>& a, const T* src, T* dst,
+                                              const T* rec, int step, int count) {
+  each_region(a.nregions, [&](int t) {
+    const BatchNode r = node_of_region<RX, RY>(a.regions, t);
+    const ModelCoef<T> m = uniform_load(a.coef + r.k);
     T nu[9], nv[9];
-    adjoint_gather<kAny, false, kVarFirst, FIRST, T>(A.g, A.n, src ? src + 18 * A.fo : nullptr,
-                                        a.seed_u + A.fo, nullptr, 0u, nu, nv, nullptr);
-    const size_t idx = A.n.r0 + A.n.x;
-    T r[5];
-    load_record<kAny, kVarFirst>(A.g, A.n, rec + 3 * A.fo, r);
-    const double share =
-        double(adjoint_collide<T, false, kVarFirst>(m, nu, nv, nullptr, r, nullptr, FIRST, false));
-    double* ga = a.gacc + A.fo + idx;
-    *ga = FIRST ? share : *ga + share;
-    if (dst) {
-      T* d = dst + 18 * A.fo;
-      store_species<kAny, false, true, true>(A.g, A.n, nu, d, 0u);
-      store_species<kAny, false, true, true>(A.g, A.n, nv, d + 9 * A.g.plane, 0u);
-    }
-  }
+    T* const nil = nullptr;
+    adjoint_gather<kRow, false, kVarFirst, FIRST, T>(r.g, r.n, src + 18 * r.fo, a.seed_u + r.fo,
+                                                     nullptr, 0u, nu, nv, nil);
+    Accumulator<false, RX * RY> sum;
+    sum.set(r.owner && !FIRST ? *own_at<kRow>(a.gacc + r.fo, r.n) : 0.0);
+    if (!adjoint_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, 0u, m, step, nu, nv, nil,
+                                                      nil, sum, rec + 3 * r.fo, a.rec_elems,
+                                                      {count, batch_steps(RX) - 1}))
+      return;
+    if (!r.owner) return;
+    *own_at<kRow>(a.gacc + r.fo, r.n) = sum.get();
+    if (!dst) return;
+    T* d = dst + 18 * r.fo;
+    store_species<kRow, false, true>(r.g, r.n, nu, d, 0u);
+    store_species<kRow, false, true>(r.g, r.n, nv, d + 9 * r.g.plane, 0u);
+  });
 }
 
-// Output of forward step n (checkpoint slot when it closes a segment).
-template <typename T>
-__device__ __forceinline__ T* fwd_dst(const BatchArgs<T>& a, int n, bool ckpt) {
-  if (ckpt && a.mode == 2 && (n + 1) % a.K == 0 && n + 1 < a.N)
-    return a.ckpt + size_t((n + 1) / a.K - 1) * a.state_elems;
-  return a.buf[n & 1];
-}
-
-// Forward steps [n0, n1): step n reads src (or the initial fields when
-// n == 0), writes fwd_dst and, from step rec0 on, the record slot n - rec0.
-// A barrier follows every step except the last one of the launch.
-template <typename T>
-__device__ void forward_steps(const BatchArgs<T>& a, int n0, int n1, int rec0,
-                              const T* src, bool ckpt, bool sync_last,
-                              unsigned nblocks, bool* alive) {
-  for (int n = n0; n < n1 && *alive; ++n) {
-    T* dst = fwd_dst(a, n, ckpt);
+// Forward steps [n0, n1) from src (null: the initial fields), recorded from
+// step rec0 on in the slots n - rec0.  A barrier follows every few steps
+// except the last ones of the launch.
+template <typename T, int RX, int RY>
+__device__ void forward_pass(Exchange<T, RX, RY, false>& lds, const BatchArgs<T>& a, int n0,
+                             int n1, int rec0, const T* src, bool ckpt, bool sync_last,
+                             unsigned nblocks, bool* alive) {
+  for (int n = n0; n < n1 && *alive;) {
+    const int seg_end = a.mode == 2 ? min(n1, (n / a.K + 1) * a.K) : n1;
+    const int count = even_steps(seg_end - n, batch_steps(RX)), end = n + count;
+    T* dst = src == a.buf[0] ? a.buf[1] : a.buf[0];
+    if (ckpt && a.mode == 2 && end % a.K == 0 && end < a.N)
+      dst = a.ckpt + size_t(end / a.K - 1) * a.state_elems;
     T* rec = n >= rec0 ? a.rec + size_t(n - rec0) * a.rec_elems : nullptr;
     if (n == 0)
-      forward_sweep_tiles<T, true>(a, nullptr, dst, rec);
+      forward_sweep<T, RX, RY, true>(lds, a, nullptr, dst, rec, count);
     else
-      forward_sweep_tiles<T, false>(a, src, dst, rec);
+      forward_sweep<T, RX, RY, false>(lds, a, src, dst, rec, count);
     src = dst;
-    if (n + 1 < n1 || sync_last) *alive = grid_sync(a.barrier, nblocks, a.timeout);
+    n = end;
+    if (n < n1 || sync_last) *alive = grid_sync(a.barrier, nblocks, a.timeout);
   }
 }
 
 // The persistent grids are sized from the runtime's occupancy query, and
 // every work-group must be resident for the grid barrier to complete.  The
-// declared minimum of wavefronts per SIMD (8 for FP32, 4 for FP64) keeps
-// the compiler's vector AND scalar register allocation within what that
-// occupancy allows; without it the scalar-loaded descriptors and
-// coefficients took 106 SGPRs, which leaves room for 7 wavefronts per SIMD
-// where the vector registers alone allow 8.
-template <typename T>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 8 : 4) void batch_forward_kernel(BatchArgs<T> a) {
+// declared wavefronts per SIMD (8 for FP32, 4 for FP64: two and one
+// work-groups of 1024 a compute unit) keep the compiler's vector AND scalar
+// register allocation within what that occupancy allows.
+#define MRT_BATCH_BOUNDS                                   \
+  __attribute__((amdgpu_flat_work_group_size(1024, 1024),  \
+                 amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 4)))
+
+template <typename T, int RX>
+__global__ MRT_BATCH_BOUNDS void batch_forward_kernel(BatchArgs<T> a) {
+  __shared__ Exchange<T, RX, 1024 / RX, false> lds;
   bool alive = true;
   // record the last segment (it is the first one the adjoint needs)
   const int rec0 = a.mode > 0 ? (a.nseg - 1) * a.K : a.N;
-  forward_steps<T>(a, 0, a.N, rec0, nullptr, true, false, gridDim.x, &alive);
+  forward_pass<T, RX, 1024 / RX>(lds, a, 0, a.N, rec0, nullptr, true, false, gridDim.x, &alive);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 8 : 4) void batch_adjoint_kernel(BatchArgs<T> a) {
+template <typename T, int RX>
+__global__ MRT_BATCH_BOUNDS void batch_adjoint_kernel(BatchArgs<T> a) {
+  constexpr int RY = 1024 / RX;
+  __shared__ Exchange<T, RX, RY, false> lds;
   bool alive = true;
   const unsigned nb = gridDim.x;
   const T* asrc = nullptr;
@@ -257,19 +278,32 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 8 : 4) void batch_adjoint_ker
     const int n0 = seg * a.K, n1 = min(a.N, n0 + a.K);
     if (seg != a.rec_seg) {
       const T* src = seg == 0 ? nullptr : a.ckpt + size_t(seg - 1) * a.state_elems;
-      forward_steps<T>(a, n0, n1, n0, src, false, true, nb, &alive);
+      forward_pass<T, RX, RY>(lds, a, n0, n1, n0, src, false, true, nb, &alive);
     }
-    for (int n = n1 - 1; n >= n0 && alive; --n) {
-      T* dst = n == 0 ? nullptr : a.abuf[n & 1];
+    for (int n = n1 - 1; n >= n0 && alive;) {
+      const int count = even_steps(n - n0 + 1, batch_steps(RX)), next = n - count;
+      T* dst = next < 0 ? nullptr : (asrc == a.abuf[0] ? a.abuf[1] : a.abuf[0]);
       const T* rec = a.rec + size_t(n - n0) * a.rec_elems;
       if (n == a.N - 1)
-        adjoint_sweep_tiles<T, true>(a, nullptr, dst, rec);
+        adjoint_sweep<T, RX, RY, true>(lds, a, nullptr, dst, rec, n, count);
       else
-        adjoint_sweep_tiles<T, false>(a, asrc, dst, rec);
+        adjoint_sweep<T, RX, RY, false>(lds, a, asrc, dst, rec, n, count);
       asrc = dst;
-      if (n > 0) alive = grid_sync(a.barrier, nb, a.timeout);
+      n = next;
+      if (n >= 0) alive = grid_sync(a.barrier, nb, a.timeout);
     }
   }
+}
+
+// Node of this thread in tile t of the one-pass kernels; false if outside
+// its lattice.
+__device__ __forceinline__ bool tile_node(const BatchTile& tl, int tile_w,
+                                          const Geometry& g, NodeIdx& n) {
+  const int x = tl.x0 + int(threadIdx.x) % tile_w;
+  const int y = tl.y0 + int(threadIdx.x) / tile_w;
+  if (x >= g.nx || y >= g.ny) return false;
+  make_node(g, x, y, n);
+  return true;
 }
 
 template <typename T>
@@ -371,23 +405,49 @@ __global__ void barrier_reset_kernel(BarrierState* bs) {
 
 }  // namespace
 
+namespace {
+// Calls f(integral constant region width).
+template <typename F>
+void dispatch_width(int w, F f) {
+  if (w == 64)
+    f(std::integral_constant<int, 64>());
+  else if (w == 128)
+    f(std::integral_constant<int, 128>());
+  else
+    f(std::integral_constant<int, 256>());
+}
+}  // namespace
+
 template <typename T>
 int batch_max_blocks_per_cu(int which) {
-  int n = 0;
-  hipError_t e = which == 0
-      ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_forward_kernel<T>, 256, 0)
-      : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_adjoint_kernel<T>, 256, 0);
-  return e == hipSuccess ? n : 0;
+  int least = 1 << 30;
+  for (int w : {64, 128, 256}) {
+    int n = 0;
+    hipError_t e = hipSuccess;
+    dispatch_width(w, [&](auto W) {
+      e = which == 0 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                           &n, batch_forward_kernel<T, W()>, 1024, 0)
+                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                           &n, batch_adjoint_kernel<T, W()>, 1024, 0);
+    });
+    if (e != hipSuccess) return 0;
+    least = std::min(least, n);
+  }
+  return least;
 }
 
 template <typename T>
 void launch_batch_forward(const BatchArgs<T>& a, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL(batch_forward_kernel<T>, dim3(blocks), dim3(256), 0, s, a);
+  dispatch_width(a.tile_w, [&](auto W) {
+    hipLaunchKernelGGL((batch_forward_kernel<T, W()>), dim3(blocks), dim3(1024), 0, s, a);
+  });
 }
 
 template <typename T>
 void launch_batch_adjoint(const BatchArgs<T>& a, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL(batch_adjoint_kernel<T>, dim3(blocks), dim3(256), 0, s, a);
+  dispatch_width(a.tile_w, [&](auto W) {
+    hipLaunchKernelGGL((batch_adjoint_kernel<T, W()>), dim3(blocks), dim3(1024), 0, s, a);
+  });
 }
 
 template <typename T>

@@ -48,9 +48,10 @@ struct mrt_batch {
   size_t* dfoff = nullptr;
   double* dalpha = nullptr;
   BatchTile* tiles = nullptr;
+  BatchTile* regions = nullptr;
   int* tbeg = nullptr;
-  size_t tile_cap = 0;
-  int ntiles = 0, tile_w = 64, bpc = 0, max_bpc_f = 0, max_bpc_a = 0, n_cu = 0;
+  size_t tile_cap = 0, region_cap = 0;
+  int ntiles = 0, nregions = 0, tile_w = 64, bpc = 0, max_bpc_f = 0, max_bpc_a = 0, n_cu = 0;
   double* partials = nullptr;
   double* res_cost = nullptr;
   double* res_grad = nullptr;
@@ -77,7 +78,9 @@ template <typename T>
 BatchArgs<T> make_args(mrt_batch* b) {
   BatchArgs<T> a{};
   a.tiles = b->tiles;
+  a.regions = b->regions;
   a.ntiles = b->ntiles;
+  a.nregions = b->nregions;
   a.tile_w = b->tile_w;
   a.coef = static_cast<const mrt::ModelCoef<T>*>(b->coef);
   a.L = b->dL;
@@ -110,6 +113,10 @@ BatchArgs<T> make_args(mrt_batch* b) {
   return a;
 }
 
+// Columns and rows that a region of width w owns.
+int owned_w(int w) { return w - 2 * (mrt::batch_steps(w) - 1); }
+int owned_h(int w) { return 1024 / w - 2 * (mrt::batch_steps(w) - 1); }
+
 int build_tiles(mrt_batch* b, int tile_w) {
   if (tile_w != 64 && tile_w != 128 && tile_w != 256)
     return err(MRT_EINVAL, "tile_w must be 64, 128 or 256");
@@ -127,6 +134,14 @@ int build_tiles(mrt_batch* b, int tile_w) {
   HIP_OK(hipMemcpy(b->tiles, t.data(), t.size() * sizeof(BatchTile), hipMemcpyHostToDevice));
   HIP_OK(hipMemcpy(b->tbeg, beg.data(), beg.size() * sizeof(int), hipMemcpyHostToDevice));
   b->ntiles = int(t.size());
+  t.clear();
+  for (int k = 0; k < b->count; ++k)
+    for (int y = 0; y < b->L[k]; y += owned_h(tile_w))
+      for (int x = 0; x < b->L[k]; x += owned_w(tile_w))
+        t.push_back({k, y, x, b->L[k], (unsigned long long)b->foff[k], 0ull});
+  if (t.size() > b->region_cap) return err(MRT_EINVAL, "region table overflow");
+  HIP_OK(hipMemcpy(b->regions, t.data(), t.size() * sizeof(BatchTile), hipMemcpyHostToDevice));
+  b->nregions = int(t.size());
   b->tile_w = tile_w;
   b->graph_valid = false;
   return MRT_OK;
@@ -134,13 +149,25 @@ int build_tiles(mrt_batch* b, int tile_w) {
 
 int persistent_blocks(const mrt_batch* b, int max_bpc) {
   const int bpc = std::max(1, std::min(b->bpc > 0 ? b->bpc : max_bpc, max_bpc));
-  return std::max(1, std::min(b->ntiles, b->n_cu * bpc));
+  return std::max(1, std::min(b->nregions, b->n_cu * bpc));
 }
 
 int launch_error() {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return err(MRT_EHIP, std::string("launch failed: ") + hipGetErrorString(e));
   return MRT_OK;
+}
+
+// The buffer that holds the state after the last step of a forward pass in
+// segments of K (the whole pass in one when K >= N): the pass alternates
+// between the two from the first, and a checkpoint is neither.
+int last_buffer(const mrt_batch* b, int K) {
+  int cur = -1;
+  for (int n = 0; n < b->N;) {
+    n += mrt::even_steps(std::min(b->N, (n / K + 1) * K) - n, mrt::batch_steps(b->tile_w));
+    cur = n % K == 0 && n < b->N ? -1 : (cur == 0 ? 1 : 0);
+  }
+  return cur;
 }
 
 // Enqueue one gradient iteration for every instance on stream s.
@@ -151,9 +178,7 @@ int enqueue_iteration(mrt_batch* b, double zeta, hipStream_t s) {
   const int ba = persistent_blocks(b, b->max_bpc_a);
   const int bs = std::min(b->ntiles, 4096);
   mrt::launch_batch_forward<T>(a, bf, s);
-  // the last forward state is buf[(N-1) & 1] (the final step never closes a
-  // checkpoint segment)
-  mrt::launch_batch_finalize<T>(a, static_cast<const T*>(b->buf[(b->N - 1) & 1]), bs, s);
+  mrt::launch_batch_finalize<T>(a, static_cast<const T*>(b->buf[last_buffer(b, b->K)]), bs, s);
   mrt::launch_batch_cost<T>(a, 1, b->partials, b->tbeg, b->res_cost, b->count, bs, s);
   mrt::launch_batch_adjoint<T>(a, ba, s);
   mrt::launch_batch_cost<T>(a, 2, b->partials, b->tbeg, b->res_grad, b->count, bs, s);
@@ -216,7 +241,7 @@ int mrt_batch_create(const mrt_problem* problems, int32_t count,
   b->elem = g0.dtype == MRT_F64 ? 8 : 4;
   b->N = g0.nsteps;
   b->probs.assign(problems, problems + count);
-  size_t ntile_max = 0;
+  size_t ntile_max = 0, nregion_max = 0;
   for (int k = 0; k < count; ++k) {
     b->L.push_back(problems[k].grid.nx);
     b->foff.push_back(b->F);
@@ -225,6 +250,11 @@ int mrt_batch_create(const mrt_problem* problems, int32_t count,
     size_t most = 0;  // partial tiles make the widest tiles the most numerous on small lattices
     for (size_t w : {64, 128, 256}) most = std::max(most, ((Lk + w - 1) / w) * ((Lk + 256 / w - 1) / (256 / w)));
     ntile_max += most;
+    most = 0;
+    for (int w : {64, 128, 256})
+      most = std::max(most, ((Lk + owned_w(w) - 1) / owned_w(w)) *
+                                ((Lk + owned_h(w) - 1) / owned_h(w)));
+    nregion_max += most;
   }
   if (ckpt_every < 0) {  // forward solves only: no adjoint buffers, no record
     b->mode = 0;
@@ -272,6 +302,8 @@ int mrt_batch_create(const mrt_problem* problems, int32_t count,
   if (!rc) rc = alloc(count * sizeof(double), (void**)&b->dalpha);
   b->tile_cap = ntile_max;
   if (!rc) rc = alloc(ntile_max * sizeof(BatchTile), (void**)&b->tiles);
+  b->region_cap = nregion_max;
+  if (!rc) rc = alloc(nregion_max * sizeof(BatchTile), (void**)&b->regions);
   if (!rc) rc = alloc((count + 1) * sizeof(int), (void**)&b->tbeg);
   if (!rc) rc = alloc(ntile_max * mrt::kRedSlots * sizeof(double), (void**)&b->partials);
   if (!rc) rc = alloc(size_t(count) * mrt::kBatchSlots * sizeof(double), (void**)&b->res_cost);
@@ -508,12 +540,12 @@ int mrt_batch_forward(mrt_batch* b, void* stream) {
     BatchArgs<double> a = make_args<double>(b);
     a.mode = 0; a.K = a.N; a.nseg = 1;
     mrt::launch_batch_forward<double>(a, bf, s);
-    mrt::launch_batch_finalize<double>(a, static_cast<const double*>(b->buf[(b->N - 1) & 1]), bs, s);
+    mrt::launch_batch_finalize<double>(a, static_cast<const double*>(b->buf[last_buffer(b, b->N)]), bs, s);
   } else {
     BatchArgs<float> a = make_args<float>(b);
     a.mode = 0; a.K = a.N; a.nseg = 1;
     mrt::launch_batch_forward<float>(a, bf, s);
-    mrt::launch_batch_finalize<float>(a, static_cast<const float*>(b->buf[(b->N - 1) & 1]), bs, s);
+    mrt::launch_batch_finalize<float>(a, static_cast<const float*>(b->buf[last_buffer(b, b->N)]), bs, s);
   }
   int rc = launch_error();
   if (rc) return rc;

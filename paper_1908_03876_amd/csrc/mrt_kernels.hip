@@ -33,6 +33,7 @@
 
 #include "mrt_device.h"
 #include "mrt_internal.h"
+#include "mrt_region.h"
 
 namespace mrt {
 namespace {
@@ -73,46 +74,6 @@ __global__ void build_link_kernel(Geometry g, int periodic,
 }
 
 // ------------------------------------------------------- time-step kernels
-//
-// A launch advances several time steps.  A work-group owns a region of
-// RX x RY nodes, one per thread; the first step gathers from memory, the
-// steps in between exchange their populations through LDS (u and v of a
-// direction side by side, one 8- or 16-byte access each), and the last one
-// stores.  With K steps the K - 1 outer rings of the region go stale one
-// after the other: they recompute what the neighbouring regions own, so a
-// region stores the RX - 2(K-1) by RY - 2(K-1) nodes inside them, and a
-// wavefront whose rows are stale leaves the work to the others.
-//
-// The wide regions are 64 x 16 (a wavefront is one row, so rows are scalar
-// addresses) for the 72 bytes a node of two species in FP32, 1024 threads and
-// two work-groups a compute unit: 64 registers a thread, 67 to 75 KB of LDS.
-// Twice as wide nodes take 32 x 16.  Lattices of a few thousand nodes take
-// 16 x 16 regions, which spread them over the chip.  The explicit second-order
-// source also reads the previous step's kinetics of its nodes, which a
-// neighbouring region may not find overwritten: where the tape holds only one
-// buffer for them it takes one step at a time, in rows of 256 nodes (kRows).
-//
-// What bounds it: with 4 steps a launch the state's traffic falls from 144 to
-// 36 B a node and step, and the vector units, of which the rings take 30%,
-// come level with memory.  Stores are ordinary ones: a region's rows begin
-// anywhere in a 64-byte chunk, and two regions' parts of a chunk merge in L2
-// (with non-temporal stores each part went to memory by itself: 65 us a step
-// at 2048^2 instead of 55).  Measured at 2048^2, masked, FP32, in us a step:
-// forward with record 122 -> 55.8, AMRT step 125 -> 65.4 (periodic: 53.5 and
-// 53.3); at 1024^2 27 -> 13.7 and 36 -> 18.3; at 128^2 4.4 -> 1.9.
-
-template <typename T>
-struct alignas(2 * sizeof(T)) Pair {
-  T u, v;
-};
-
-template <typename T, int RX, int RY, bool W3>
-struct Exchange {
-  static constexpr int kNodes = RX * RY;
-  static constexpr int kPad = RX + 1;  // the outer ring reads past the region
-  Pair<T> uv[8 * kNodes + 2 * kPad];
-  T w[W3 ? 8 * kNodes + 2 * kPad : 1];
-};
 
 // One thread's node of a region.  Regions that reach past a lattice edge
 // wrap around it, periodic or not: across a wall nothing is taken from the
@@ -121,10 +82,6 @@ struct RegionNode {
   int x, y;
   bool owner;  // its results are stored by this thread
 };
-
-// Regions of one row and one step.
-template <int RY>
-constexpr bool kRows = RY == 1;
 
 template <int RX, int RY>
 __device__ __forceinline__ RegionNode region_node(const Geometry& g, const TileGrid& tg,
@@ -156,6 +113,10 @@ __device__ __forceinline__ RegionNode region_node(const Geometry& g, const TileG
   r.y = r.y < 0 ? r.y + g.ny : r.y;
   if (RX % 64 == 0) r.y = __builtin_amdgcn_readfirstlane(r.y);
   return r;
+}
+
+__device__ __forceinline__ Steps steps_of(const TileGrid& tg) {
+  return {tg.steps, tg.steps - 1};
 }
 
 // The node again, at the end of a launch, with the plane size it is
@@ -198,117 +159,6 @@ __device__ __forceinline__ bool links(const Geometry& g, const NodeIdx& n, unsig
   return true;
 }
 
-template <typename T>
-__device__ __forceinline__ void swap_(T& a, T& b) {
-  const T t = a;
-  a = b;
-  b = t;
-}
-
-// Streaming between two steps of a launch: the populations of every node go
-// to LDS (give), each node takes back those its neighbours send it, or its own
-// opposite one where the neighbour is a wall (ADJ: the transposed stream,
-// from x + e_i).
-template <typename T, int RX, int RY, bool W3>
-__device__ __forceinline__ void give(Exchange<T, RX, RY, W3>& lds, const T fu[9], const T fv[9],
-                                     const T fw[9]) {
-  constexpr int N = RX * RY, P = RX + 1;
-  __syncthreads();  // the reads of the exchange before are done
-#pragma unroll
-  for (int i = 1; i < 9; ++i) {
-    lds.uv[P + (i - 1) * N + int(threadIdx.x)] = Pair<T>{fu[i], fv[i]};
-    if (W3) lds.w[P + (i - 1) * N + int(threadIdx.x)] = fw[i];
-  }
-  __syncthreads();
-}
-
-template <bool WALLS, bool ADJ, typename T, int RX, int RY, bool W3>
-__device__ __forceinline__ void take(const Exchange<T, RX, RY, W3>& lds, T fu[9], T fv[9],
-                                     T fw[9], unsigned lm) {
-  constexpr int N = RX * RY, P = RX + 1;
-  constexpr int ex[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
-  constexpr int ey[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
-  auto one = [&](int i) {
-    const int o = P + (i - 1) * N + (ADJ ? 1 : -1) * (ex[i] + ey[i] * RX) + int(threadIdx.x);
-    const Pair<T> p = lds.uv[o];
-    fu[i] = p.u;
-    fv[i] = p.v;
-    if (W3) fw[i] = lds.w[o];
-  };
-  if (WALLS && __builtin_amdgcn_ballot_w64((lm & 0x1FEu) != 0u) != 0ull) {
-    // opposite populations change places, then those from fluid neighbours
-    // are read over them
-#pragma unroll
-    for (int i = 1; i < 9; ++i) {
-      if (i < opp(i)) {
-        swap_(fu[i], fu[opp(i)]);
-        swap_(fv[i], fv[opp(i)]);
-        if (W3) swap_(fw[i], fw[opp(i)]);
-      }
-    }
-#pragma unroll
-    for (int i = 1; i < 9; ++i)
-      if (!((lm >> (ADJ ? opp(i) : i)) & 1u)) one(i);
-  } else {
-#pragma unroll
-    for (int i = 1; i < 9; ++i) one(i);
-  }
-}
-
-// Does this wavefront still hold rows that step s of a launch needs?  The
-// outer rows go stale with their rings.
-template <int RX, int RY>
-__device__ __forceinline__ bool live_rows(int s) {
-  const int lo = __builtin_amdgcn_readfirstlane(threadIdx.x / 64) * 64 / RX;
-  const int hi = lo + (RX < 64 ? 64 / RX : 1) - 1;
-  return hi >= s && lo < RY - s;
-}
-
-// A wavefront of stale rows after step s: it only meets the others at the
-// barriers of the exchanges to come.
-__device__ __forceinline__ void retire(const TileGrid& tg, int s) {
-  for (; s < tg.steps - 2; ++s) {
-    __syncthreads();
-    __syncthreads();
-  }
-}
-
-// The initial populations of a lattice with walls enter the collision as
-// rounded products: the compiler may not contract them into its sums.  (On
-// the others it may.  Either way is as near the exact value; each kind of
-// lattice keeps its bits.)
-template <bool W3, typename T>
-__device__ __forceinline__ void keep_rounded(T fu[9], T fv[9], T fw[9]) {
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    asm volatile("" : "+v"(fu[i]), "+v"(fv[i]));
-    if (W3) asm volatile("" : "+v"(fw[i]));
-  }
-}
-
-// The gradient accumulator of a thread's node over the steps of a launch: in
-// a register pair, or (IN_LDS) in LDS, where the adjoint's walls leave no
-// registers for it (they went to scratch memory: 82 us a step instead of 58
-// at 2048 x 2048).
-template <bool IN_LDS, int N>
-struct Accumulator {
-  double v;
-  __device__ __forceinline__ void set(double x) { v = x; }
-  __device__ __forceinline__ void add(double x) { v += x; }
-  __device__ __forceinline__ double get() { return v; }
-};
-template <int N>
-struct Accumulator<true, N> {
-  double* p;
-  __device__ __forceinline__ Accumulator() {
-    __shared__ double slots[N];
-    p = slots + threadIdx.x;
-  }
-  __device__ __forceinline__ void set(double x) { *p = x; }
-  __device__ __forceinline__ void add(double x) { *p += x; }
-  __device__ __forceinline__ double get() { return *p; }
-};
-
 // A node's populations take more than the 72 bytes of two species in FP32.
 template <typename T, int VAR>
 constexpr bool kWide = sizeof(T) == 8 || VAR == kVarThree;
@@ -333,7 +183,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void forward_kernel(Geometry g, Mod
   NodeIdx n;
   make_node(g, r.x, r.y, n);
   unsigned lm = 0;
-  T fu[9], fv[9], fw[9], rec[5], lag[2] = {T(0), T(0)}, c = T(0);
+  T fu[9], fv[9], fw[9], lag[2] = {T(0), T(0)}, c = T(0);
   if (WALLS && !links<kRows<RY>, A>(g, n, lm)) return;
   if (kRows<RY> && WALLS && (lm & 1u)) {
     // a solid node loads nothing and collides zeros: it takes part in the
@@ -350,30 +200,9 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void forward_kernel(Geometry g, Mod
       lag[1] = *own_at<A>(a.lag + g.plane, n);
     }
   }
-  auto record = [&](int s) {
-    if (a.rec != nullptr && r.owner)
-      store_record<A, VAR, kRows<RY>>(g, n, a.rec + size_t(s) * a.rec_stride, rec);
-  };
-  int s = 0;
-  if (FIRST) {  // step 0 on its own: it differs for the second-order sources
-    if (WALLS) keep_rounded<W3>(fu, fv, fw);
-    forward_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, true);
-    record(0);
-    if (!kRows<RY> && tg.steps > 1) {
-      give(lds, fu, fv, fw);
-      if (!live_rows<RX, RY>(1)) return retire(tg, 0);
-      take<WALLS, false>(lds, fu, fv, fw, lm);
-    }
-    s = 1;
-  }
-  for (; s < tg.steps; ++s) {
-    forward_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, false);
-    record(s);
-    if (kRows<RY> || s + 1 == tg.steps) break;
-    give(lds, fu, fv, fw);
-    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
-    take<WALLS, false>(lds, fu, fv, fw, lm);
-  }
+  if (!forward_steps<WALLS, VAR, A, FIRST>(lds, g, n, lm, m, c, r.owner, fu, fv, fw, lag, a.rec,
+                                           a.rec_stride, steps_of(tg)))
+    return;
   if (!node_again<RX, RY>(g, tg, n)) return;
   if (LAG) {
     *own_at<A>(a.lag_out, n) = lag[0];
@@ -481,29 +310,20 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
   NodeIdx n;
   make_node(g, r.x, r.y, n);
   unsigned lm = 0;
-  T nu[9], nv[9], nw[9], rec[5], mu[2] = {T(0), T(0)};
+  T nu[9], nv[9], nw[9], mu[2] = {T(0), T(0)};
   Accumulator<WALLS && sizeof(T) == 4 && !kRows<RY>, RX * RY> sum;
-  const T* in = a.rec;
   constexpr bool fresh = FIRST && !IMPL;  // the sweep's first step: g starts at zero
   if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) return;
   if (kRows<RY> && WALLS && !FIRST && a.step > 0 && (lm & 1u)) return;
   adjoint_gather<A, WALLS, VAR, FIRST, T>(g, n, a.src, a.seed_u, a.seed_v, lm, nu, nv, nw);
-  load_record<A, VAR>(g, n, in, rec);
   if (LAG && !FIRST) {
     mu[0] = *own_at<A>(a.mu, n);
     mu[1] = *own_at<A>(a.mu + g.plane, n);
   }
   sum.set(r.owner && !fresh ? *own_at<A>(a.g, n) : 0.0);
-  for (int s = 0;; ++s) {
-    sum.add(double(adjoint_collide<T, WALLS, VAR>(m, nu, nv, nw, rec, mu, FIRST && s == 0,
-                                           a.step - s == 0)));
-    if (kRows<RY> || s + 1 == tg.steps) break;
-    in -= a.rec_stride;
-    load_record<A, VAR>(g, n, in, rec);
-    give(lds, nu, nv, nw);
-    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
-    take<WALLS, true>(lds, nu, nv, nw, lm);
-  }
+  if (!adjoint_steps<WALLS, VAR, A, FIRST>(lds, g, n, lm, m, a.step, nu, nv, nw, mu, sum, a.rec,
+                                           a.rec_stride, steps_of(tg)))
+    return;
   if (!node_again<RX, RY>(g, tg, n)) return;
   const bool solid = WALLS && (lm & 1u);
   if (solid) {
@@ -554,6 +374,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCo
     lag[0] = *own_at<A>(a.dlag, n);
     lag[1] = *own_at<A>(a.dlag + g.plane, n);
   }
+  const Steps st = steps_of(tg);
   int s = 0;
   if (FIRST) {
     tlm_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, true);
@@ -561,7 +382,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCo
       in += a.rec_stride;
       load_record<A, VAR>(g, n, in, rec);
       give(lds, fu, fv, fw);
-      if (!live_rows<RX, RY>(1)) return retire(tg, 0);
+      if (!live_rows<RX, RY>(st, 1)) return void(retire(st, 0));
       take<WALLS, false>(lds, fu, fv, fw, lm);
     }
     s = 1;
@@ -572,7 +393,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCo
     in += a.rec_stride;
     load_record<A, VAR>(g, n, in, rec);
     give(lds, fu, fv, fw);
-    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
+    if (!live_rows<RX, RY>(st, s + 1)) return void(retire(st, s));
     take<WALLS, false>(lds, fu, fv, fw, lm);
   }
   if (!node_again<RX, RY>(g, tg, n) || (WALLS && (lm & 1u))) return;
@@ -607,13 +428,14 @@ __global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, 
   pull_species<A, FIRST>(g, n, m.v, a.src + 9 * g.plane, static_cast<const T*>(nullptr), fq);
   load_record<A, kVarFirst>(g, n, in, rec);
   if (r.owner && !FIRST) sum = *own_at<A>(a.g, n);
+  const Steps st = steps_of(tg);
   for (int s = 0;; ++s) {
     sum += double(cadj_collide<T>(m, cc, fp, fq, rec));
     if (kRows<RY> || s + 1 == tg.steps) break;
     in -= a.rec_stride;
     load_record<A, kVarFirst>(g, n, in, rec);
     give(lds, fp, fq, static_cast<T*>(nullptr));
-    if (!live_rows<RX, RY>(s + 1)) return retire(tg, s);
+    if (!live_rows<RX, RY>(st, s + 1)) return void(retire(st, s));
     take<WALLS, false>(lds, fp, fq, static_cast<T*>(nullptr), lm);
   }
   if (!node_again<RX, RY>(g, tg, n)) return;
