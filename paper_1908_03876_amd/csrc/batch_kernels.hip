@@ -188,7 +188,8 @@ __device__ __forceinline__ void forward_sweep(Exchange<T, RX, RY, false>& lds,
     pull_species<kRow, FIRST>(r.g, r.n, m.v, s + 9 * r.g.plane, a.v0 + r.fo, fv);
     const T c = *own_at<kRow>(a.ctrl + r.fo, r.n);
     T* const nil = nullptr;
-    if (!forward_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, 0u, m, c, r.owner, fu, fv,
+    unsigned open = 0u;  // no walls
+    if (!forward_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, open, m, c, r.owner, fu, fv,
                                                       nil, nil, rec ? rec + 3 * r.fo : nil,
                                                       a.rec_elems, {count, batch_steps(RX) - 1}))
       return;
@@ -208,16 +209,16 @@ __device__ __forceinline__ void adjoint_sweep(Exchange<T, RX, RY, false>& lds,
     const ModelCoef<T> m = uniform_load(a.coef + r.k);
     T nu[9], nv[9];
     T* const nil = nullptr;
+    unsigned open = 0u;  // no walls
     adjoint_gather<kRow, false, kVarFirst, FIRST, T>(r.g, r.n, src + 18 * r.fo, a.seed_u + r.fo,
                                                      nullptr, 0u, nu, nv, nil);
-    Accumulator<false, RX * RY> sum;
-    sum.set(r.owner && !FIRST ? *own_at<kRow>(a.gacc + r.fo, r.n) : 0.0);
-    if (!adjoint_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, 0u, m, step, nu, nv, nil,
+    double sum = r.owner && !FIRST ? *own_at<kRow>(a.gacc + r.fo, r.n) : 0.0;
+    if (!adjoint_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, open, m, step, nu, nv, nil,
                                                       nil, sum, rec + 3 * r.fo, a.rec_elems,
                                                       {count, batch_steps(RX) - 1}))
       return;
     if (!r.owner) return;
-    *own_at<kRow>(a.gacc + r.fo, r.n) = sum.get();
+    *own_at<kRow>(a.gacc + r.fo, r.n) = sum;
     if (!dst) return;
     T* d = dst + 18 * r.fo;
     store_species<kRow, false, true>(r.g, r.n, nu, d, 0u);

@@ -375,9 +375,9 @@ __device__ __forceinline__ void forward_collide(const ModelCoef<T>& m, T fu[9], 
   constexpr bool W3 = VAR == kVarThree;
   constexpr bool LAG = VAR == kVarExplicit;
   // macroscopic values (UGS) and the first moment of v
-  T u = T(0), v = T(0);
+  T u = fu[0], v = fv[0];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
+  for (int i = 1; i < 9; ++i) {
     u += fu[i];
     v += fv[i];
   }
@@ -392,8 +392,9 @@ __device__ __forceinline__ void forward_collide(const ModelCoef<T>& m, T fu[9], 
   }
   T wv = T(0), kx = T(0), ky = T(0);
   if (W3) {
+    wv = fw[0];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) wv += fw[i];
+    for (int i = 1; i < 9; ++i) wv += fw[i];
     kx = fw[1] - fw[3] + fw[5] - fw[6] - fw[7] + fw[8];
     ky = fw[2] - fw[4] + fw[5] + fw[6] - fw[7] - fw[8];
     r[3] = kx;
@@ -446,13 +447,16 @@ __device__ __forceinline__ void store_record(const Geometry& g, const NodeIdx& n
     put<NT>(own_at<A>(rec + size_t(k) * g.plane, n), r[k]);
 }
 
-// Read once: non-temporal.
-template <Lanes A, int VAR, typename T>
+// Non-temporal (NT) for a record that one thread reads; regions share the
+// records of their rings.
+template <Lanes A, int VAR, bool NT = false, typename T>
 __device__ __forceinline__ void load_record(const Geometry& g, const NodeIdx& n,
                                             const T* __restrict__ rec, T r[5]) {
 #pragma unroll
-  for (int k = 0; k < (VAR == kVarThree ? 5 : 3); ++k)
-    r[k] = __builtin_nontemporal_load(own_at<A>(rec + size_t(k) * g.plane, n));
+  for (int k = 0; k < (VAR == kVarThree ? 5 : 3); ++k) {
+    const T* p = own_at<A>(rec + size_t(k) * g.plane, n);
+    r[k] = NT ? __builtin_nontemporal_load(p) : *p;
+  }
 }
 
 // Tangent-linear step (sensitivity LBE, LIBEG-V) at a node: the derivative
@@ -478,9 +482,9 @@ __device__ __forceinline__ void tlm_collide(const ModelCoef<T>& m, T fu[9], T fv
   constexpr bool LAG = VAR == kVarExplicit;
   constexpr bool W3 = VAR == kVarThree;
   const T u = r[0], jx = r[1], jy = r[2];
-  T du = T(0), dv = T(0);
+  T du = fu[0], dv = fv[0];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
+  for (int i = 1; i < 9; ++i) {
     du += fu[i];
     dv += fv[i];
   }
@@ -501,8 +505,9 @@ __device__ __forceinline__ void tlm_collide(const ModelCoef<T>& m, T fu[9], T fv
   T dw = T(0);
   if (W3) {
     const T kx = r[3], ky = r[4];
+    dw = fw[0];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) dw += fw[i];
+    for (int i = 1; i < 9; ++i) dw += fw[i];
     const T dkx = fw[1] - fw[3] + fw[5] - fw[6] - fw[7] + fw[8];
     const T dky = fw[2] - fw[4] + fw[5] + fw[6] - fw[7] - fw[8];
     dax += du * dot2(m.bw00, kx, m.bw01, ky) + u * dot2(m.bw00, dkx, m.bw01, dky);
@@ -549,9 +554,9 @@ template <typename T>
 __device__ __forceinline__ T cadj_collide(const ModelCoef<T>& m, const CadjCoef<T>& cc, T fp[9],
                                           T fq[9], const T r[5]) {
   const T u = r[0], jvx = r[1], jvy = r[2];
-  T P = T(0), Qv = T(0);
+  T P = fp[0], Qv = fq[0];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
+  for (int i = 1; i < 9; ++i) {
     P += fp[i];
     Qv += fq[i];
   }

@@ -62,9 +62,11 @@ struct StepPlan {
 // one step a launch, for variant 2 with a single buffer of kinetics).
 StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool one);
 
-// The regions of a launch: ntx across, ntiles in all, `steps` steps each.
+// The regions of a launch: ntx across, ntiles in all, `steps` steps each;
+// inv_ntx = (2^32 - 1) / ntx, rounded down.
 struct TileGrid {
   int steps, ntx, ntiles;
+  unsigned inv_ntx;
 };
 
 template <typename T>

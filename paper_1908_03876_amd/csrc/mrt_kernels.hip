@@ -88,7 +88,11 @@ __device__ __forceinline__ RegionNode region_node(const Geometry& g, const TileG
                                                   int tid) {
   const int halo = kRows<RY> ? 0 : tg.steps - 1;
   const int t = xcd_tile(blockIdx.x, tg.ntiles);
-  const int ty = t / tg.ntx, tx = t - ty * tg.ntx;
+  int ty = int((unsigned long long)unsigned(t) * tg.inv_ntx >> 32), tx = t - ty * tg.ntx;
+  if (tx >= tg.ntx) {  // the reciprocal is rounded down
+    ++ty;
+    tx -= tg.ntx;
+  }
   int dx = unsigned(tid) % RX, dy = unsigned(tid) / RX;
   if (RX % 64 == 0) dy = __builtin_amdgcn_readfirstlane(dy);  // a wavefront is one row
   RegionNode r;
@@ -311,7 +315,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
   make_node(g, r.x, r.y, n);
   unsigned lm = 0;
   T nu[9], nv[9], nw[9], mu[2] = {T(0), T(0)};
-  Accumulator<WALLS && sizeof(T) == 4 && !kRows<RY>, RX * RY> sum;
+  double sum = 0.0;
   constexpr bool fresh = FIRST && !IMPL;  // the sweep's first step: g starts at zero
   if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) return;
   if (kRows<RY> && WALLS && !FIRST && a.step > 0 && (lm & 1u)) return;
@@ -320,7 +324,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
     mu[0] = *own_at<A>(a.mu, n);
     mu[1] = *own_at<A>(a.mu + g.plane, n);
   }
-  sum.set(r.owner && !fresh ? *own_at<A>(a.g, n) : 0.0);
+  if (r.owner && !fresh) sum = *own_at<A>(a.g, n);
   if (!adjoint_steps<WALLS, VAR, A, FIRST>(lds, g, n, lm, m, a.step, nu, nv, nw, mu, sum, a.rec,
                                            a.rec_stride, steps_of(tg)))
     return;
@@ -333,7 +337,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
     if (a.adj_v0) *own_at<A>(a.adj_v0, n) = T(0);
     return;
   }
-  *own_at<A>(a.g, n) = sum.get();
+  *own_at<A>(a.g, n) = sum;
   if (LAG) {
     *own_at<A>(a.mu_out, n) = mu[0];
     *own_at<A>(a.mu_out + g.plane, n) = mu[1];
@@ -368,33 +372,35 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCo
   pull_species<A, FIRST>(g, n, m.v, a.src + 9 * g.plane, a.dv0, fv);
   if (W3)
     pull_species<A, FIRST>(g, n, m.w, a.src + 18 * g.plane, static_cast<const T*>(nullptr), fw);
-  load_record<A, VAR>(g, n, in, rec);
+  load_record<A, VAR, kRows<RY>>(g, n, in, rec);
   if (a.dc) c = *own_at<A>(a.dc, n);
   if (LAG && !FIRST) {
     lag[0] = *own_at<A>(a.dlag, n);
     lag[1] = *own_at<A>(a.dlag + g.plane, n);
   }
   const Steps st = steps_of(tg);
+  const int row = first_row<RX, RY>();
+  if (WALLS && !kRows<RY> && st.count > 1) lm = links_inside<RX, RY>(lm);
   int s = 0;
   if (FIRST) {
     tlm_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, true);
     if (!kRows<RY> && tg.steps > 1) {
-      in += a.rec_stride;
-      load_record<A, VAR>(g, n, in, rec);
-      give(lds, fu, fv, fw);
-      if (!live_rows<RX, RY>(st, 1)) return void(retire(st, 0));
-      take<WALLS, false>(lds, fu, fv, fw, lm);
+      in = scalar(in + a.rec_stride);
+      load_record<A, VAR, kRows<RY>>(g, n, in, rec);
+      give<WALLS, false>(lds, fu, fv, fw, lm);
+      if (!live_rows<RX, RY>(st, 1, row)) return void(retire(st, 0));
+      take<false>(lds, fu, fv, fw);
     }
     s = 1;
   }
   for (; s < tg.steps; ++s) {
     tlm_collide<T, VAR>(m, fu, fv, fw, c, rec, lag, false);
     if (kRows<RY> || s + 1 == tg.steps) break;
-    in += a.rec_stride;
-    load_record<A, VAR>(g, n, in, rec);
-    give(lds, fu, fv, fw);
-    if (!live_rows<RX, RY>(st, s + 1)) return void(retire(st, s));
-    take<WALLS, false>(lds, fu, fv, fw, lm);
+    in = scalar(in + a.rec_stride);
+    load_record<A, VAR, kRows<RY>>(g, n, in, rec);
+    give<WALLS, false>(lds, fu, fv, fw, lm);
+    if (!live_rows<RX, RY>(st, s + 1, row)) return void(retire(st, s));
+    take<false>(lds, fu, fv, fw);
   }
   if (!node_again<RX, RY>(g, tg, n) || (WALLS && (lm & 1u))) return;
   if (LAG) {
@@ -426,17 +432,19 @@ __global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, 
   if (WALLS) lm = link_word<A>(g, n);
   pull_species<A, FIRST>(g, n, m.u, a.src, a.seed_u, fp);
   pull_species<A, FIRST>(g, n, m.v, a.src + 9 * g.plane, static_cast<const T*>(nullptr), fq);
-  load_record<A, kVarFirst>(g, n, in, rec);
+  load_record<A, kVarFirst, kRows<RY>>(g, n, in, rec);
   if (r.owner && !FIRST) sum = *own_at<A>(a.g, n);
   const Steps st = steps_of(tg);
+  const int row = first_row<RX, RY>();
+  if (WALLS && !kRows<RY> && st.count > 1) lm = links_inside<RX, RY>(lm);
   for (int s = 0;; ++s) {
     sum += double(cadj_collide<T>(m, cc, fp, fq, rec));
     if (kRows<RY> || s + 1 == tg.steps) break;
-    in -= a.rec_stride;
-    load_record<A, kVarFirst>(g, n, in, rec);
-    give(lds, fp, fq, static_cast<T*>(nullptr));
-    if (!live_rows<RX, RY>(st, s + 1)) return void(retire(st, s));
-    take<WALLS, false>(lds, fp, fq, static_cast<T*>(nullptr), lm);
+    in = scalar(in - a.rec_stride);
+    load_record<A, kVarFirst, kRows<RY>>(g, n, in, rec);
+    give<WALLS, false>(lds, fp, fq, static_cast<T*>(nullptr), lm);
+    if (!live_rows<RX, RY>(st, s + 1, row)) return void(retire(st, s));
+    take<false>(lds, fp, fq, static_cast<T*>(nullptr));
   }
   if (!node_again<RX, RY>(g, tg, n)) return;
   if (WALLS && (lm & 1u)) {
@@ -649,6 +657,7 @@ TileGrid region_grid(const Geometry& g, const StepPlan& p) {
   t.steps = p.steps;
   const int wx = p.rx - 2 * (p.steps - 1), wy = p.ry - 2 * (p.steps - 1);
   t.ntx = (g.nx + wx - 1) / wx;
+  t.inv_ntx = 0xFFFFFFFFu / unsigned(t.ntx);
   t.ntiles = t.ntx * ((g.ny + wy - 1) / wy);
   return t;
 }
@@ -689,29 +698,37 @@ void dispatch_variant(int variant, F f) {
 
 }  // namespace
 
-// A launch costs about 4 us beside its steps (the gather, the stores and the
-// gap before it), and every further step costs a ring of each region.
+// A launch costs about 5 us beside its steps (the gather, the stores and the
+// gap before it), every further step costs a ring of each region, and the time
+// of a small lattice goes up in whole rounds of regions: with up to 256 of them
+// each has a compute unit to itself, with up to 512 two share one.  So: the
+// most steps whose regions fit one round (of 256 with 6 or 7 steps, of 512 with
+// 4 or 5), and 5 for the large lattices, where memory and the vector units come
+// level.  The small regions spread the smallest lattices over the chip.
 // Measured in us per forward step, FP32, steps per launch in brackets:
-//   2048^2  64x16 regions  136 (1)   85 (2)   61 (3)  53.5 (4)  51 (5)  59 (6)
-//    512^2                 9.1 (1)  7.1 (2)  5.4 (3)  4.6 (4)  5.3 (5)  5.5 (6)
-//    256^2                 7.2 (1)  5.0 (2)  3.9 (3)  3.3 (4)  2.8 (5)  2.6 (6)
-//          16x16 regions   3.0 (4)  2.9 (5)  3.6 (6)
-//    128^2 64x16 2.5 (6); 16x16  2.2 (4)  1.9 (5)  2.0 (6)
-// The wide regions use the chip as long as there are more of them than
-// compute units; below that the steps' latency counts, and it is shortest in
-// small regions spread over all of the chip.
+//   2048^2  64x16 regions  64.2 (3)  57.0 (4)  51.1 (5)  57.2 (6)
+//    550^2                  5.1 (3)   5.7 (4)   4.8 (5)   5.1 (6)
+//    512^2                  4.7 (3)   4.2 (4)   4.7 (5)   4.9 (6)
+//    448^2                  5.0 (3)   4.3 (4)   3.6 (5)   4.2 (6)
+//    256^2                  3.2 (3)   2.7 (4)   2.4 (5)   2.2 (6)
+//    200^2                  1.9 (6)   1.8 (7);  16x16  1.9 (4)  2.3 (5)
+//    128^2                  2.0 (6);  16x16     1.8 (4)   1.6 (5)   1.7 (6)
+//     64^2                  1.8 (7);  16x16     1.9 (4)   1.6 (5)   1.4 (7)
 StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool one) {
-  const bool wide = elem == 8 || variant == kVarThree;
-  const size_t nodes = size_t(g.nx) * g.ny;
-  StepPlan p;
-  p.ry = 16;
   if (one) return {256, 1, 1};
-  if (nodes <= 160 * 160) {
-    p.rx = 16;
-    p.steps = 5;
-  } else {
+  const bool wide = elem == 8 || variant == kVarThree;
+  auto regions = [&](int rx, int steps) {
+    return region_grid(g, StepPlan{rx, 16, steps}).ntiles;
+  };
+  StepPlan p{16, 16, 7};
+  while (p.steps > 4 && regions(16, p.steps) > 256) --p.steps;
+  if (regions(16, p.steps) > 256) {
     p.rx = wide ? 32 : 64;
-    p.steps = nodes <= 384 * 384 ? 6 : 4;
+    p.steps = regions(p.rx, 7) <= 256   ? 7
+              : regions(p.rx, 6) <= 256 ? 6
+              : regions(p.rx, 5) <= 512 ? 5
+              : regions(p.rx, 4) <= 512 ? 4
+                                        : 5;
   }
   // as many launches as that takes, their steps spread evenly
   const int launches = (left + p.steps - 1) / p.steps;
