@@ -23,9 +23,11 @@ struct BatchTile {
 
 // Steps that the sweeps take between two grid barriers, by the width of their
 // regions (width x 1024 / width nodes, of which batch_steps - 1 on each side
-// are recomputed): as many as leave a region two rows or more.
+// are recomputed): as many as leave a region two rows or more, and 5 of the
+// tallest, as for a large lattice by itself (4 and 5 are measured in
+// batch_kernels.hip).
 __host__ __device__ constexpr int batch_steps(int width) {
-  return width == 64 ? 4 : width == 128 ? 3 : 2;
+  return width == 64 ? 5 : width == 128 ? 3 : 2;
 }
 
 // Steps of the next launch (or barrier) of `left`, when as few launches as

@@ -9,9 +9,10 @@
 // single run.
 //
 // One step a barrier was bound by HBM (148 to 172 B a node and step at 63 to
-// 68% of 8 TB/s) and by the barrier itself (12 us).  Four steps a barrier,
-// 16 instances of 128^2 to 1024^2, N = 100, FP32: forward pass 16.6 -> 6.9
-// ms, adjoint pass with the recomputation 31.0 -> 14.7 ms.
+// 68% of 8 TB/s) and by the barrier itself (12 us).  16 instances of 128^2 to
+// 1024^2, N = 100, FP32: forward pass 16.6 ms, adjoint pass with the
+// recomputation 31.0 ms; with four steps a barrier 6.9 and 14.7, with five 6.5
+// and 13.7.
 //
 // The grid barrier spins with a time limit.  A wait that exceeds it (which
 // can only happen if the work-groups are not all resident) sets a sticky
