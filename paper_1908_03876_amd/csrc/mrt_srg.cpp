@@ -84,8 +84,8 @@ int launch_err() {
 }
 
 void forward(mrt_srg* s, const float* x, float* y, int B, int H, int W, hipStream_t st) {
-  mrt::launch_srg_l0_fwd(x, s->L[0].wb, s->L[0].b, s->act[0], B, H, W, s->s_in, st);
-  mrt::launch_srg_c32_fwd(s->act[0], s->L[1].wf, s->L[1].b, s->act[1], B, H, W, st);
+  mrt::launch_srg_head_fwd(x, s->L[0].wb, s->L[0].b, s->act[0], s->L[1].wf, s->L[1].b, s->act[1],
+                           B, H, W, s->s_in, st);
   mrt::launch_srg_c32_fwd(s->act[1], s->L[2].wf, s->L[2].b, s->act[2], B, H, W, st);
   mrt::launch_srg_l3_fwd(s->act[2], s->L[3].wb, s->L[3].b, y, B, H, W, s->s_out, st);
 }

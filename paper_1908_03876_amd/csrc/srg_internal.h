@@ -16,8 +16,10 @@ constexpr int kSrgThinBlocks = 1024;         // max blocks of the thin ones
 constexpr size_t kSrgThinPartDoubles = size_t(11) * kSrgThinBlocks * 32 + kSrgThinBlocks;
 
 // Hidden activations and gradients are BF16 channels-last [B][H][W][32].
-void launch_srg_l0_fwd(const float* x, const uint16_t* w, const float* b, uint16_t* out, int B,
-                       int H, int W, float iscale, hipStream_t s);
+// The first two layers: a0 from x, out from a0.
+void launch_srg_head_fwd(const float* x, const uint16_t* w0, const float* b0, uint16_t* a0,
+                         const uint16_t* wf, const float* b, uint16_t* out, int B, int H, int W,
+                         float iscale, hipStream_t s);
 void launch_srg_l0_bwd_data(const uint16_t* dz, const uint16_t* w, float* dx, int B, int H,
                             int W, float iscale, hipStream_t s);
 void launch_srg_l3_fwd(const uint16_t* a, const uint16_t* w, const float* b, float* y, int B,

@@ -123,80 +123,63 @@ __device__ __forceinline__ double block_sum_d(double v) {
 
 // ------------------------------------------------ first layer (1 -> 32)
 
-// a0 = bf16(tanh(b + W0 * (s_in x))), 32 channels.  A wavefront takes 64
-// consecutive pixels of one row as four tiles of 16.  Per tile the 32 x 9
-// weight matrix times the 9 x 16 window matrix is six
+// a0 = bf16(tanh(b + W0 * (s_in x))), 32 channels, in tiles of 16 pixels.  Per
+// tile the 32 x 9 weight matrix times the 9 x 16 window matrix is six
 // v_mfma_f32_16x16x4_f32 (FP32 operands and accumulation), which takes the
 // 288 multiply-adds per pixel off the vector ALU; the tanh stays there.
 // K-step ks takes the window row y + ks - 1, and its slot q < 3 the column
-// x + q - 1 (slot 3 is zero padding), so a k-step reads one wave-uniform
-// row and a tile's three k-steps share their column offsets.  Lane
-// (q, pixel) ends with channels 8q..8q+7 of its pixel and writes them with
-// one 16-byte store.
-__global__ __launch_bounds__(kB) void l0_fwd_kernel(const float* __restrict__ x,
-                                                    const uint16_t* __restrict__ w,
-                                                    const float* __restrict__ bias,
-                                                    uint16_t* __restrict__ out, int B, int H,
-                                                    int W, float iscale) {
-  const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
-  // (row, segment) units fit 32 bits: fields hold at most 2^28 pixels
-  const unsigned nseg = unsigned(W + 63) >> 6;
-  const unsigned unit = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (unit >= unsigned(B) * unsigned(H) * nseg) return;  // the whole wavefront
-  const int seg = int(unit % nseg);
-  const unsigned row = unit / nseg;  // image b, row y: b H + y
-  const int y = int(row % unsigned(H));
-  const float* xr[3];  // the three window rows, periodic
-#pragma unroll
-  for (int ks = 0; ks < 3; ++ks)
-    xr[ks] = x + size_t(row - y + wrap(y + ks - 1, H)) * W;
+// x + q - 1 (slot 3 is zero padding).  Lane (q, pixel) ends with channels
+// 8q..8q+7 of its pixel, 16 bytes.
+struct FirstLayer {
   float wa[2][3];  // A operands: W0[frag_row(mb, n)][3 ks + q], zero for q = 3
-#pragma unroll
-  for (int ks = 0; ks < 3; ++ks)
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      const float wv = bf16_to_f32(w[frag_row(mb, n) * 9 + 3 * ks + (q < 3 ? q : 2)]);
-      wa[mb][ks] = q < 3 ? wv : 0.f;
-    }
   f32x4 b0, b1;
+
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ w,
+                                       const float* __restrict__ bias, int q, int n) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    b0[i] = bias[8 * q + i];
-    b1[i] = bias[8 * q + 4 + i];
-  }
-  // the window values of all four tiles, loaded together; every address
-  // is in the row (lanes past a ragged row end and the padding slot read a
-  // valid pixel and use zero)
-  float v[4][3];
+    for (int ks = 0; ks < 3; ++ks)
 #pragma unroll
-  for (int tile = 0; tile < 4; ++tile) {
-    const int px = seg * 64 + tile * 16 + n;
-    const bool use = px < W && q < 3;
-    const int col = px < W ? wrap(px + (q < 3 ? q : 1) - 1, W) : 0;
+      for (int mb = 0; mb < 2; ++mb) {
+        const float wv = bf16_to_f32(w[frag_row(mb, n) * 9 + 3 * ks + (q < 3 ? q : 2)]);
+        wa[mb][ks] = q < 3 ? wv : 0.f;
+      }
 #pragma unroll
-    for (int ks = 0; ks < 3; ++ks) {
-      const float xv = xr[ks][col];
-      v[tile][ks] = use ? iscale * xv : 0.f;
+    for (int i = 0; i < 4; ++i) {
+      b0[i] = bias[8 * q + i];
+      b1[i] = bias[8 * q + 4 + i];
     }
   }
-  uint16_t* orow = out + size_t(row) * W * kC + 8 * q;
+
+  // The window of pixel (y, px) that slot q holds: its column, and the three
+  // rows of it (x an image of H x W; a row's index and a column fit 32 bits).
+  // Coordinates just outside wrap; further out (no output depends on those)
+  // they are clamped.
+  static __device__ __forceinline__ uint32_t column(int px, int W, int q) {
+    return uint32_t(wrap(wrap_any(px, W) + (q < 3 ? q : 1) - 1, W)) * 4u;
+  }
+  static __device__ __forceinline__ void window(const float* __restrict__ x, int H, int W, int y,
+                                                uint32_t col, float (&v)[3]) {
+    const int yy = wrap_any(y, H);
 #pragma unroll
-  for (int tile = 0; tile < 4; ++tile) {
-    const int px = seg * 64 + tile * 16 + n;
+    for (int ks = 0; ks < 3; ++ks)
+      v[ks] = *reinterpret_cast<const float*>(
+          reinterpret_cast<const char*>(x + size_t(wrap(yy + ks - 1, H)) * W) + col);
+  }
+
+  __device__ __forceinline__ u32x4 apply(const float (&v)[3], int q, float iscale) const {
     f32x4 a0 = b0, a1 = b1;
 #pragma unroll
     for (int ks = 0; ks < 3; ++ks) {
-      a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[0][ks], v[tile][ks], a0, 0, 0, 0);
-      a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[1][ks], v[tile][ks], a1, 0, 0, 0);
+      const float s = q < 3 ? iscale * v[ks] : 0.f;
+      a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[0][ks], s, a0, 0, 0, 0);
+      a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[1][ks], s, a1, 0, 0, 0);
     }
-    if (px < W)
-      __builtin_nontemporal_store(u32x4{pack_bf16(tanh_fast(a0[0]), tanh_fast(a0[1])),
-                                        pack_bf16(tanh_fast(a0[2]), tanh_fast(a0[3])),
-                                        pack_bf16(tanh_fast(a1[0]), tanh_fast(a1[1])),
-                                        pack_bf16(tanh_fast(a1[2]), tanh_fast(a1[3]))},
-                                  reinterpret_cast<u32x4*>(orow + size_t(px) * kC));
+    return u32x4{pack_bf16(tanh_fast(a0[0]), tanh_fast(a0[1])),
+                 pack_bf16(tanh_fast(a0[2]), tanh_fast(a0[3])),
+                 pack_bf16(tanh_fast(a1[0]), tanh_fast(a1[1])),
+                 pack_bf16(tanh_fast(a1[2]), tanh_fast(a1[3]))};
   }
-}
+};
 
 // dx[p] = s_in * sum_t sum_co W0[co][t] dz0[p - off(t)][co]: one thread per
 // pixel, the 32 channels of each mirrored tap summed as 16 two-channel dot
@@ -613,12 +596,25 @@ __global__ __launch_bounds__(kB) void pack_weights_kernel(const float* __restric
   bwd[i] = f32_to_bf16(w[(b * kC + a) * 9 + t]);
 }
 
+// Byte offsets of the kPR + 2 staged rows of a patch, the first one in slot
+// `base` of a ring of as many.
+struct RowOffsets {
+  uint32_t v[kPR + 2];
+  __device__ __forceinline__ explicit RowOffsets(int base = 0, int width = kSW) {
+#pragma unroll
+    for (int i = 0; i < kPR + 2; ++i) {
+      const int slot = base + i < kPR + 2 ? base + i : base + i - (kPR + 2);
+      v[i] = uint32_t(slot * width * 64);
+    }
+  }
+};
+
 // The 18 MFMAs per tile of a staged patch for the kPR rows of wavefront
 // column wv: tap t = 3 dy + dx reads the staged pixel at p + sgn off(t).
 template <int SGN>
 __device__ __forceinline__ void staged_taps(const unsigned char* st, const bf16x8* wl,
-                                            const uint32_t (&colo)[3], int lane,
-                                            f32x4 (&acc)[kPR][2]) {
+                                            const uint32_t (&colo)[3], const RowOffsets& ro,
+                                            int lane, f32x4 (&acc)[kPR][2]) {
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
     const int dy = SGN > 0 ? t / 3 : 2 - t / 3, dx = SGN > 0 ? t % 3 : 2 - t % 3;
@@ -626,9 +622,180 @@ __device__ __forceinline__ void staged_taps(const unsigned char* st, const bf16x
 #pragma unroll
     for (int j = 0; j < kPR; ++j) {
       const bf16x8 v = *reinterpret_cast<const bf16x8*>(
-          st + colo[dx] + uint32_t((j + dy) * kSW * 64));
+          st + colo[dx] + ro.v[j + dy]);
       acc[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, v, acc[j][0], 0, 0, 0);
       acc[j][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, v, acc[j][1], 0, 0, 0);
+    }
+  }
+}
+
+// bf16(tanh) of a tile's accumulators: channels 8q..8q+7 of the lane's pixel.
+__device__ __forceinline__ u32x4 tanh8(const f32x4 (&acc)[2]) {
+  return u32x4{pack_bf16(tanh_fast(acc[0][0]), tanh_fast(acc[0][1])),
+               pack_bf16(tanh_fast(acc[0][2]), tanh_fast(acc[0][3])),
+               pack_bf16(tanh_fast(acc[1][0]), tanh_fast(acc[1][1])),
+               pack_bf16(tanh_fast(acc[1][2]), tanh_fast(acc[1][3]))};
+}
+
+// Patches in column-major order: down a 64-pixel column, row block after row
+// block, field after field.  A block takes a contiguous range of them, in runs
+// that stay in one column of one field.
+struct PatchRun {
+  int pr, pc, rows, s1;
+  __device__ __forceinline__ PatchRun(int B, int H, int W, int& s0) {
+    pr = (H + kPR - 1) / kPR;
+    pc = (W + 63) >> 6;
+    rows = B * pr;
+    const int n = rows * pc, per = (n + int(gridDim.x) - 1) / int(gridDim.x);
+    s0 = int(blockIdx.x) * per;
+    s1 = min(s0 + per, n);
+  }
+  // Field, row block in the field and first pixel of patch sq.
+  __device__ __forceinline__ void at(int sq, int& b, int& k, int& x0) const {
+    const int cb = sq / rows, r = sq - cb * rows;
+    b = r / pr;
+    k = r - b * pr;
+    x0 = 64 * cb;
+  }
+};
+
+// The first two layers in one pass: a0 = first layer of x, out = bf16(tanh(b +
+// sum_t W_t a0[p + off(t)])).  Both are stored (the backward pass reads a0),
+// but a0 reaches the second layer through LDS: a block walks down a 64-pixel
+// column, kPR rows at a time, and keeps the kPR + 2 rows of a0 that the taps of
+// a patch read (66 pixels, periodic) in a ring, so it computes a0 once but for
+// two pixels a row and two rows a run.  Wavefront w computes row w of the next
+// kPR rows of a0, and one wavefront in turn the two halo pixels of all of them
+// (a tile of 8); then wavefront w computes the 16-pixel column w of all kPR
+// rows of out, lane = (channel group q, pixel c16), reading each weight
+// fragment once per tap for the kPR rows.
+//
+// What bounds it: the vector ALU (half of its time the 64 tanh a pixel) and the
+// matrix cores, 57% and 35% of the cycles, which a wavefront uses in turn; a0
+// is written (1.1 GB for 17 fields of 1024^2) and no longer read.  There the
+// two layers took 383 + 530 us apart and take 797 us together; at 64 fields of
+// 64^2 21 and 20 us.
+__global__ __launch_bounds__(kB, 3) void head_fwd_kernel(
+    const float* __restrict__ x, const uint16_t* __restrict__ w0, const float* __restrict__ bias0,
+    uint16_t* __restrict__ a0, const uint16_t* __restrict__ wf, const float* __restrict__ bias,
+    uint16_t* __restrict__ out, int B, int H, int W, float iscale) {
+  static_assert(kPR == kWaves, "a wavefront per row of a patch");
+  __shared__ bf16x8 wl[18 * 64];
+  __shared__ __attribute__((aligned(16))) unsigned char st[kStage * 16];
+  const int lane = threadIdx.x & 63, q = lane >> 4, c16 = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  for (int k = threadIdx.x; k < 18 * 64; k += kB) wl[k] = load8(wf + size_t(k) * 8);
+  f32x4 bv[2];
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bv[mb][j] = bias[8 * q + 4 * mb + j];
+  FirstLayer first;
+  first.load(w0, bias0, q, c16);
+  int s0;
+  const PatchRun run(B, H, W, s0);
+  uint32_t colo[3];
+#pragma unroll
+  for (int dx = 0; dx < 3; ++dx) colo[dx] = stage_off(0, 16 * wv + c16 + dx, q);
+  const int hrow = (c16 >> 1) & 3, hcol = (c16 & 1) * (kSW - 1);  // halo pixel of this lane
+
+  const uint32_t opix = uint32_t(c16 * kC + 8 * q) * 2u;  // this lane's part of a tile, bytes
+
+  float v[4][3], vh[3];
+  uint32_t col[4], colh = 0;
+  u32x4 z[4], zh;
+  // Windows of the rows r0 .. r0 + 3 of a0 (of which from `from` on).
+  auto fetch = [&](const float* xb, int r0, int from, bool halo) {
+    if (r0 + wv >= from) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) FirstLayer::window(xb, H, W, r0 + wv, col[t], v[t]);
+    }
+    if (halo) {
+      const int yy = wrap_any(r0 + hrow, H);
+#pragma unroll
+      for (int ks = 0; ks < 3; ++ks)
+        vh[ks] = *reinterpret_cast<const float*>(
+            reinterpret_cast<const char*>(xb) +
+            (uint32_t(wrap(yy + ks - 1, H)) * uint32_t(W) * 4u + colh));
+    }
+  };
+  // a0 of those rows, to memory where the run owns them.
+  auto compute = [&](int b, int r0, int from, int ys, int ye, int x0, bool halo) {
+    const int r = r0 + wv;
+    if (r >= from) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) z[t] = first.apply(v[t], q, iscale);
+      if (r >= ys && r < ye) {
+        unsigned char* o =
+            reinterpret_cast<unsigned char*>(a0 + pix(b * H + r, W, x0) * kC);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (x0 + 16 * t + c16 < W)
+            __builtin_nontemporal_store(z[t],
+                                        reinterpret_cast<u32x4*>(o + (opix + 1024u * t)));
+      }
+    }
+    if (halo) zh = first.apply(vh, q, iscale);
+  };
+  // ... and to the ring, rows r0 .. r0 + 3 in the slots from `slot` on.
+  auto stage = [&](int r0, int from, int slot, bool halo) {
+    auto at = [&](int i) { return slot + i < kPR + 2 ? slot + i : slot + i - (kPR + 2); };
+    if (r0 + wv >= from) {
+      const int sl = at(wv);
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        *reinterpret_cast<u32x4*>(st + stage_off(sl, 1 + 16 * t + c16, q)) = z[t];
+    }
+    if (halo && c16 < 2 * kPR && r0 + hrow >= from)
+      *reinterpret_cast<u32x4*>(st + stage_off(at(hrow), hcol, q)) = zh;
+  };
+
+  int base = 0, ys = 0, ye = 0;
+  for (int sq = s0; sq < run.s1; ++sq) {
+    int b, k, x0;
+    run.at(sq, b, k, x0);
+    const int y0 = kPR * k;
+    const float* xb = x + size_t(b) * H * W;
+    const bool halo = ((sq + int(blockIdx.x)) & 3) == wv;
+    if (sq == s0 || k == 0) {  // a run begins: rows y0 - 1 and y0, then the next ones
+      base = 0;
+      ys = y0;
+      ye = min(kPR * min(run.pr, k + run.s1 - sq), H);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) col[t] = FirstLayer::column(x0 + 16 * t + c16, W, q);
+      colh = FirstLayer::column(x0 - 1 + hcol, W, q);
+      fetch(xb, y0 - 3, y0 - 1, halo);
+      compute(b, y0 - 3, y0 - 1, ys, ye, x0, halo);
+      __syncthreads();  // the patch before is done with the ring
+      stage(y0 - 3, y0 - 1, kPR, halo);
+      fetch(xb, y0 + 1, y0 + 1, halo);
+    } else {
+      base = base + kPR < kPR + 2 ? base + kPR : base - 2;
+    }
+    compute(b, y0 + 1, y0 + 1, ys, ye, x0, halo);
+    __syncthreads();  // the patch before is done with the ring (and wl is written)
+    stage(y0 + 1, y0 + 1, base + 2 < kPR + 2 ? base + 2 : base - kPR, halo);
+    __syncthreads();
+    if (sq + 1 < run.s1 && k + 1 < run.pr)
+      fetch(xb, y0 + 1 + kPR, y0 + 1 + kPR, ((sq + 1 + int(blockIdx.x)) & 3) == wv);
+    f32x4 acc[kPR][2];
+#pragma unroll
+    for (int j = 0; j < kPR; ++j) {
+      acc[j][0] = bv[0];
+      acc[j][1] = bv[1];
+    }
+    staged_taps<1>(st, wl, colo, RowOffsets(base), lane, acc);
+    u32x4 r[kPR];
+#pragma unroll
+    for (int j = 0; j < kPR; ++j) r[j] = tanh8(acc[j]);
+    if (x0 + 16 * wv + c16 < W) {
+      unsigned char* o = reinterpret_cast<unsigned char*>(
+          out + (pix(b * H + y0, W, x0) + size_t(16 * wv)) * kC);
+#pragma unroll
+      for (int j = 0; j < kPR; ++j)
+        if (y0 + j < H)
+          __builtin_nontemporal_store(
+              r[j], reinterpret_cast<u32x4*>(o + size_t(j) * W * (2 * kC) + opix));
     }
   }
 }
@@ -689,20 +856,14 @@ __global__ __launch_bounds__(kB, 3) void c32_fwd_kernel(const uint16_t* __restri
       acc[j][0] = bv[0];
       acc[j][1] = bv[1];
     }
-    staged_taps<1>(st, wl, colo, lane, acc);
+    staged_taps<1>(st, wl, colo, RowOffsets(), lane, acc);
     const int px = x0 + 16 * wv + c16;
 #pragma unroll
     for (int j = 0; j < kPR; ++j) {
       const int y = y0 + j;
       if (y < H && px < W) {
-        // channels 8q..8q+7 of the pixel
         uint16_t* o = out + pix(b * H + y, W, px) * kC + 8 * q;
-        u32x4 r;
-        r[0] = pack_bf16(tanh_fast(acc[j][0][0]), tanh_fast(acc[j][0][1]));
-        r[1] = pack_bf16(tanh_fast(acc[j][0][2]), tanh_fast(acc[j][0][3]));
-        r[2] = pack_bf16(tanh_fast(acc[j][1][0]), tanh_fast(acc[j][1][1]));
-        r[3] = pack_bf16(tanh_fast(acc[j][1][2]), tanh_fast(acc[j][1][3]));
-        __builtin_nontemporal_store(r, reinterpret_cast<u32x4*>(o));
+        __builtin_nontemporal_store(tanh8(acc[j]), reinterpret_cast<u32x4*>(o));
       }
     }
   }
@@ -742,7 +903,7 @@ __global__ __launch_bounds__(kB, 3) void c32_bwd_data_kernel(const uint16_t* __r
       acc[j][0] = f32x4{0.f, 0.f, 0.f, 0.f};
       acc[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    staged_taps<-1>(st, wl, colo, lane, acc);
+    staged_taps<-1>(st, wl, colo, RowOffsets(), lane, acc);
     const int px = x0 + 16 * wv + c16;
 #pragma unroll
     for (int j = 0; j < kPR; ++j) {
@@ -1272,13 +1433,14 @@ int blocks_for_pixels(int B, int H, int W) { return blocks_for(size_t(B) * H * W
 
 }  // namespace
 
-void launch_srg_l0_fwd(const float* x, const uint16_t* w, const float* b, uint16_t* out, int B,
-                       int H, int W, float iscale, hipStream_t s) {
-  // one wavefront per 64-pixel segment of a row
-  const size_t units = size_t(B) * H * ((W + 63) / 64);
-  const int nb = int((units + kWaves - 1) / kWaves);
-  hipLaunchKernelGGL(l0_fwd_kernel, dim3(nb > 0 ? nb : 1), dim3(kB), 0, s, x, w, b, out, B, H,
-                     W, iscale);
+void launch_srg_head_fwd(const float* x, const uint16_t* w0, const float* b0, uint16_t* a0,
+                         const uint16_t* wf, const float* b, uint16_t* out, int B, int H, int W,
+                         float iscale, hipStream_t s) {
+  // patches of kPR rows x 64 pixels, three blocks per CU
+  const int np = B * ((H + kPR - 1) / kPR) * ((W + 63) / 64);
+  const int nb = np < 768 ? (np > 0 ? np : 1) : 768;
+  hipLaunchKernelGGL(head_fwd_kernel, dim3(nb), dim3(kB), 0, s, x, w0, b0, a0, wf, b, out, B, H, W,
+                     iscale);
 }
 
 void launch_srg_l0_bwd_data(const uint16_t* dz, const uint16_t* w, float* dx, int B, int H,
