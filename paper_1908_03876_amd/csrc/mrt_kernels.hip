@@ -163,6 +163,10 @@ __device__ __forceinline__ bool links(const Geometry& g, const NodeIdx& n, unsig
   return true;
 }
 
+// Regions of 16 x 16 and of 32 x 32 nodes are taken on planes below 4 GiB only.
+template <int RX, int RY>
+constexpr Lanes lanes_of = RX % 64 == 0 ? kRow : RX == RY ? kSmall : kAny;
+
 // A node's populations take more than the 72 bytes of two species in FP32.
 template <typename T, int VAR>
 constexpr bool kWide = sizeof(T) == 8 || VAR == kVarThree;
@@ -180,7 +184,7 @@ template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
 __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void forward_kernel(Geometry g, ModelCoef<T> m,
                                                                  FwdLaunch<T> a, TileGrid tg) {
   constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit;
-  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  constexpr Lanes A = lanes_of<RX, RY>;
   __shared__ Exchange<T, RX, RY, W3> lds;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
   if (kRows<RY> && !r.owner) return;
@@ -308,7 +312,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
                                                             AdjLaunch<T> a, TileGrid tg) {
   constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit, IMPL = VAR == kVarImplicit;
   __shared__ Exchange<T, RX, RY, W3> lds;
-  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  constexpr Lanes A = lanes_of<RX, RY>;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
   if (kRows<RY> && !r.owner) return;
   NodeIdx n;
@@ -357,7 +361,7 @@ template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
 __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCoef<T> m,
                                                              TlmLaunch<T> a, TileGrid tg) {
   constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit;
-  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  constexpr Lanes A = lanes_of<RX, RY>;
   __shared__ Exchange<T, RX, RY, W3> lds;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
   if (kRows<RY> && !r.owner) return;
@@ -420,7 +424,7 @@ __global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, 
                                                          CadjCoef<T> cc, CadjLaunch<T> a,
                                                          TileGrid tg) {
   __shared__ Exchange<T, RX, RY, false> lds;
-  constexpr Lanes A = RX % 64 == 0 ? kRow : RX == 16 ? kSmall : kAny;
+  constexpr Lanes A = lanes_of<RX, RY>;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
   if (kRows<RY> && !r.owner) return;
   NodeIdx n;
@@ -663,18 +667,20 @@ TileGrid region_grid(const Geometry& g, const StepPlan& p) {
 }
 
 // Calls f(integral constants walls, region width, region height) for a
-// lattice and a plan.  The regions of wide nodes are half as large.
+// lattice and a plan.
 template <typename T, int VAR, typename F>
 void dispatch_region(const Geometry& g, const StepPlan& p, F f) {
   using std::integral_constant;
-  constexpr bool WIDE = kWide<T, VAR>;
   auto shape = [&](auto W) {
     if constexpr (VAR == kVarExplicit)
       if (p.ry == 1) return f(W, integral_constant<int, 256>(), integral_constant<int, 1>());
-    if (p.rx == 16)
-      f(W, integral_constant<int, 16>(), integral_constant<int, 16>());
-    else
-      f(W, integral_constant<int, WIDE ? 32 : 64>(), integral_constant<int, 16>());
+    if (p.rx == 16) return f(W, integral_constant<int, 16>(), integral_constant<int, 16>());
+    if constexpr (kWide<T, VAR>) {
+      f(W, integral_constant<int, 32>(), integral_constant<int, 16>());
+    } else {
+      if (p.ry == 32) return f(W, integral_constant<int, 32>(), integral_constant<int, 32>());
+      f(W, integral_constant<int, 64>(), integral_constant<int, 16>());
+    }
   };
   if (g.masked || !g.periodic)
     shape(std::true_type());
@@ -702,33 +708,46 @@ void dispatch_variant(int variant, F f) {
 // gap before it), every further step costs a ring of each region, and the time
 // of a small lattice goes up in whole rounds of regions: with up to 256 of them
 // each has a compute unit to itself, with up to 512 two share one.  So: the
-// most steps whose regions fit one round (of 256 with 6 or 7 steps, of 512 with
-// 4 or 5), and 5 for the large lattices, where memory and the vector units come
-// level.  The small regions spread the smallest lattices over the chip.
-// Measured in us per forward step, FP32, steps per launch in brackets:
-//   2048^2  64x16 regions  64.2 (3)  57.0 (4)  51.1 (5)  57.2 (6)
-//    550^2                  5.1 (3)   5.7 (4)   4.8 (5)   5.1 (6)
-//    512^2                  4.7 (3)   4.2 (4)   4.7 (5)   4.9 (6)
-//    448^2                  5.0 (3)   4.3 (4)   3.6 (5)   4.2 (6)
-//    256^2                  3.2 (3)   2.7 (4)   2.4 (5)   2.2 (6)
-//    200^2                  1.9 (6)   1.8 (7);  16x16  1.9 (4)  2.3 (5)
-//    128^2                  2.0 (6);  16x16     1.8 (4)   1.6 (5)   1.7 (6)
-//     64^2                  1.8 (7);  16x16     1.9 (4)   1.6 (5)   1.4 (7)
+// most steps whose regions fit one round of 256, or else of 512, as long as the
+// rings leave enough of a region; and 5 for the large lattices, where memory
+// and the vector units come level.  Of the shapes, 16 x 16 spreads the smallest
+// lattices over the chip; 64 x 16, whose rows are scalar addresses, has the
+// shortest steps; 32 x 32 owns more of its nodes (with 5 steps 56% instead of
+// 44%).  Measured in us per forward step, FP32, steps per launch in brackets:
+//            64 x 16                                      32 x 32
+//   2048^2   64.2 (3)  57.0 (4)  51.2 (5)  57.2 (6)       61.4 (4)  50.9 (5)  53.2 (6)
+//            54.7 (5) the AMRT step                       52.7 (5)
+//   1024^2   12.8 (3)  13.9 (4)  12.2 (5)  13.8 (6)       12.8 (4)  11.8 (5)  12.3 (6)
+//    512^2    4.7 (3)   4.2 (4)   4.7 (5)   4.9 (6)        4.4 (4)   3.8 (5)   4.6 (6)
+//    400^2    3.5 (3)   3.8 (4)   3.3 (5)   3.7 (6)        3.2 (4)   3.3 (6)   3.1 (7)
+//    300^2    2.9 (3)   2.6 (4)   2.4 (5)   2.8 (6)        2.4 (6)   2.3 (7)   2.7 (9)
+//    256^2    2.7 (4)   2.4 (5)   2.2 (6)   2.5 (7)        2.3 (8)   2.1 (9)   2.6 (10)
+//    200^2    2.2 (5)   1.9 (6)   1.75 (7)                 1.9 (9)   1.8 (10)
+//  301x157    2.1 (5)   1.9 (6)   1.8 (7)                  2.0 (9)   2.4 (10)
+//            16 x 16
+//    128^2    1.8 (4)   1.6 (5)   1.7 (6)  (64 x 16: 2.0 (6), 1.9 (7))
+//     64^2    1.9 (4)   1.6 (5)   1.4 (7)  (64 x 16: 1.8 (7))
+// The regions of wide nodes are 32 x 16: 1024^2, FP64, 30.4 (4) and 28.7 (5);
+// 32 x 32, which leaves one of them to a compute unit, 34.7 (5).
 StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool one) {
   if (one) return {256, 1, 1};
-  const bool wide = elem == 8 || variant == kVarThree;
-  auto regions = [&](int rx, int steps) {
-    return region_grid(g, StepPlan{rx, 16, steps}).ntiles;
+  StepPlan p;
+  // the most steps, from `most` down to `least`, whose regions are at most n
+  auto fits = [&](int rx, int ry, int most, int least, int n) {
+    for (p = {rx, ry, most}; p.steps >= least; --p.steps)
+      if (region_grid(g, p).ntiles <= n) return true;
+    return false;
   };
-  StepPlan p{16, 16, 7};
-  while (p.steps > 4 && regions(16, p.steps) > 256) --p.steps;
-  if (regions(16, p.steps) > 256) {
-    p.rx = wide ? 32 : 64;
-    p.steps = regions(p.rx, 7) <= 256   ? 7
-              : regions(p.rx, 6) <= 256 ? 6
-              : regions(p.rx, 5) <= 512 ? 5
-              : regions(p.rx, 4) <= 512 ? 4
-                                        : 5;
+  if (!fits(16, 16, 7, 4, 256)) {
+    if (elem == 8 || variant == kVarThree) {
+      if (!fits(32, 16, 7, 6, 256) && !fits(32, 16, 5, 4, 512)) p = {32, 16, 5};
+    } else if (!fits(64, 16, 7, 7, 256)) {
+      const bool small = g.plane * elem < (size_t(1) << 32);
+      if (!small)
+        p = {64, 16, 5};
+      else if (!fits(32, 32, 10, 5, 256) && !fits(32, 32, 10, 4, 512))
+        p = {32, 32, 5};
+    }
   }
   // as many launches as that takes, their steps spread evenly
   const int launches = (left + p.steps - 1) / p.steps;

@@ -18,10 +18,10 @@ namespace dev {
 // region stores the RX - 2(K-1) by RY - 2(K-1) nodes inside them, and a
 // wavefront whose rows are stale leaves the work to the others.
 //
-// The wide regions are 64 x 16 (a wavefront is one row, so rows are scalar
-// addresses) for the 72 bytes a node of two species in FP32, 1024 threads and
-// two work-groups a compute unit: 64 registers a thread, 67 KB of LDS.
-// Twice as wide nodes take 32 x 16.  Lattices of a few thousand nodes take
+// The regions are 32 x 32, or 64 x 16 (a wavefront is one row, so rows are
+// scalar addresses), for the 72 bytes a node of two species in FP32: 1024
+// threads and two work-groups a compute unit, 64 registers a thread, 67 KB of
+// LDS.  Twice as wide nodes take 32 x 16.  Lattices of a few thousand nodes take
 // 16 x 16 regions, which spread them over the chip.  The explicit second-order
 // source also reads the previous step's kinetics of its nodes, which a
 // neighbouring region may not find overwritten: where the tape holds only one
@@ -33,8 +33,9 @@ namespace dev {
 // anywhere in a 64-byte chunk, and two regions' parts of a chunk merge in L2
 // (with non-temporal stores each part went to memory by itself: 65 us a step
 // at 2048^2 instead of 55).  Measured at 2048^2, masked, FP32, in us a step:
-// forward with record 122 -> 51.1, AMRT step 125 -> 55.4 (periodic: 49.2 and
-// 51.7); at 1024^2, periodic, 27 -> 13.1 and 36 -> 14.3; at 128^2 4.4 -> 1.6.
+// forward with record 122 -> 50.9, AMRT step 125 -> 52.7 (periodic: 49.6 and
+// 49.4); at 1024^2, periodic, 27 -> 11.8 and 36 -> 13.2; at 512^2, masked,
+// 9.7 -> 3.8 and 10.4 -> 4.0; at 128^2 4.4 -> 1.6.
 
 // The steps of a launch, and how many nodes on each side of a region it does
 // not own (at least count - 1).

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 
 # (nx, ny, steps): one region, its last column or row, one node more; lattices
 # narrower or lower than a region; the widths that 64-, 32- and 16-node regions
-# own with 4, 5 or 6 steps; both sides of the lines between the plans
+# own with 4 to 9 steps; both sides of the lines between the plans
 SIZES = [(6, 6, 5), (7, 13, 6), (16, 16, 9), (17, 5, 11), (3, 40, 4), (61, 2, 7),
          (160, 160, 11), (161, 160, 12), (54, 498, 7), (1200, 23, 6),
-         (384, 384, 7), (386, 384, 9), (58 * 7, 390, 5), (26 * 15 + 1, 401, 4)]
+         (384, 384, 7), (386, 384, 9), (58 * 7, 390, 5), (26 * 15 + 1, 401, 4),
+         (16 * 16, 16 * 16, 18), (16 * 16 + 1, 16 * 16, 9), (24 * 22 + 1, 24 * 23, 10),
+         (24 * 30, 650, 10)]
 KINDS = {"periodic": (True, False), "masked": (False, True), "walls": (False, False),
          "masked_periodic": (True, True)}
 
@@ -49,3 +51,18 @@ def test_regions_of_the_other_schemes(size, source, species):
     r = device_gradient(p, _torch_dtype("f64"), ckpt_every=4)
     assert rel_l2(r["uN"], ref["uN"], p.fluid) <= 1e-12
     assert rel_l2(r["grad"], ref["grad"], p.fluid) <= 1e-12
+
+
+@pytest.mark.parametrize("source", [2, 3])
+@pytest.mark.parametrize("size", [(256, 257, 9), (529, 552, 10)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_square_regions_of_the_other_schemes(size, source):
+    nx, ny, steps = size
+    p = I.slow_reaction(_ragged(nx * 1000 + ny, nx, ny, steps, False, True), 0.1).copy(
+        source_term=source)
+    print(f"case {size} source {source}", flush=True)
+    ref = O.cost_gradient(p)
+    ftol, gtol = TOL["f32"]
+    r = device_gradient(p, _torch_dtype("f32"))
+    assert rel_l2(r["uN"], ref["uN"], p.fluid) <= ftol
+    assert rel_l2(r["grad"], ref["grad"], p.fluid) <= gtol
