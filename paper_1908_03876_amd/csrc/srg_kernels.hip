@@ -440,6 +440,18 @@ __global__ __launch_bounds__(kB) void l3_bwd_data_kernel(const float* __restrict
   }
 }
 
+// Sum over the lanes congruent modulo 8, in every lane: the partner of xor 8 by
+// a row rotation, those of xor 16 and 32 by swapping rows and halves.  (By LDS
+// permutes, 123 of them a wavefront, thin_wgrad_kernel took 16.3 us at 64 fields
+// of 64^2 instead of 13.5.)
+__device__ __forceinline__ float sum_octets(float v) {
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x128, 0xf, 0xf, true));
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
 // Weight gradients of a one-channel layer from a 32-channel field F and a
 // one-channel field S:  out[c][t] = sum_p F[p][c] S[p + sgn off(t)], all nine
 // taps in one pass over F.  Lane = (pixel pp = lane / 8 of the wavefront's 8
@@ -518,10 +530,7 @@ __global__ __launch_bounds__(kB) void thin_wgrad_kernel(const uint16_t* __restri
   __shared__ float red[kWaves][8][kV];
 #pragma unroll
   for (int k = 0; k < kV; ++k) {
-    float v = k < 36 ? acc[k / 4][k % 4] : (k < 40 ? fs[k - 36] : ss);
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
+    const float v = sum_octets(k < 36 ? acc[k / 4][k % 4] : (k < 40 ? fs[k - 36] : ss));
     if (pp == 0) red[wv][cq][k] = v;
   }
   __syncthreads();
@@ -941,9 +950,13 @@ __global__ __launch_bounds__(kB, 3) void c32_bwd_data_kernel(const uint16_t* __r
 // or 16 lanes on consecutive channels fall on distinct banks.  For each row
 // of taps a lane reads 8 + 2 staged pixels once: the taps dx = 0, 1, 2 are
 // that window at offsets 0, 1 (realigned with alignbit) and 2.  Wavefront
-// w takes the 32-pixel chunk column w % 2 of rows 2 (w / 2) and
-// 2 (w / 2) + 1 and accumulates all 9 x 2 x 2 output fragments over its
-// chunks.  The block's wavefronts are summed in a fixed order, and the block
+// w takes the 32-pixel chunk column w % 2 of rows 2 (w / 2 % 2) and
+// 2 (w / 2 % 2) + 1 and the output channels 16 (w / 4) .. + 15, and
+// accumulates 9 x 2 output fragments over its chunks.  (With all 9 x 2 x 2 in
+// four wavefronts the registers left one of them to a SIMD: 22.2 us at 64
+// fields of 64^2 instead of 21.4.  Four patches a block, one after the other,
+// and the sum of the partials are what is left.)
+// The block's wavefronts are summed in a fixed order, and the block
 // writes one partial [kSrgWPart] in fragment order: the weights as
 // [t][mb][nb][lane][4] (co = 16 mb + 4 (lane / 16) + j, ci = 16 nb +
 // lane % 16), then the 32 bias sums.
@@ -973,8 +986,8 @@ __device__ __forceinline__ void transpose8(const u32x4 (&v)[8], u32x4 (&o)[8]) {
 
 // Staging item `it` of a patch: its 8 x 16-byte loads (issued, not waited
 // for), and where its 8 channel rows go in the stage.
-constexpr int kWItems = (kAItems + kDItems + kB - 1) / kB;  // items per thread
-static_assert(kWItems == 2, "two staging items per thread");
+constexpr int kBW = 512;  // threads of a weight-gradient block
+static_assert(kAItems + kDItems <= kBW, "one staging item per thread");
 
 __device__ __forceinline__ void wgrad_fetch(const uint16_t* __restrict__ dz,
                                             const uint16_t* __restrict__ a, int it, int b,
@@ -1023,7 +1036,7 @@ __device__ __forceinline__ void wgrad_stage(uint16_t* aT, uint16_t* dT, int it,
 
 // One block per CU: the next patch's loads are in flight while the MFMAs of
 // the current one run.
-__global__ __launch_bounds__(kB, 1) void c32_bwd_weight_kernel(const uint16_t* __restrict__ dz,
+__global__ __launch_bounds__(kBW, 2) void c32_bwd_weight_kernel(const uint16_t* __restrict__ dz,
                                                                const uint16_t* __restrict__ a,
                                                                float* __restrict__ part, int B,
                                                                int H, int W) {
@@ -1032,30 +1045,26 @@ __global__ __launch_bounds__(kB, 1) void c32_bwd_weight_kernel(const uint16_t* _
   uint16_t* dT = sm + kC * kCSa; // [co][r][p]: dz at row y0 + r, column x0 + p
   const int lane = threadIdx.x & 63, q = lane >> 4, c16 = lane & 15;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  const int cw = wv & 1, rh = wv >> 1;
-  f32x4 acc[9][2][2];
+  const int cw = wv & 1, rh = (wv >> 1) & 1, mb = wv >> 2;
+  f32x4 acc[9][2];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int n = 0; n < 2; ++n) acc[t][m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float dbs[2] = {0.f, 0.f};
+    for (int n = 0; n < 2; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float dbs = 0.f;
   const int pr = (H + kPR - 1) / kPR, pc = (W + 63) >> 6;
   const int npatch = B * pr * pc;
-  const int it0 = threadIdx.x, it1 = threadIdx.x + kB;
-  u32x4 v0[8], v1[8];
+  const int it = threadIdx.x;
+  u32x4 v[8];
   auto fetch = [&](int patch) {
     const int b = patch / (pr * pc), rem = patch - b * (pr * pc);
     const int y0 = (rem / pc) * kPR, x0 = (rem - (rem / pc) * pc) * 64;
-    wgrad_fetch(dz, a, it0, b, y0, x0, H, W, v0);
-    wgrad_fetch(dz, a, it1, b, y0, x0, H, W, v1);
+    wgrad_fetch(dz, a, it, b, y0, x0, H, W, v);
   };
   if (int(blockIdx.x) < npatch) fetch(blockIdx.x);
   for (int patch = blockIdx.x; patch < npatch; patch += gridDim.x) {
     __syncthreads();  // the previous patch's reads are done
-    wgrad_stage(aT, dT, it0, v0);
-    wgrad_stage(aT, dT, it1, v1);
+    wgrad_stage(aT, dT, it, v);
     __syncthreads();
     if (patch + int(gridDim.x) < npatch) fetch(patch + gridDim.x);
 #pragma unroll
@@ -1063,13 +1072,10 @@ __global__ __launch_bounds__(kB, 1) void c32_bwd_weight_kernel(const uint16_t* _
       const int row = 2 * rh + jr;
       const int p0 = 32 * cw + 8 * q;  // first pixel of this lane's K slice
       // A[m = co][k = pixel]: dz of the lane's 8 pixels for co = 16 mb + c16
-      bf16x8 af[2];
+      const bf16x8 af =
+          *reinterpret_cast<const bf16x8*>(dT + (16 * mb + c16) * kCSd + row * 64 + p0);
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
-        af[mb] = *reinterpret_cast<const bf16x8*>(dT + (16 * mb + c16) * kCSd + row * 64 + p0);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) dbs[mb] += float(af[mb][j]);
-      }
+      for (int j = 0; j < 8; ++j) dbs += float(af[j]);
 #pragma unroll
       for (int dy = 0; dy < 3; ++dy) {
         // B[k = pixel][n = ci]: a of the lane's 8 pixels shifted by the tap,
@@ -1090,41 +1096,27 @@ __global__ __launch_bounds__(kB, 1) void c32_bwd_weight_kernel(const uint16_t* _
 #pragma unroll
         for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-              acc[3 * dy + dx][mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  af[mb], bf[dx][nb], acc[3 * dy + dx][mb][nb], 0, 0, 0);
+          for (int nb = 0; nb < 2; ++nb)
+            acc[3 * dy + dx][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                af, bf[dx][nb], acc[3 * dy + dx][nb], 0, 0, 0);
       }
     }
   }
-  __syncthreads();  // the stage becomes four regions, one per wavefront
+  __syncthreads();  // the stage becomes four regions, one per pair of wavefronts
   float* reg = reinterpret_cast<float*>(sm);
-  float db2[2];
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    float v = dbs[mb];
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    db2[mb] = v;
-  }
-  float* mine = reg + wv * kSrgWPart;
+  dbs += __shfl_xor(dbs, 16, 64);
+  dbs += __shfl_xor(dbs, 32, 64);
+  float* mine = reg + (wv & 3) * kSrgWPart;
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-        *reinterpret_cast<f32x4*>(mine + (((t * 2 + mb) * 2 + nb) * 64 + lane) * 4) =
-            acc[t][mb][nb];
-  if (q == 0) {
-    mine[kC * kC * 9 + c16] = db2[0];
-    mine[kC * kC * 9 + 16 + c16] = db2[1];
-  }
+    for (int nb = 0; nb < 2; ++nb)
+      *reinterpret_cast<f32x4*>(mine + (((t * 2 + mb) * 2 + nb) * 64 + lane) * 4) = acc[t][nb];
+  if (q == 0) mine[kC * kC * 9 + 16 * mb + c16] = dbs;
   __syncthreads();
   // the block's partial in fragment order (wavefronts summed in a fixed order)
   float* P = part + size_t(blockIdx.x) * kSrgWPart;
-  for (int i = threadIdx.x; i < kSrgWPart; i += kB)
+  for (int i = threadIdx.x; i < kSrgWPart; i += kBW)
     P[i] = ((reg[i] + reg[kSrgWPart + i]) + reg[2 * kSrgWPart + i]) + reg[3 * kSrgWPart + i];
 }
 
@@ -1510,7 +1502,7 @@ void launch_srg_c32_bwd_weight(const uint16_t* dz, const uint16_t* a, float* par
                                float* db, int B, int H, int W, hipStream_t s) {
   const int np = B * ((H + kPR - 1) / kPR) * ((W + 63) / 64);
   const int nb = np < kSrgWBlocks ? (np > 0 ? np : 1) : kSrgWBlocks;
-  hipLaunchKernelGGL(c32_bwd_weight_kernel, dim3(nb), dim3(kB), 0, s, dz, a, part, B, H, W);
+  hipLaunchKernelGGL(c32_bwd_weight_kernel, dim3(nb), dim3(kBW), 0, s, dz, a, part, B, H, W);
   hipLaunchKernelGGL(wpart_sum_kernel, dim3((kSrgWPart + 31) / 32), dim3(kB), 0, s, part, nb,
                      dw, db);
 }
