@@ -32,7 +32,7 @@ HBM_PEAK_GBS = 8000.0
 # sources the single-lattice step kernels are compiled from: HBM counters
 # taken on other sources are stale
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1908_03876_amd", "csrc", f)
-               for f in ("mrt_kernels.hip", "mrt_device.h", "mrt_internal.h")]
+               for f in ("mrt_kernels.hip", "mrt_device.h", "mrt_region.h", "mrt_internal.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.txt")
 # the same for the D3Q19 step kernels
 KERNEL3_SRCS = [os.path.join(ROOT, "paper_1908_03876_amd", "csrc", f)
@@ -52,9 +52,9 @@ def kernel_hash(srcs=None) -> str:
     return h.hexdigest()[:16]
 
 
-def read_traffic(kernel: str, L: int, path: str = None, srcs=None):
-    """Calibrated HBM bytes per launch of `kernel` from the committed counter
-    summary (`key = value` lines), or None when it is absent, taken on
+def read_traffic(kernel: str, L: int, path: str = None, srcs=None, per="step"):
+    """Calibrated HBM bytes per step (or launch) of `kernel` from the committed
+    counter summary (`key = value` lines), or None when it is absent, taken on
     another workload size, or taken on other kernel sources."""
     path = TRAFFIC_FILE if path is None else path
     if not os.path.exists(path):
@@ -68,28 +68,32 @@ def read_traffic(kernel: str, L: int, path: str = None, srcs=None):
                 kv[k.strip()] = v.strip()
     if kv.get("kernel_source_sha256_16") != kernel_hash(srcs) or kv.get("L") != str(L):
         return None
-    v = kv.get(kernel + ".hbm_bytes_per_launch")
+    v = kv.get(f"{kernel}.hbm_bytes_per_{per}")
     return int(v) if v is not None else None
 
 
-def bytes_per_site(elem: int, source_term: int = 1, nspecies: int = 2):
-    """Algorithmic HBM bytes per fluid node and step (the counts of the
-    measurement plan: 148 forward, 160 with the record, 172 adjoint for two
-    species in FP32):
-    forward with record: 9 NS loads + 9 NS stores + control + record stores
-    (u, j_v; and j_w with three species); adjoint: 9 NS + 9 NS + the record
-    loads + FP64 gradient read-modify-write.  The explicit second-order
-    source term adds a read and a write of two planes (the previous step's
-    kinetics, or their adjoint) to both; the implicit one adds no traffic
-    (the node solve is arithmetic).  The 2-byte link word every node reads
-    is an overhead of the masked layout, reported on its own, not counted."""
+# time steps that one launch (or grid barrier) takes on a large lattice
+STEPS_PER_LAUNCH = 5
+
+
+def bytes_per_site(elem: int, source_term: int = 1, nspecies: int = 2,
+                   steps: int = STEPS_PER_LAUNCH):
+    """Algorithmic HBM bytes per fluid node and time step, `steps` of them in a
+    launch.  Every step writes (forward) or reads (adjoint) its record: u, j_v;
+    and j_w with three species.  A launch reads and writes once: 9 NS planes of
+    the state; forward, the control; adjoint, the FP64 gradient.  The explicit
+    second-order source term adds a read and a write of two planes (the
+    previous step's kinetics, or their adjoint) to both; the implicit one adds
+    no traffic (the node solve is arithmetic).  With one step a launch these
+    are 160 (148 without the record) and 172 B for two species in FP32, with
+    five 41.6 (29.6) and 44 B.  The 2-byte link word every node of a masked
+    lattice reads and the nodes that neighbouring regions read twice are
+    overheads, not counted."""
     lag = 4 * elem if source_term == 2 else 0
     pops = 18 * nspecies * elem
     rec = (5 if nspecies == 3 else 3) * elem
-    fwd = pops + elem + rec + lag
-    adj = pops + rec + 16 + lag
-    fwd_norec = pops + elem + lag
-    return fwd, adj, fwd_norec
+    fwd_norec = (pops + elem + lag) / steps
+    return fwd_norec + rec, (pops + 16 + lag) / steps + rec, fwd_norec
 
 
 def _gomp():
@@ -179,33 +183,18 @@ def bench_batched(args):
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     ms = (t1 - t0) * 1e3 / args.steps
-    # per site-step bytes (FP32, periodic, no mask): forward 18+18 planes +
-    # control, with the record on the recomputed/last segment, adjoint 18+18
-    # planes + 3 record loads + FP64 gradient read-modify-write
-    fwd_b, rec_b, adj_b = 36 * 4 + 4, 36 * 4 + 4 + 12, 36 * 4 + 12 + 16
-    bytes_it = sites * (N * fwd_b + N * rec_b + N * adj_b)
+    # forward, recomputation with the record, adjoint
+    rec_b, adj_b, fwd_b = bytes_per_site(4)
+    bytes_it = sites * N * (fwd_b + rec_b + adj_b)
     out = {"metric": "batched coupled MRT+AMRT MLUPS (96 uneven instances)",
            "value": round(sites * N / (ms / 1e3) / 1e6, 1), "unit": "MLUPS",
            "ms_per_iteration": round(ms, 1), "iterations": args.steps,
            "instances": 96, "sites": sites, "nsteps": N, "ckpt_every": K,
-           "tiles": best, "algorithmic_GBps_per_iteration": round(bytes_it / (ms / 1e3) / 1e9, 1),
+           "tiles": best, "steps_per_barrier": STEPS_PER_LAUNCH,
+           "algorithmic_GBps_per_iteration": round(bytes_it / (ms / 1e3) / 1e9, 1),
            "hbm_frac": round(bytes_it / (ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
            "J_sum_history": [round(x, 4) for x in js]}
     b.close()
-    # the streaming probe with each launch's access mix at this size: the
-    # iteration's ceiling is its bytes over the sum of each part's bytes at
-    # its own ceiling
-    dev = torch.device("cuda:0")
-    parts = [(19, 18, N * fwd_b), (19, 21, N * rec_b), (23, 20, N * adj_b)]
-    t_ideal = 0.0
-    ceil = {}
-    for r, w, nb in parts:
-        c = stream_ceiling(r, w, sites, dev)
-        ceil[f"{r}+{w}"] = c["GBps"]
-        t_ideal += sites * nb / (c["GBps"] * 1e9)
-    out["stream_ceiling_GBps"] = ceil
-    out["iteration_stream_ceiling_GBps"] = round(bytes_it / t_ideal / 1e9, 1)
-    out["frac_of_stream_ceiling"] = round(t_ideal / (ms / 1e3), 4)
     print(json.dumps(out), flush=True)
 
 
@@ -723,7 +712,8 @@ def bench_d3q19(args):
     dom = max(kern, key=lambda k: kern[k][0])
     avg_ms = kern[dom][1]
     achieved = launch_bytes[dom] / (avg_ms / 1e3) / 1e9
-    traffic = read_traffic(dom, L, TRAFFIC3_FILE, KERNEL3_SRCS) if info.mode == 1 else None
+    traffic = (read_traffic(dom, L, TRAFFIC3_FILE, KERNEL3_SRCS, "launch")
+               if info.mode == 1 else None)
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
             "kernel": dom, "avg_launch_ms": round(avg_ms, 5),
@@ -754,7 +744,6 @@ def bench_d3q19(args):
         "recompute_launches": r_n,
         "J_history": [round(x, 6) for x in hist],
         "roofline": roof,
-        "other_kernel": side,
     }
     it.close()
     del dp
@@ -885,15 +874,18 @@ def main():
     value = n_fluid * dp.nsteps / (ms_step / 1e3) / 1e6
 
     elem = 4
-    b_fwd, b_adj, b_norec = bytes_per_site(elem, args.source_term, args.species)
-    # per-launch algorithmic bytes: fluid nodes only
-    launch_bytes_adj = n_fluid * b_adj
+    # the explicit second-order source takes one step a launch unless the tape
+    # holds every step
+    per_launch = STEPS_PER_LAUNCH if args.source_term != 2 or info.mode == 1 else 1
+    b_fwd, b_adj, b_norec = bytes_per_site(elem, args.source_term, args.species, per_launch)
+    # per-step algorithmic bytes: fluid nodes only
+    step_bytes_adj = n_fluid * b_adj
     fwd_rec_share = 1.0 if info.mode == 1 else 1.0 / info.n_segments
-    launch_bytes_fwd = n_fluid * (fwd_rec_share * b_fwd + (1 - fwd_rec_share) * b_norec)
+    step_bytes_fwd = n_fluid * (fwd_rec_share * b_fwd + (1 - fwd_rec_share) * b_norec)
     avg_adj_ms = a_ms / max(a_n, 1)
     avg_fwd_ms = f_ms / max(f_n, 1)
-    kern = {"mrt_forward_step": (f_ms, avg_fwd_ms, launch_bytes_fwd),
-            "amrt_adjoint_step": (a_ms, avg_adj_ms, launch_bytes_adj)}
+    kern = {"mrt_forward_step": (f_ms, avg_fwd_ms, step_bytes_fwd),
+            "amrt_adjoint_step": (a_ms, avg_adj_ms, step_bytes_adj)}
     dom = max(kern, key=lambda k: kern[k][0])
     _, avg_ms, lbytes = kern[dom]
     achieved = lbytes / (avg_ms / 1e3) / 1e9
@@ -901,30 +893,32 @@ def main():
                if args.source_term == 1 and args.species == 2 else None)
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": traffic, "kernel": dom,
-            "avg_launch_ms": round(avg_ms, 5),
-            "algorithmic_bytes_per_launch": int(lbytes),
-            "algorithmic_bytes_per_fluid_node": b_adj if dom == "amrt_adjoint_step" else b_fwd,
-            "link_word_bytes_per_launch": 2 * dp.nx * dp.ny}
+            "traffic": traffic, "kernel": dom, "steps_per_launch": per_launch,
+            "avg_step_ms": round(avg_ms, 5),
+            "algorithmic_bytes_per_step": int(lbytes),
+            "algorithmic_bytes_per_fluid_node": round(
+                b_adj if dom == "amrt_adjoint_step" else b_fwd, 1),
+            # the rate at which one step a launch would have to stream
+            "one_step_a_launch_GBps": round(
+                n_fluid * bytes_per_site(elem, args.source_term, args.species, 1)[
+                    1 if dom == "amrt_adjoint_step" else 0] / (avg_ms / 1e3) / 1e9, 1)}
     roof.update(traffic_rate(traffic, avg_ms))
-    # the other step kernel beside it, against the ceiling of its own mix
+    # the other step kernel beside it
     other = "mrt_forward_step" if dom == "amrt_adjoint_step" else "amrt_adjoint_step"
     _, o_ms, o_bytes = kern[other]
     o_rate = o_bytes / (o_ms / 1e3) / 1e9 if o_ms > 0 else 0.0
-    side = {"kernel": other, "avg_launch_ms": round(o_ms, 5),
-            "algorithmic_bytes_per_launch": int(o_bytes), "achieved": round(o_rate, 1),
+    side = {"kernel": other, "avg_step_ms": round(o_ms, 5),
+            "algorithmic_bytes_per_step": int(o_bytes), "achieved": round(o_rate, 1),
             "unit": "GB/s", "frac": round(o_rate / HBM_PEAK_GBS, 4),
             "traffic": (read_traffic(other, args.L)
                         if args.source_term == 1 and args.species == 2 else None)}
     if o_ms > 0:
         side.update(traffic_rate(side["traffic"], o_ms))
     if args.source_term == 1 and args.species == 2:
+        # what one step a launch could reach at best: its planes streamed with
+        # no arithmetic
         mix = {"amrt_adjoint_step": (23, 20), "mrt_forward_step": (19, 21)}
-        add_stream_ceiling(roof, *mix[dom], dp.nx * dp.ny, dev)
-        # a recording forward's mix; with a checkpointed tape most forward
-        # launches do not record
-        if o_rate > 0 and (other == "amrt_adjoint_step" or fwd_rec_share == 1.0):
-            add_stream_ceiling(side, *mix[other], dp.nx * dp.ny, dev)
+        roof["stream_ceiling"] = stream_ceiling(*mix[dom], dp.nx * dp.ny, dev)
     out = {
         "metric": "coupled MRT+AMRT MLUPS (gradient iteration: forward + adjoint), "
                   "HBM GB/s fraction; s per gradient iteration",
@@ -951,7 +945,7 @@ def main():
         "s_per_iteration": round(ms_step / 1e3, 4),
         "forward_mlups": round(n_fluid * f_n / (f_ms / 1e3) / 1e6, 1) if f_ms else None,
         "adjoint_mlups": round(n_fluid * a_n / (a_ms / 1e3) / 1e6, 1) if a_ms else None,
-        "recompute_launches": r_n,
+        "recompute_steps": r_n,
         "J_history": [round(x, 6) for x in hist],
         "roofline": roof,
         "other_kernel": side,
