@@ -954,7 +954,7 @@ __global__ __launch_bounds__(kB, 3) void c32_bwd_data_kernel(const uint16_t* __r
 // 2 (w / 2 % 2) + 1 and the output channels 16 (w / 4) .. + 15, and
 // accumulates 9 x 2 output fragments over its chunks.  (With all 9 x 2 x 2 in
 // four wavefronts the registers left one of them to a SIMD: 22.2 us at 64
-// fields of 64^2 instead of 21.4.  Four patches a block, one after the other,
+// fields of 64^2 instead of 21.4, now 20.4.  Four patches a block, one after the other,
 // and the sum of the partials are what is left.)
 // The block's wavefronts are summed in a fixed order, and the block
 // writes one partial [kSrgWPart] in fragment order: the weights as
@@ -1085,8 +1085,15 @@ __global__ __launch_bounds__(kBW, 2) void c32_bwd_weight_kernel(const uint16_t* 
         for (int nb = 0; nb < 2; ++nb) {
           const uint16_t* src = aT + (16 * nb + c16) * kCSa + (row + dy) * kTW + p0;
           const u32x4 d = *reinterpret_cast<const u32x4*>(src);
-          const uint32_t d4 = *reinterpret_cast<const uint32_t*>(src + 8);
           const uint32_t d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3];
+          // pixels p0 + 8 and 9: the next slice's first two, of the lane 16
+          // further on; the last slice reads them (4-byte reads by all lanes
+          // met on a quarter of the banks: 3.0e6 conflict cycles a launch at
+          // 64 fields of 64^2 instead of 0.6e6, 21.4 us instead of 20.4)
+          const auto odd = __builtin_amdgcn_permlane16_swap(d0, d0, false, false);
+          const auto far = __builtin_amdgcn_permlane32_swap(odd[0], odd[0], false, false);
+          uint32_t d4 = q == 1 ? far[1] : odd[1];
+          if (q == 3) d4 = *reinterpret_cast<const uint32_t*>(src + 8);
           bf[0][nb] = __builtin_bit_cast(bf16x8, d);
           bf[1][nb] = __builtin_bit_cast(
               bf16x8, u32x4{__builtin_amdgcn_alignbit(d1, d0, 16), __builtin_amdgcn_alignbit(d2, d1, 16),
