@@ -609,11 +609,11 @@ __global__ __launch_bounds__(kB) void pack_weights_kernel(const float* __restric
 // `base` of a ring of as many.
 struct RowOffsets {
   uint32_t v[kPR + 2];
-  __device__ __forceinline__ explicit RowOffsets(int base = 0, int width = kSW) {
+  __device__ __forceinline__ explicit RowOffsets(int base = 0) {
 #pragma unroll
     for (int i = 0; i < kPR + 2; ++i) {
       const int slot = base + i < kPR + 2 ? base + i : base + i - (kPR + 2);
-      v[i] = uint32_t(slot * width * 64);
+      v[i] = uint32_t(slot * kSW * 64);
     }
   }
 };
@@ -658,6 +658,11 @@ struct PatchRun {
     const int n = rows * pc, per = (n + int(gridDim.x) - 1) / int(gridDim.x);
     s0 = int(blockIdx.x) * per;
     s1 = min(s0 + per, n);
+  }
+  // Index of patch sq in row-major order.
+  __device__ __forceinline__ int patch(int sq) const {
+    const int cb = sq / rows;
+    return (sq - cb * rows) * pc + cb;
   }
   // Field, row block in the field and first pixel of patch sq.
   __device__ __forceinline__ void at(int sq, int& b, int& k, int& x0) const {
@@ -830,35 +835,25 @@ __global__ __launch_bounds__(kB, 3) void c32_fwd_kernel(const uint16_t* __restri
   for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
     for (int j = 0; j < 4; ++j) bv[mb][j] = bias[8 * q + 4 * mb + j];
-  const int pr = (H + kPR - 1) / kPR, pc = (W + 63) >> 6;
-  const int npatch = B * pr * pc;
   // column offsets (bytes) of this lane's three x taps in a staged row
   uint32_t colo[3];
 #pragma unroll
   for (int dx = 0; dx < 3; ++dx) colo[dx] = stage_off(0, 16 * wv + c16 + dx, q);
-  // the next patch's chunks are loaded into registers while the current
-  // one computes
-  // A block takes a contiguous run of patches in column-major order (down
-  // a 64-pixel column, row block after row block), so that the two halo
-  // rows it stages for the next patch are rows it fetched for this one
-  // and are still in L2.
-  const int rows = B * pr;  // row blocks over all fields
-  const int per = (npatch + int(gridDim.x) - 1) / int(gridDim.x);
-  const int s0 = int(blockIdx.x) * per, s1 = min(s0 + per, npatch);
-  auto patch_of = [&](int sq) {
-    const int cb = sq / rows;
-    return (sq - cb * rows) * pc + cb;
-  };
+  // the next patch's chunks are loaded into registers while the current one
+  // computes; the two halo rows staged for it are rows that were fetched for
+  // this one and are still in L2
+  int s0;
+  const PatchRun run(B, H, W, s0);
   u32x4 pre[kChunks];
-  if (s0 < s1) fetch_patch(in, patch_of(s0), pr, pc, H, W, pre);
-  for (int sq = s0; sq < s1; ++sq) {
-    const int patch = patch_of(sq);
-    const int b = patch / (pr * pc), rem = patch - b * (pr * pc);
-    const int y0 = (rem / pc) * kPR, x0 = (rem - (rem / pc) * pc) * 64;
+  if (s0 < run.s1) fetch_patch(in, run.patch(s0), run.pr, run.pc, H, W, pre);
+  for (int sq = s0; sq < run.s1; ++sq) {
+    int b, k, x0;
+    run.at(sq, b, k, x0);
+    const int y0 = kPR * k;
     __syncthreads();  // the previous patch's reads of st are done (and wl is written)
     store_patch(st, pre);
     __syncthreads();
-    if (sq + 1 < s1) fetch_patch(in, patch_of(sq + 1), pr, pc, H, W, pre);
+    if (sq + 1 < run.s1) fetch_patch(in, run.patch(sq + 1), run.pr, run.pc, H, W, pre);
     f32x4 acc[kPR][2];
 #pragma unroll
     for (int j = 0; j < kPR; ++j) {
