@@ -168,6 +168,19 @@ int mrt_tape_create(const mrt_problem* p, int32_t ckpt_every,
 void mrt_tape_destroy(mrt_tape* t);
 int mrt_tape_query(const mrt_tape* t, mrt_tape_info* info /* host */);
 
+/* How a forward, adjoint or tangent sweep on a tape with this ckpt_every takes
+ * its next time steps when `left` of them remain to the end of its segment:
+ * the nodes of a work-group's region, the steps of the launch, and whether the
+ * kernel addresses a node by a 32-bit byte offset from the start of its plane
+ * (the results do not depend on any of it).  Host-only (no device call). */
+typedef struct mrt_step_shape {
+  int32_t width, height;
+  int32_t steps;
+  int32_t short_offsets;
+} mrt_step_shape;
+int mrt_step_plan(const mrt_problem* p, int32_t ckpt_every, int32_t left,
+                  mrt_step_shape* out /* host */);
+
 /* Forward MRT solve (eq:LBEG with the sources (S), (PhiS); collision (MC) in
  * moment space (MF); streaming with halfway bounce-back), N steps from the
  * equilibrium of (u0, v0) (phieq).  Writes u^N, v^N after the last

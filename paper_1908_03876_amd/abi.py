@@ -71,6 +71,11 @@ class mrt_tape_info(ctypes.Structure):
                 ("n_fluid", ctypes.c_int64), ("device_bytes", ctypes.c_size_t)]
 
 
+class mrt_step_shape(ctypes.Structure):
+    _fields_ = [("width", ctypes.c_int32), ("height", ctypes.c_int32),
+                ("steps", ctypes.c_int32), ("short_offsets", ctypes.c_int32)]
+
+
 class mrt_batch_tiles(ctypes.Structure):
     _fields_ = [("tile_w", ctypes.c_int32), ("blocks_per_cu", ctypes.c_int32),
                 ("max_blocks_per_cu", ctypes.c_int32), ("reserved", ctypes.c_int32),
@@ -100,7 +105,7 @@ MRT_FIELD_U0, MRT_FIELD_V0, MRT_FIELD_CONTROL, MRT_FIELD_TARGET = 0, 1, 2, 3
 MRT_FIELD_UN, MRT_FIELD_VN, MRT_FIELD_GRAD = 4, 5, 6
 
 EXPORTS = ["mrt_validate", "mrt_tape_bytes", "mrt_tape_create",
-           "mrt_tape_destroy", "mrt_tape_query", "mrt_forward", "amrt_adjoint",
+           "mrt_tape_destroy", "mrt_tape_query", "mrt_step_plan", "mrt_forward", "amrt_adjoint",
            "cost_gradient", "cost_gradient_noalloc", "gd_step", "mrt_last_error",
            "mrt_timing_enable",
            "mrt_timing_reset", "mrt_timing_read", "mrt_stream_probe", "mrt_tlm", "mrt_dot",
@@ -135,6 +140,8 @@ def _load():
     L.mrt_tape_destroy.argtypes = [vp]
     L.mrt_tape_destroy.restype = None
     L.mrt_tape_query.argtypes = [vp, ctypes.POINTER(mrt_tape_info)]
+    L.mrt_step_plan.argtypes = [P, ctypes.c_int32, ctypes.c_int32,
+                                ctypes.POINTER(mrt_step_shape)]
     L.mrt_forward.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp]
     L.amrt_adjoint.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     L.cost_gradient.argtypes = [P, vp, vp, vp, vp, vp, vp, vp,
@@ -260,6 +267,12 @@ def mrt_tape_query(tape) -> mrt_tape_info:
     info = mrt_tape_info()
     _check(lib.mrt_tape_query(tape, ctypes.byref(info)))
     return info
+
+
+def mrt_step_plan(p: mrt_problem, ckpt_every: int, left: int) -> mrt_step_shape:
+    out = mrt_step_shape()
+    _check(lib.mrt_step_plan(ctypes.byref(p), int(ckpt_every), int(left), ctypes.byref(out)))
+    return out
 
 
 def mrt_forward(p, tape, u0, v0, control, state=None, uN=None, vN=None,

@@ -475,7 +475,8 @@ int variant(const mrt_tape* t) { return t->ns == 3 ? 4 : (t->so2 ? 2 : (t->impl 
 bool lag_pair(const mrt_tape* t) { return t->mode == 1; }
 void* lag_of(const mrt_tape* t, int k) { return k && lag_pair(t) ? t->alag : t->lag; }
 void* alag_of(const mrt_tape* t, int k) { return k && lag_pair(t) ? t->lag : t->alag; }
-bool one_step(const mrt_tape* t) { return t->so2 && !lag_pair(t); }
+bool one_step(int so2, int mode) { return so2 && mode != 1; }
+bool one_step(const mrt_tape* t) { return one_step(t->so2, t->mode); }
 
 // Forward steps [n0, n1) starting from `src` (null = equilibrium of u0, v0).
 // Several steps run in one launch; the output of its last step n goes to
@@ -950,6 +951,26 @@ int mrt_tape_query(const mrt_tape* t, mrt_tape_info* info) {
   info->reserved = 0;
   info->n_fluid = t->n_fluid;
   info->device_bytes = t->total_bytes;
+  return MRT_OK;
+}
+
+int mrt_step_plan(const mrt_problem* p, int32_t ckpt_every, int32_t left, mrt_step_shape* out) {
+  int rc = validate(p);
+  if (rc) return rc;
+  if (!out) return fail(MRT_EINVAL, "out is NULL");
+  if (left < 1) return fail(MRT_EINVAL, "left must be at least 1");
+  const Layout L = plan(p, ckpt_every);
+  mrt::Geometry g{};
+  g.nx = p->grid.nx;
+  g.ny = p->grid.ny;
+  g.pitch = p->grid.pitch;
+  g.periodic = p->grid.periodic;
+  g.masked = p->grid.mask != nullptr;
+  g.plane = L.plane;
+  const int var = p->nspecies == 3 ? 4 : std::max(1, p->source_term);
+  const mrt::StepPlan s =
+      mrt::plan_steps(g, L.elem, var, left, one_step(p->source_term == 2, L.mode));
+  *out = {s.rx, s.ry, s.steps, mrt::short_offsets(s.rx, s.ry)};
   return MRT_OK;
 }
 

@@ -92,8 +92,9 @@ __device__ __forceinline__ unsigned link_of(const Geometry& g, unsigned flag,
 
 // How the lanes of a wavefront lie, and so how an element is addressed:
 // kRow, one row (a scalar row base and a 32-bit lane offset); kSmall, several
-// rows of a plane below 4 GiB (a scalar plane base and a 32-bit lane offset);
-// kAny, several rows of any plane (a 64-bit address per lane).
+// rows of a plane below 4 GiB, whatever its element (a scalar plane base and a
+// 32-bit lane offset); kAny, several rows of any plane (a 64-bit address per
+// lane).
 enum Lanes { kRow, kSmall, kAny };
 
 template <Lanes A, typename T>

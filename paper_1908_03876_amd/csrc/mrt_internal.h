@@ -58,6 +58,14 @@ struct StepPlan {
   int rx, ry, steps;
 };
 
+// Regions whose wavefronts cover several rows and address a node by a 32-bit
+// byte offset from the start of its plane; all others take 64-bit row bases.
+constexpr bool short_offsets(int rx, int ry) { return rx == ry; }
+
+// Widest element of the planes that a step kernel addresses by such an offset:
+// the gradient accumulator is FP64 in every precision.
+constexpr size_t kWidestElement = sizeof(double);
+
 // Plan for a sweep that has `left` steps to go (elem: bytes per value; one:
 // one step a launch, for variant 2 with a single buffer of kinetics).
 StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool one);

@@ -163,9 +163,10 @@ __device__ __forceinline__ bool links(const Geometry& g, const NodeIdx& n, unsig
   return true;
 }
 
-// Regions of 16 x 16 and of 32 x 32 nodes are taken on planes below 4 GiB only.
+// Regions of 32 x 32 nodes are taken only where a plane's offsets fit 32 bits
+// (plan_steps).
 template <int RX, int RY>
-constexpr Lanes lanes_of = RX % 64 == 0 ? kRow : RX == RY ? kSmall : kAny;
+constexpr Lanes lanes_of = short_offsets(RX, RY) ? kSmall : RX % 64 == 0 ? kRow : kAny;
 
 // A node's populations take more than the 72 bytes of two species in FP32.
 template <typename T, int VAR>
@@ -742,7 +743,8 @@ StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool 
     if (elem == 8 || variant == kVarThree) {
       if (!fits(32, 16, 7, 6, 256) && !fits(32, 16, 5, 4, 512)) p = {32, 16, 5};
     } else if (!fits(64, 16, 7, 7, 256)) {
-      const bool small = g.plane * elem < (size_t(1) << 32);
+      // 2^29 elements: the FP64 accumulator is addressed with the FP32 fields
+      const bool small = g.plane * kWidestElement < (size_t(1) << 32);
       if (!small)
         p = {64, 16, 5};
       else if (!fits(32, 32, 10, 5, 256) && !fits(32, 32, 10, 4, 512))
