@@ -163,8 +163,8 @@ __device__ __forceinline__ bool links(const Geometry& g, const NodeIdx& n, unsig
   return true;
 }
 
-// Regions of 32 x 32 nodes are taken only where a plane's offsets fit 32 bits
-// (plan_steps).
+// Regions of 16 x 16 and of 32 x 32 nodes are taken only where a plane's offsets
+// fit 32 bits (plan_steps).
 template <int RX, int RY>
 constexpr Lanes lanes_of = short_offsets(RX, RY) ? kSmall : RX % 64 == 0 ? kRow : kAny;
 
@@ -739,12 +739,13 @@ StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool 
       if (region_grid(g, p).ntiles <= n) return true;
     return false;
   };
-  if (!fits(16, 16, 7, 4, 256)) {
+  // 2^29 elements (of which a lattice of few nodes may have as many, its rows
+  // lying far apart): the FP64 accumulator is addressed with the FP32 fields
+  const bool small = g.plane * kWidestElement < (size_t(1) << 32);
+  if (!small || !fits(16, 16, 7, 4, 256)) {
     if (elem == 8 || variant == kVarThree) {
       if (!fits(32, 16, 7, 6, 256) && !fits(32, 16, 5, 4, 512)) p = {32, 16, 5};
     } else if (!fits(64, 16, 7, 7, 256)) {
-      // 2^29 elements: the FP64 accumulator is addressed with the FP32 fields
-      const bool small = g.plane * kWidestElement < (size_t(1) << 32);
       if (!small)
         p = {64, 16, 5};
       else if (!fits(32, 32, 10, 5, 256) && !fits(32, 32, 10, 4, 512))

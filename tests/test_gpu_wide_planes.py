@@ -33,7 +33,7 @@ def _sweeps(p, dtype, ckpt, pitch, monkeypatch):
     return out
 
 
-@pytest.mark.parametrize("nx,prec,ckpt", [(300, "f32", -1)])
+@pytest.mark.parametrize("nx,prec,ckpt", [(300, "f32", -1), (40, "f32", -1), (40, "f64", 0)])
 def test_rows_far_apart(nx, prec, ckpt, monkeypatch):
     import torch
     ny, steps, pitch = 520, 4, 1 << 20

@@ -34,3 +34,13 @@ def test_offsets_of_large_lattices(nx, ny, source, species, dtype):
     for left in (1, 2, 5, 100):
         assert _offsets_fit(_plan(nx, ny, nx, dtype, source=source, species=species, left=left),
                             ny, nx)
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP64])
+@pytest.mark.parametrize("source,species", SCHEMES)
+@pytest.mark.parametrize("nx,ny,pitch", [(10, 2560, 1 << 18), (1, 1, 1 << 30), (64, 64, 1 << 23),
+                                         (64, 64, (1 << 23) + 64), (128, 128, 1 << 30)])
+def test_offsets_of_rows_far_apart(nx, ny, pitch, source, species, dtype):
+    for left in (1, 2, 5, 100):
+        assert _offsets_fit(_plan(nx, ny, pitch, dtype, source=source, species=species, left=left),
+                            ny, pitch)
