@@ -322,8 +322,15 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
   T nu[9], nv[9], nw[9], mu[2] = {T(0), T(0)};
   double sum = 0.0;
   constexpr bool fresh = FIRST && !IMPL;  // the sweep's first step: g starts at zero
-  if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) return;
-  if (kRows<RY> && WALLS && !FIRST && a.step > 0 && (lm & 1u)) return;
+  // a sweep's outputs are zero on solid nodes: what it starts, it clears there
+  // in its first launch, what it ends in its last
+  auto clear = [&] {
+    if (fresh) *own_at<A>(a.g, n) = 0.0;
+    if (a.adj_u0) *own_at<A>(a.adj_u0, n) = T(0);
+    if (a.adj_v0) *own_at<A>(a.adj_v0, n) = T(0);
+  };
+  if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) lm = 1u;
+  if (kRows<RY> && WALLS && !FIRST && (lm & 1u)) return clear();
   adjoint_gather<A, WALLS, VAR, FIRST, T>(g, n, a.src, a.seed_u, a.seed_v, lm, nu, nv, nw);
   if (LAG && !FIRST) {
     mu[0] = *own_at<A>(a.mu, n);
@@ -334,14 +341,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
                                            a.rec_stride, steps_of(tg)))
     return;
   if (!node_again<RX, RY>(g, tg, n)) return;
-  const bool solid = WALLS && (lm & 1u);
-  if (solid) {
-    // a sweep's outputs are zero on solid nodes
-    if (fresh) *own_at<A>(a.g, n) = 0.0;
-    if (a.adj_u0) *own_at<A>(a.adj_u0, n) = T(0);
-    if (a.adj_v0) *own_at<A>(a.adj_v0, n) = T(0);
-    return;
-  }
+  if (WALLS && (lm & 1u)) return clear();
   *own_at<A>(a.g, n) = sum;
   if (LAG) {
     *own_at<A>(a.mu_out, n) = mu[0];

@@ -66,3 +66,35 @@ def test_square_regions_of_the_other_schemes(size, source):
     r = device_gradient(p, _torch_dtype("f32"))
     assert rel_l2(r["uN"], ref["uN"], p.fluid) <= ftol
     assert rel_l2(r["grad"], ref["grad"], p.fluid) <= gtol
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("source,ckpt", [(2, 4), (2, -1), (1, 4)])
+def test_initial_sensitivities_on_solid_blocks(source, ckpt, prec):
+    """dJ/du0 and dJ/dv0 in buffers that held NaN: exact zeros on solid nodes,
+    whole 64-node segments and frame rows of them included."""
+    import torch
+    from paper_1908_03876_amd import abi
+    from paper_1908_03876_amd.solver import DeviceProblem, GradientIteration
+    p = _ragged(77, 200, 23, 9, False, True)
+    p.solid[[0, -1], :] = p.solid[5:12, 64:192] = 1
+    for a in (p.u0, p.v0, p.control, p.u_target):
+        a[p.solid != 0] = 0.0
+    p = I.slow_reaction(p, 0.1).copy(source_term=source)
+    print(f"source {source} ckpt {ckpt} {prec}", flush=True)
+    seed = (O.forward(p)["uN"] - p.u_target) * p.fluid
+    _, want_u0, want_v0 = O.adjoint(p, seed)
+    dp = DeviceProblem(p, dtype=_torch_dtype(prec))
+    it = GradientIteration(dp, ckpt_every=ckpt)
+    it.gradient()
+    it.gacc.fill_(float("nan"))
+    au0, av0 = (torch.full_like(it.uN, float("nan")) for _ in range(2))
+    abi.amrt_adjoint(dp.struct, it.tape.handle, dp.u0, dp.v0, dp.control, it.seed, None, it.gacc,
+                     au0, av0)
+    gtol = TOL[prec][1]
+    for dev, want in ((au0, want_u0), (av0, want_v0)):
+        dev = dp.host(dev)
+        assert (dev[p.solid != 0] == 0.0).all()
+        assert rel_l2(dev, want, p.fluid) <= gtol
+    assert (dp.host(it.gacc)[p.solid != 0] == 0.0).all()
+    it.close()
