@@ -478,6 +478,12 @@ void* alag_of(const mrt_tape* t, int k) { return k && lag_pair(t) ? t->lag : t->
 bool one_step(int so2, int mode) { return so2 && mode != 1; }
 bool one_step(const mrt_tape* t) { return one_step(t->so2, t->mode); }
 
+// Does an output of `na` bytes at a share memory with an input of `nb` at b?
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const char *x = static_cast<const char*>(a), *y = static_cast<const char*>(b);
+  return x && y && x < y + nb && y < x + na;
+}
+
 // Forward steps [n0, n1) starting from `src` (null = equilibrium of u0, v0).
 // Several steps run in one launch; the output of its last step n goes to
 // ckpt[(n+1)/K] when that step closes a segment (checkpointed mode, forward
@@ -610,6 +616,11 @@ int adjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0,
       su = tu;
       sv = tv;
     }
+    // Sensitivities written over the seeds: the last launch is not the first one,
+    // whose regions read the seeds of each other's nodes.
+    const size_t nb = t->plane * sizeof(T);
+    const bool in_place = overlap(adj_u0, nb, su, nb) || overlap(adj_u0, nb, sv, nb) ||
+                          overlap(adj_v0, nb, su, nb) || overlap(adj_v0, nb, sv, nb);
     SpanGuard span(1, s);
     for (int n = n1 - 1; n >= n0;) {
       mrt::AdjLaunch<T> a;
@@ -623,7 +634,9 @@ int adjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0,
       a.mu = mu;
       mu = a.mu_out = static_cast<T*>(alag_of(t, mu == t->alag ? 1 : 0));
       a.step = n;
-      const mrt::StepPlan plan = mrt::plan_steps(g, sizeof(T), a.variant, n - n0 + 1, one_step(t));
+      int left = n - n0 + 1;
+      if (!asrc && n0 == 0 && in_place && left > 1) --left;
+      const mrt::StepPlan plan = mrt::plan_steps(g, sizeof(T), a.variant, left, one_step(t));
       n -= plan.steps;
       const bool ends = n < 0;
       a.dst = ends ? nullptr : static_cast<T*>(t->abuf[asrc == t->abuf[0] ? 1 : 0]);
@@ -731,7 +744,11 @@ int cadjoint_impl(const mrt_problem* p, mrt_tape* t, const void* u0, const void*
       a.rec = slot<T>(t, n - n0);
       a.rec_stride = t->rec_slot_bytes / sizeof(T);
       a.g = gacc;
-      const mrt::StepPlan plan = mrt::plan_steps(g, sizeof(T), 1, n - n0 + 1, false);
+      // the integral written over the seed: the launch that reads the seed takes
+      // one step, in which a node reads its own
+      const bool in_place = !src && overlap(gacc, t->plane * sizeof(double), seed_u,
+                                            t->plane * sizeof(T));
+      const mrt::StepPlan plan = mrt::plan_steps(g, sizeof(T), 1, in_place ? 1 : n - n0 + 1, false);
       mrt::launch_cadj<T>(g, m, cc, a, plan, s);
       span.count(plan.steps);
       int rc = last_launch_error();

@@ -98,3 +98,30 @@ def test_initial_sensitivities_on_solid_blocks(source, ckpt, prec):
         assert rel_l2(dev, want, p.fluid) <= gtol
     assert (dp.host(it.gacc)[p.solid != 0] == 0.0).all()
     it.close()
+
+
+@pytest.mark.parametrize("steps", [2, 4, 7])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_sensitivities_over_the_seeds(steps, prec):
+    """dJ/du0, dJ/dv0 (and, in FP64, the continuous adjoint's integral) written
+    over the seeds of a sweep so short that one launch could take all of it: the
+    bits of separate buffers."""
+    from paper_1908_03876_amd import abi
+    from paper_1908_03876_amd.solver import DeviceProblem, GradientIteration
+    p = _ragged(78, 300, 333, steps, False, True)
+    print(f"{steps} steps {prec}", flush=True)
+    dp = DeviceProblem(p, dtype=_torch_dtype(prec))
+    it = GradientIteration(dp)
+    it.gradient()
+    fields = (dp.u0, dp.v0, dp.control)
+    su, sv = it.seed.clone(), dp.field(p.u0)
+    au0, av0 = dp.empty_field(), dp.empty_field()
+    abi.amrt_adjoint(dp.struct, it.tape.handle, *fields, su, sv, it.gacc, au0, av0)
+    abi.amrt_adjoint(dp.struct, it.tape.handle, *fields, su, sv, it.gacc, su, sv)
+    assert (dp.host(su) == dp.host(au0)).all() and (dp.host(sv) == dp.host(av0)).all()
+    if prec == "f64":
+        su = it.seed.clone()
+        abi.mrt_cadjoint(dp.struct, it.tape.handle, *fields, it.seed, it.gacc)
+        abi.mrt_cadjoint(dp.struct, it.tape.handle, *fields, su, su)
+        assert (dp.host(su) == dp.host(it.gacc)).all()
+    it.close()
