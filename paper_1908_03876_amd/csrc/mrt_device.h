@@ -293,7 +293,11 @@ __device__ __forceinline__ void put(T* p, T v) {
 template <Lanes A, bool WALLS, bool ADJ, bool NT = false, typename T>
 __device__ __forceinline__ void store_species(const Geometry& g, const NodeIdx& n, const T f[9],
                                               T* __restrict__ dst, unsigned lm) {
-  if (WALLS && !g.periodic && (n.ex0 || n.ex1 || n.ey0 || n.ey1)) {
+  bool edge = WALLS && !g.periodic && (n.ex0 || n.ex1 || n.ey0 || n.ey1);
+  // a wavefront of which some lanes store less than the others makes ordinary
+  // stores, so that the parts of a chunk merge
+  if (WALLS && NT) edge = __builtin_amdgcn_ballot_w64(edge) != 0ull;
+  if (edge) {
 #pragma unroll
     for (int i = 0; i < 9; ++i)
       if (!(ADJ ? pull_outside(n, i) : push_outside(n, i)))
@@ -324,7 +328,7 @@ __device__ __forceinline__ void implicit_solve(const ModelCoef<T>& m, T Gu, T Gv
                                                T& v) {
   const T hr = T(0.5) * m.r_u;
   const T bq = T(1) - hr;
-  u = T(2) * Gu / (bq + dsqrt(bq * bq + T(4) * hr * Gu));
+  u = T(2) * Gu / (bq + dsqrt(dot2(T(4) * hr, Gu, bq, bq)));
   v = (Gv + T(0.5) * (m.a_uv * u + c)) / (T(1) + T(0.5) * m.b_v);
 }
 

@@ -331,6 +331,15 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
   };
   if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) lm = 1u;
   if (kRows<RY> && WALLS && !FIRST && (lm & 1u)) return clear();
+  if (kRows<RY> && !a.dst && !a.adj_u0 && !a.adj_v0) {
+    // step 0 of a sweep that asks for the gradient alone: its share needs no
+    // record and no adjoint of u
+    if (WALLS && (lm & 1u)) return clear();
+    adjoint_gather<A, WALLS, VAR, FIRST, T>(g, n, a.src, a.seed_u, a.seed_v, lm, nu, nv, nw);
+    const T share = weighted(nv);
+    *own_at<A>(a.g, n) = (fresh ? 0.0 : *own_at<A>(a.g, n)) + double(IMPL ? T(0.5) * share : share);
+    return;
+  }
   adjoint_gather<A, WALLS, VAR, FIRST, T>(g, n, a.src, a.seed_u, a.seed_v, lm, nu, nv, nw);
   if (LAG && !FIRST) {
     mu[0] = *own_at<A>(a.mu, n);
@@ -434,11 +443,14 @@ __global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, 
   T fp[9], fq[9], rec[5];
   double sum = 0.0;
   const T* in = a.rec;
-  if (WALLS) lm = link_word<A>(g, n);
+  if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) return;
+  if (kRows<RY> && WALLS && !FIRST && (lm & 1u)) return;
   pull_species<A, FIRST>(g, n, m.u, a.src, a.seed_u, fp);
   pull_species<A, FIRST>(g, n, m.v, a.src + 9 * g.plane, static_cast<const T*>(nullptr), fq);
   load_record<A, kVarFirst, kRows<RY>>(g, n, in, rec);
   if (r.owner && !FIRST) sum = *own_at<A>(a.g, n);
+  // as the loop of several steps, which carries its populations, sees them
+  if (FIRST && kRows<RY>) keep_rounded<false>(fp, fq, static_cast<T*>(nullptr));
   const Steps st = steps_of(tg);
   const int row = first_row<RX, RY>();
   if (WALLS && !kRows<RY> && st.count > 1) lm = links_inside<RX, RY>(lm);
@@ -673,8 +685,7 @@ template <typename T, int VAR, typename F>
 void dispatch_region(const Geometry& g, const StepPlan& p, F f) {
   using std::integral_constant;
   auto shape = [&](auto W) {
-    if constexpr (VAR == kVarExplicit)
-      if (p.ry == 1) return f(W, integral_constant<int, 256>(), integral_constant<int, 1>());
+    if (p.ry == 1) return f(W, integral_constant<int, 256>(), integral_constant<int, 1>());
     if (p.rx == 16) return f(W, integral_constant<int, 16>(), integral_constant<int, 16>());
     if constexpr (kWide<T, VAR>) {
       f(W, integral_constant<int, 32>(), integral_constant<int, 16>());
@@ -730,8 +741,18 @@ void dispatch_variant(int variant, F f) {
 //     64^2    1.9 (4)   1.6 (5)   1.4 (7)  (64 x 16: 1.8 (7))
 // The regions of wide nodes are 32 x 16: 1024^2, FP64, 30.4 (4) and 28.7 (5);
 // 32 x 32, which leaves one of them to a compute unit, 34.7 (5).
+//
+// A step by itself (an interval of one step, a sweep of one) exchanges nothing,
+// and rows of 256 nodes take it faster: whole chunks of non-temporal stores, and
+// small work-groups, which leave solid segments at once.  In us a forward step
+// checkpointed at every step, regions and rows: 2048^2 134 and 114, FP64 259 and
+// 233; 1024^2 FP64 65 and 60; 256^2 5.6 and 4.2.  Only where rows need more than
+// one round of eight work-groups a compute unit and compute more than four times
+// (wide nodes: eight times) the nodes of the regions do they lose: 16 x 32768 30
+// and 34, FP64 41 and 54; not 24 x 32768 in FP64, the AMRT step 143 and 129.
 StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool one) {
-  if (one) return {256, 1, 1};
+  constexpr StepPlan kRowPlan = {256, 1, 1};
+  if (one) return kRowPlan;
   StepPlan p;
   // the most steps, from `most` down to `least`, whose regions are at most n
   auto fits = [&](int rx, int ry, int most, int least, int n) {
@@ -742,8 +763,9 @@ StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool 
   // 2^29 elements (of which a lattice of few nodes may have as many, its rows
   // lying far apart): the FP64 accumulator is addressed with the FP32 fields
   const bool small = g.plane * kWidestElement < (size_t(1) << 32);
+  const bool wide = elem == 8 || variant == kVarThree;
   if (!small || !fits(16, 16, 7, 4, 256)) {
-    if (elem == 8 || variant == kVarThree) {
+    if (wide) {
       if (!fits(32, 16, 7, 6, 256) && !fits(32, 16, 5, 4, 512)) p = {32, 16, 5};
     } else if (!fits(64, 16, 7, 7, 256)) {
       if (!small)
@@ -755,6 +777,11 @@ StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool 
   // as many launches as that takes, their steps spread evenly
   const int launches = (left + p.steps - 1) / p.steps;
   p.steps = (left + launches - 1) / launches;
+  if (p.steps == 1) {
+    const int n = region_grid(g, kRowPlan).ntiles;
+    const size_t most = (wide ? 8 : 4) * size_t(region_grid(g, p).ntiles) * p.rx * p.ry;
+    if (n <= 8 * 256 || size_t(n) * 256 <= most) return kRowPlan;
+  }
   return p;
 }
 

@@ -25,7 +25,8 @@ namespace dev {
 // 16 x 16 regions, which spread them over the chip.  The explicit second-order
 // source also reads the previous step's kinetics of its nodes, which a
 // neighbouring region may not find overwritten: where the tape holds only one
-// buffer for them it takes one step at a time, in rows of 256 nodes (kRows).
+// buffer for them it takes one step at a time.  A launch of one step goes over
+// rows of 256 nodes (kRows).
 //
 // What bounds it: with 5 steps a launch the state's traffic falls from 144 to
 // 29 B a node and step, and the vector units, of which the rings take 35%,
@@ -198,7 +199,8 @@ __device__ __forceinline__ bool forward_steps(Exchange<T, RX, RY, W3>& lds, cons
     if (WALLS) keep_rounded<W3>(fu, fv, fw);
     forward_collide<T, VAR>(m, fu, fv, fw, c, r, lag, true);
     record();
-    if (!kRows<RY> && st.count > 1) {
+    if (kRows<RY>) return true;
+    if (st.count > 1) {
       give<WALLS, false>(lds, fu, fv, fw, lm);
       if (!live_rows<RX, RY>(st, 1, row)) return retire(st, 0);
       take<false>(lds, fu, fv, fw);

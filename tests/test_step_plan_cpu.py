@@ -44,3 +44,20 @@ def test_offsets_of_rows_far_apart(nx, ny, pitch, source, species, dtype):
     for left in (1, 2, 5, 100):
         assert _offsets_fit(_plan(nx, ny, pitch, dtype, source=source, species=species, left=left),
                             ny, pitch)
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP64])
+@pytest.mark.parametrize("source,species", SCHEMES)
+@pytest.mark.parametrize("nx,ny", [(1, 1), (64, 64), (255, 3), (300, 157), (2048, 2048),
+                                   (32768, 1), (24576, 24576)])
+def test_a_step_by_itself_takes_rows(nx, ny, source, species, dtype):
+    s = _plan(nx, ny, nx, dtype, source=source, species=species, left=1)
+    assert (s.width, s.height, s.steps) == (256, 1, 1)
+
+
+@pytest.mark.parametrize("nx,rows", [(1, False), (16, False), (32, False), (40, True), (128, True)])
+def test_a_step_by_itself_on_few_columns(nx, rows):
+    """Rows of 256 nodes for lattices much narrower than that only where all of
+    them run at once."""
+    assert _plan(nx, 2000, nx, FP32, left=1).height == 1
+    assert (_plan(nx, 30000, nx, FP32, left=1).height == 1) == rows
