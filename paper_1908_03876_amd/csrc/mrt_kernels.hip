@@ -742,6 +742,17 @@ void dispatch_variant(int variant, F f) {
 // The regions of wide nodes are 32 x 16: 1024^2, FP64, 30.4 (4) and 28.7 (5);
 // 32 x 32, which leaves one of them to a compute unit, 34.7 (5).
 //
+// Low lattices of many columns: a region has nodes of a row several times over.
+// 64 x 16 regions are taken where they are fewer than 32 x 32, and one step a
+// launch in rows of 256 nodes where the regions take more than one round (wide
+// nodes: two) and compute over eight times the nodes that the rows do (4.5 times
+// with three species in FP64, of which a compute unit holds one region).  A
+// forward step in us, 32 x 32 (FP64: 32 x 16), 64 x 16 and rows:
+//   32768 x 1   7.8   -    3.7      FP64   7.1  4.5     three species, FP64   -    6.1
+//   32768 x 2   7.8   -    4.9             7.3  7.0                           -    9.4
+//   32768 x 4   8.1  4.7   6.4             7.8  9.8                         15.8  11.9
+//   32768 x 8   8.9  5.0   9.6             8.2 17.1                         31.4  30.3 (x 9)
+//
 // A step by itself (an interval of one step, a sweep of one) exchanges nothing,
 // and rows of 256 nodes take it faster: whole chunks of non-temporal stores, and
 // small work-groups, which leave solid segments at once.  In us a forward step
@@ -764,15 +775,26 @@ StepPlan plan_steps(const Geometry& g, size_t elem, int variant, int left, bool 
   // lying far apart): the FP64 accumulator is addressed with the FP32 fields
   const bool small = g.plane * kWidestElement < (size_t(1) << 32);
   const bool wide = elem == 8 || variant == kVarThree;
+  bool large = false;  // more than a round or two of regions
   if (!small || !fits(16, 16, 7, 4, 256)) {
     if (wide) {
-      if (!fits(32, 16, 7, 6, 256) && !fits(32, 16, 5, 4, 512)) p = {32, 16, 5};
+      large = !fits(32, 16, 7, 6, 256) && !fits(32, 16, 5, 4, 512);
+      if (large) p = {32, 16, 5};
     } else if (!fits(64, 16, 7, 7, 256)) {
-      if (!small)
-        p = {64, 16, 5};
-      else if (!fits(32, 32, 10, 5, 256) && !fits(32, 32, 10, 4, 512))
+      large = !small || (!fits(32, 32, 10, 5, 256) && !fits(32, 32, 10, 4, 512));
+      if (large) {
+        const StepPlan low = {64, 16, 5};
         p = {32, 32, 5};
+        if (!small || region_grid(g, low).ntiles < region_grid(g, p).ntiles) p = low;
+      }
     }
+  }
+  if (large) {
+    const bool widest = elem == 8 && variant == kVarThree;
+    const size_t n = region_grid(g, p).ntiles, nodes = n * p.rx * p.ry;
+    if (n > (wide ? 1024 : 512) &&
+        nodes > (widest ? 9 : 16) * size_t(region_grid(g, kRowPlan).ntiles) * 128)
+      return kRowPlan;
   }
   // as many launches as that takes, their steps spread evenly
   const int launches = (left + p.steps - 1) / p.steps;

@@ -61,3 +61,18 @@ def test_a_step_by_itself_on_few_columns(nx, rows):
     them run at once."""
     assert _plan(nx, 2000, nx, FP32, left=1).height == 1
     assert (_plan(nx, 30000, nx, FP32, left=1).height == 1) == rows
+
+
+@pytest.mark.parametrize("nx,ny,dtype,species,shape",
+                         [(32768, 1, FP32, 2, (256, 1)), (32768, 2, FP32, 2, (256, 1)),
+                          (32768, 4, FP32, 2, (64, 16)), (32768, 8, FP32, 2, (64, 16)),
+                          (32768, 44, FP32, 2, (32, 32)), (4, 32768, FP32, 2, (32, 32)),
+                          (16384, 1, FP32, 2, (64, 16)), (16384, 1, FP64, 2, (32, 16)),
+                          (32768, 1, FP64, 2, (256, 1)), (32768, 4, FP64, 2, (32, 16)),
+                          (32768, 4, FP32, 3, (32, 16)), (32768, 4, FP64, 3, (256, 1)),
+                          (32768, 16, FP64, 3, (32, 16)), (2048, 2048, FP32, 2, (32, 32))])
+def test_low_lattices(nx, ny, dtype, species, shape):
+    """Regions hold a low lattice's rows several times over: fewer of them, or rows."""
+    s = _plan(nx, ny, nx, dtype, species=species)
+    assert (s.width, s.height) == shape
+    assert s.steps == (1 if shape == (256, 1) else 5)
