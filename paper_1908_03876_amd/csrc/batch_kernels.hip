@@ -115,6 +115,7 @@ __device__ __forceinline__ Geometry inst_geom(int L) {
   g.link = nullptr;
   g.wflag = nullptr;
   g.nsx = (L + 63) / 64;
+  g.solid_areas = 0;
   return g;
 }
 

@@ -363,6 +363,7 @@ struct mrt_tape {
   double* result = nullptr;
   double* host = nullptr;   // pinned
   int64_t n_fluid = 0;
+  int solid_areas = 0;      // a share of the 64-node segments are all solid
   // last forward
   bool fwd_done = false;
   int rec_seg = -1;         // segment whose (u, j_v) record the slots hold
@@ -450,6 +451,7 @@ mrt::Geometry geometry(const mrt_tape* t) {
   g.link = t->masked ? t->link : nullptr;
   g.wflag = t->masked ? t->wflag : nullptr;
   g.nsx = (t->nx + 63) / 64;
+  g.solid_areas = t->solid_areas;
   return g;
 }
 
@@ -944,12 +946,14 @@ int mrt_tape_create(const mrt_problem* p, int32_t ckpt_every,
     mrt::launch_build_link(geo, g.periodic, g.mask, t->link, t->wflag, s);
   mrt::launch_count_fluid(geo, t->partials, t->result, s);
   rc = last_launch_error();
-  if (!rc) rc = read_result(t, s, 1);
+  if (!rc) rc = read_result(t, s, 2);
   if (rc) {
     free_tape(t);
     return rc;
   }
   t->n_fluid = int64_t(t->host[0]);
+  t->solid_areas =
+      t->masked && t->host[1] * mrt::kSolidAreas >= double(geo.nsx) * double(geo.ny);
   *out = t;
   return MRT_OK;
 }

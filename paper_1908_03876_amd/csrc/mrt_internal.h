@@ -44,11 +44,15 @@ struct Geometry {
   const uint32_t* wflag; // [ny][nsx]: 1 if a 64-node row segment touches a
                          // solid node (itself or a neighbour), when masked
   int nsx;               // 64-node segments per row, ceil(nx / 64)
+  int solid_areas;       // 1: regions look for solid ones among them and leave
 };
 
+// Share of all-solid segments from which on they do (solid_region in
+// mrt_kernels.hip gives both sides).
+constexpr int kSolidAreas = 8;  // one in 8
+
 // Link mask: bit 0 = node solid, bit i (1..8) = node x - e_i solid (wrapped
-// when periodic; outside a non-periodic lattice is handled from the node
-// coordinates, not by the mask).
+// when periodic) or outside a non-periodic lattice.
 void launch_build_link(const Geometry& g, int periodic, const uint8_t* mask,
                        uint16_t* link_out, uint32_t* wflag_out, hipStream_t s);
 
@@ -220,6 +224,7 @@ void launch_gd_step(const Geometry& g, T* ctrl,
                     const T* grad, double zeta, double lo, double hi,
                     double* partials, double* result, hipStream_t s);
 
+// result[0] = fluid nodes, result[1] = all-solid segments.
 void launch_count_fluid(const Geometry& g, double* partials, double* result,
                         hipStream_t s);
 

@@ -163,6 +163,24 @@ __device__ __forceinline__ bool links(const Geometry& g, const NodeIdx& n, unsig
   return true;
 }
 
+// Are all nodes of this work-group's region solid, by the flags of the 64-node
+// segments that it touches?  Every wavefront reads all of them (a lane per row
+// and side) and comes to the same answer without a barrier.  A region that wraps
+// around an end of its rows is not asked.
+template <int RX, int RY>
+__device__ __forceinline__ bool solid_region(const Geometry& g, const TileGrid& tg) {
+  if (kRows<RY> || !g.solid_areas) return false;
+  static_assert(kRows<RY> || (RX <= 64 && 2 * RY <= 64), "two flags a row");
+  const int lane = threadIdx.x & 63;
+  const int t = xcd_tile(blockIdx.x, tg.ntiles), halo = tg.steps - 1;
+  const int x0 = t % tg.ntx * (RX - 2 * halo) - halo;
+  int y = t / tg.ntx * (RY - 2 * halo) - halo + lane % RY;
+  if (x0 < 0 || x0 + RX > g.nx) return false;
+  y = (y < 0 ? y + g.ny * RY : y) % g.ny;
+  const int x = x0 + (lane / RY & 1) * (RX - 1);
+  return __builtin_amdgcn_ballot_w64(g.wflag[size_t(y) * g.nsx + (x >> 6)] != 2u) == 0ull;
+}
+
 // Regions of 16 x 16 and of 32 x 32 nodes are taken only where a plane's offsets
 // fit 32 bits (plan_steps).
 template <int RX, int RY>
@@ -191,6 +209,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void forward_kernel(Geometry g, Mod
   if (kRows<RY> && !r.owner) return;
   NodeIdx n;
   make_node(g, r.x, r.y, n);
+  if (WALLS && solid_region<RX, RY>(g, tg)) return;
   unsigned lm = 0;
   T fu[9], fv[9], fw[9], lag[2] = {T(0), T(0)}, c = T(0);
   if (WALLS && !links<kRows<RY>, A>(g, n, lm)) return;
@@ -331,6 +350,10 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
   };
   if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) lm = 1u;
   if (kRows<RY> && WALLS && !FIRST && (lm & 1u)) return clear();
+  if (WALLS && solid_region<RX, RY>(g, tg)) {
+    if (r.owner) clear();
+    return;
+  }
   if (kRows<RY> && !a.dst && !a.adj_u0 && !a.adj_v0) {
     // step 0 of a sweep that asks for the gradient alone: its share needs no
     // record and no adjoint of u
@@ -377,6 +400,7 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCo
   if (kRows<RY> && !r.owner) return;
   NodeIdx n;
   make_node(g, r.x, r.y, n);
+  if (WALLS && solid_region<RX, RY>(g, tg)) return;
   unsigned lm = 0;
   T fu[9], fv[9], fw[9], rec[5], lag[2] = {T(0), T(0)}, c = T(0);
   const T* in = a.rec;
@@ -443,6 +467,10 @@ __global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, 
   T fp[9], fq[9], rec[5];
   double sum = 0.0;
   const T* in = a.rec;
+  if (WALLS && solid_region<RX, RY>(g, tg)) {
+    if (FIRST && r.owner) *own_at<A>(a.g, n) = 0.0;
+    return;
+  }
   if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) return;
   if (kRows<RY> && WALLS && !FIRST && (lm & 1u)) return;
   pull_species<A, FIRST>(g, n, m.u, a.src, a.seed_u, fp);
@@ -649,6 +677,10 @@ __global__ __launch_bounds__(kBlock) void count_fluid_kernel(
     const size_t y = k / g.nx, x = k % g.nx;
     if (is_fluid(link, y * g.pitch + x)) acc[0] += 1.0;
   }
+  if (g.wflag)
+    for (size_t k = size_t(blockIdx.x) * kBlock + threadIdx.x; k < size_t(g.nsx) * g.ny;
+         k += size_t(gridDim.x) * kBlock)
+      if (g.wflag[k] == 2u) acc[1] += 1.0;
   block_reduce_store(acc, partials + size_t(blockIdx.x) * kRedSlots);
 }
 
