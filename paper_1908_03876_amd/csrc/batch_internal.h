@@ -21,11 +21,10 @@ struct BatchTile {
   unsigned long long pad;
 };
 
-// Steps that the sweeps take between two grid barriers, by the width of their
-// regions (width x 1024 / width nodes, of which batch_steps - 1 on each side
-// are recomputed): as many as leave a region two rows or more, and 5 of the
-// tallest, as for a large lattice by itself (4 and 5 are measured in
-// batch_kernels.hip).
+// Most steps that the sweeps take between two grid barriers, by the width of
+// their regions (width x 1024 / width nodes): as many as leave a region two rows
+// or more, and 5 of the tallest, as for a large lattice by itself (4 and 5 are
+// measured in batch_kernels.hip).
 __host__ __device__ constexpr int batch_steps(int width) {
   return width == 64 ? 5 : width == 128 ? 3 : 2;
 }
@@ -62,6 +61,8 @@ struct BatchArgs {
   const BatchTile* tiles;    // of the one-pass kernels
   const BatchTile* regions;  // of the sweeps
   int ntiles, nregions, tile_w;
+  int steps;                 // steps a barrier that the regions are cut for: they
+                             // own all nodes but steps - 1 on each side
   const ModelCoef<T>* coef;  // [count]
   const int* L;              // [count] lattice side
   const size_t* foff;        // [count] offset of instance k's fields

@@ -145,8 +145,7 @@ struct BatchNode {
 };
 
 template <int RX, int RY>
-__device__ __forceinline__ BatchNode node_of_region(const BatchTile* regions, int t) {
-  constexpr int halo = batch_steps(RX) - 1;
+__device__ __forceinline__ BatchNode node_of_region(const BatchTile* regions, int t, int halo) {
   const BatchTile tl = uniform_load(regions + t);
   BatchNode r;
   r.k = __builtin_amdgcn_readfirstlane(tl.k);
@@ -182,7 +181,7 @@ __device__ __forceinline__ void forward_sweep(Exchange<T, RX, RY, false>& lds,
                                               const BatchArgs<T>& a, const T* src, T* dst,
                                               T* rec, int count) {
   each_region(a.nregions, [&](int t) {
-    const BatchNode r = node_of_region<RX, RY>(a.regions, t);
+    const BatchNode r = node_of_region<RX, RY>(a.regions, t, a.steps - 1);
     const ModelCoef<T> m = uniform_load(a.coef + r.k);
     T fu[9], fv[9];
     const T* s = src + 18 * r.fo;
@@ -193,7 +192,7 @@ __device__ __forceinline__ void forward_sweep(Exchange<T, RX, RY, false>& lds,
     unsigned open = 0u;  // no walls
     if (!forward_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, open, m, c, r.owner, fu, fv,
                                                       nil, nil, rec ? rec + 3 * r.fo : nil,
-                                                      a.rec_elems, {count, batch_steps(RX) - 1}))
+                                                      a.rec_elems, {count, a.steps - 1}))
       return;
     if (!r.owner) return;
     T* d = dst + 18 * r.fo;
@@ -207,7 +206,7 @@ __device__ __forceinline__ void adjoint_sweep(Exchange<T, RX, RY, false>& lds,
                                               const BatchArgs<T>& a, const T* src, T* dst,
                                               const T* rec, int step, int count) {
   each_region(a.nregions, [&](int t) {
-    const BatchNode r = node_of_region<RX, RY>(a.regions, t);
+    const BatchNode r = node_of_region<RX, RY>(a.regions, t, a.steps - 1);
     const ModelCoef<T> m = uniform_load(a.coef + r.k);
     T nu[9], nv[9];
     T* const nil = nullptr;
@@ -217,7 +216,7 @@ __device__ __forceinline__ void adjoint_sweep(Exchange<T, RX, RY, false>& lds,
     double sum = r.owner && !FIRST ? *own_at<kRow>(a.gacc + r.fo, r.n) : 0.0;
     if (!adjoint_steps<false, kVarFirst, kRow, FIRST>(lds, r.g, r.n, open, m, step, nu, nv, nil,
                                                       nil, sum, rec + 3 * r.fo, a.rec_elems,
-                                                      {count, batch_steps(RX) - 1}))
+                                                      {count, a.steps - 1}))
       return;
     if (!r.owner) return;
     *own_at<kRow>(a.gacc + r.fo, r.n) = sum;
@@ -237,7 +236,7 @@ __device__ void forward_pass(Exchange<T, RX, RY, false>& lds, const BatchArgs<T>
                              unsigned nblocks, bool* alive) {
   for (int n = n0; n < n1 && *alive;) {
     const int seg_end = a.mode == 2 ? min(n1, (n / a.K + 1) * a.K) : n1;
-    const int count = even_steps(seg_end - n, batch_steps(RX)), end = n + count;
+    const int count = even_steps(seg_end - n, a.steps), end = n + count;
     T* dst = src == a.buf[0] ? a.buf[1] : a.buf[0];
     if (ckpt && a.mode == 2 && end % a.K == 0 && end < a.N)
       dst = a.ckpt + size_t(end / a.K - 1) * a.state_elems;
@@ -284,7 +283,7 @@ __global__ MRT_BATCH_BOUNDS void batch_adjoint_kernel(BatchArgs<T> a) {
       forward_pass<T, RX, RY>(lds, a, n0, n1, n0, src, false, true, nb, &alive);
     }
     for (int n = n1 - 1; n >= n0 && alive;) {
-      const int count = even_steps(n - n0 + 1, batch_steps(RX)), next = n - count;
+      const int count = even_steps(n - n0 + 1, a.steps), next = n - count;
       T* dst = next < 0 ? nullptr : (asrc == a.abuf[0] ? a.abuf[1] : a.abuf[0]);
       const T* rec = a.rec + size_t(n - n0) * a.rec_elems;
       if (n == a.N - 1)

@@ -219,3 +219,26 @@ def test_batch_forward_timeout_is_reported():
         b.forward()
     assert e.value.code == abi.MRT_EHIP
     b.close()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("tile_w", [64, 128, 256])
+@pytest.mark.parametrize("nsteps,ckpt", [(1, 0), (11, 1), (11, 2), (11, 3), (13, 6), (12, 0)])
+def test_batch_regions_cut_for_the_steps_they_take(nsteps, ckpt, tile_w, prec):
+    """Regions own as many nodes as the steps between two barriers leave them:
+    the gradients and, by the pass without checkpoints, u(T) are bit for bit
+    those of single-lattice runs."""
+    import torch
+    from tests.gpu_util import device_gradient
+    dtype = torch.float32 if prec == "f32" else torch.float64
+    ps = _problems(nsteps=nsteps, sizes=(40, 67, 150), n=3)
+    b = _batch(ps, dtype, ckpt_every=ckpt)
+    b.set_tiles(tile_w, 1)
+    b.forward()
+    end = [b.get(k, "uN").double().cpu().numpy() for k in range(3)]
+    b.iterate(use_graph=False)
+    print(f"{nsteps} steps, interval {ckpt}, width {tile_w}, {prec}", flush=True)
+    for p, g, u in zip(ps, _grads(b), end):
+        one = device_gradient(p, dtype)
+        assert np.array_equal(g, one["grad"]) and np.array_equal(u, one["uN"])
+    b.close()
