@@ -386,8 +386,9 @@ enum {
 /* Launch shape of the persistent kernels: regions of tile_w x (1024/tile_w)
  * nodes (tile_w 64, 128 or 256; the passes over the last state and the
  * gradient take tiles of tile_w x (256/tile_w)) and blocks_per_cu resident
- * work-groups per compute unit (1..max_blocks_per_cu, the occupancy limit, so
- * that every work-group of a persistent launch is resident). */
+ * work-groups per compute unit (max_blocks_per_cu at most, the occupancy limit,
+ * so that every work-group of a persistent launch is resident; counts up to four
+ * times that, which work-groups of 256 nodes may have, are taken as that). */
 typedef struct mrt_batch_tiles {
   int32_t tile_w;
   int32_t blocks_per_cu;

@@ -415,12 +415,13 @@ int mrt_batch_copy(mrt_batch* b, int32_t k, int32_t which, int32_t to_batch,
 
 int mrt_batch_set_tiles(mrt_batch* b, const mrt_batch_tiles* tiles) {
   if (!b || !tiles) return err(MRT_EINVAL, "NULL argument");
-  const int maxb = std::min(b->max_bpc_f, b->max_bpc_a);
-  if (tiles->blocks_per_cu < 1 || tiles->blocks_per_cu > maxb)
-    return err(MRT_EINVAL, "blocks_per_cu outside 1.." + std::to_string(maxb));
+  // a count may stem from work-groups of 256 nodes, four of which are one region
+  const int maxb = std::min(b->max_bpc_f, b->max_bpc_a), most = 4 * maxb;
+  if (tiles->blocks_per_cu < 1 || tiles->blocks_per_cu > most)
+    return err(MRT_EINVAL, "blocks_per_cu outside 1.." + std::to_string(most));
   int rc = build_tiles(b, tiles->tile_w);
   if (rc) return rc;
-  b->bpc = tiles->blocks_per_cu;
+  b->bpc = std::min(tiles->blocks_per_cu, maxb);
   return MRT_OK;
 }
 

@@ -242,3 +242,27 @@ def test_batch_regions_cut_for_the_steps_they_take(nsteps, ckpt, tile_w, prec):
         one = device_gradient(p, dtype)
         assert np.array_equal(g, one["grad"]) and np.array_equal(u, one["uN"])
     b.close()
+
+
+@pytest.mark.parametrize("prec,most", [("f32", 8), ("f64", 4)])
+def test_batch_takes_the_counts_of_smaller_work_groups(prec, most):
+    """Work-groups per compute unit up to 2048 nodes (FP64: 1024) of 256 each are
+    accepted, and mean as many as can be resident; more or none are refused."""
+    import torch
+    from paper_1908_03876_amd import abi
+    ps = _problems(nsteps=6, sizes=(64, 150), n=2)
+    dtype = torch.float32 if prec == "f32" else torch.float64
+    ref = None
+    for n in range(1, most + 1):
+        b = _batch(ps, dtype)
+        b.set_tiles(64, n)
+        t = b.tiles()
+        assert t["blocks_per_cu"] == min(n, t["max_blocks_per_cu"])
+        b.iterate(use_graph=True)
+        g = _grads(b)
+        ref = g if ref is None else ref
+        assert all(np.array_equal(x, y) for x, y in zip(ref, g))
+        for bad in (0, most + 1):
+            with pytest.raises(abi.MrtError):
+                b.set_tiles(64, bad)
+        b.close()
