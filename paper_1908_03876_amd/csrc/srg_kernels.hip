@@ -181,6 +181,37 @@ struct FirstLayer {
   }
 };
 
+// The first layer by itself: a wavefront takes 64 consecutive pixels of one row
+// as four tiles.
+__global__ __launch_bounds__(kB) void l0_fwd_kernel(const float* __restrict__ x,
+                                                    const uint16_t* __restrict__ w,
+                                                    const float* __restrict__ bias,
+                                                    uint16_t* __restrict__ out, int B, int H,
+                                                    int W, float iscale) {
+  const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+  // (row, segment) units fit 32 bits: fields hold at most 2^28 pixels
+  const unsigned nseg = unsigned(W + 63) >> 6;
+  const unsigned unit = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (unit >= unsigned(B) * unsigned(H) * nseg) return;  // the whole wavefront
+  const int x0 = int(unit % nseg) * 64;
+  const unsigned row = unit / nseg;  // image b, row y: b H + y
+  const int y = int(row % unsigned(H));
+  FirstLayer first;
+  first.load(w, bias, q, n);
+  float v[4][3];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    FirstLayer::window(x + size_t(row - y) * W, H, W, y, FirstLayer::column(x0 + 16 * t + n, W, q),
+                       v[t]);
+  uint16_t* o = out + (size_t(row) * W + x0) * kC + 8 * q;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const u32x4 z = first.apply(v[t], q, iscale);
+    if (x0 + 16 * t + n < W)
+      __builtin_nontemporal_store(z, reinterpret_cast<u32x4*>(o + (16 * t + n) * kC));
+  }
+}
+
 // dx[p] = s_in * sum_t sum_co W0[co][t] dz0[p - off(t)][co]: one thread per
 // pixel, the 32 channels of each mirrored tap summed as 16 two-channel dot
 // products of BF16 pairs (exact products, FP32 sums), the weight pairs read
@@ -1430,11 +1461,26 @@ int blocks_for_pixels(int B, int H, int W) { return blocks_for(size_t(B) * H * W
 void launch_srg_head_fwd(const float* x, const uint16_t* w0, const float* b0, uint16_t* a0,
                          const uint16_t* wf, const float* b, uint16_t* out, int B, int H, int W,
                          float iscale, hipStream_t s) {
-  // patches of kPR rows x 64 pixels, three blocks per CU
-  const int np = B * ((H + kPR - 1) / kPR) * ((W + 63) / 64);
-  const int nb = np < 768 ? (np > 0 ? np : 1) : 768;
-  hipLaunchKernelGGL(head_fwd_kernel, dim3(nb), dim3(kB), 0, s, x, w0, b0, a0, wf, b, out, B, H, W,
+  // Patches of kPR rows x 64 pixels, three blocks per CU.  One pass recomputes two
+  // rows of the first layer in each run down a column and keeps a block's lanes
+  // beyond the field's last pixel over both layers.  Where blocks have more than
+  // a patch each, fields of few rows, or of few rows and part of a column, take
+  // a pass per layer; us of the whole forward, one pass and two:
+  //   1 x 3 x 262144   122  103    1024 x 8 x 8     63   56   512 x 32 x 32      98   95
+  //   1 x 6 x 262144   215  205    1024 x 16 x 16   93   88   64 x 128 x 128    114  116
+  //   1 x 12 x 131072  160  168    100000 x 9      398  386   17 x 1024 x 1024 1453 1544
+  //   1 x 24 x 65536   153  163    100000 x 30     447  472
+  const int pr = (H + kPR - 1) / kPR, np = B * pr * ((W + 63) / 64), blocks = 768;
+  if (np <= blocks || (pr >= 3 && (W >= 64 || (W >= 20 && pr >= 16)))) {
+    hipLaunchKernelGGL(head_fwd_kernel, dim3(np < blocks ? (np > 0 ? np : 1) : blocks), dim3(kB), 0,
+                       s, x, w0, b0, a0, wf, b, out, B, H, W, iscale);
+    return;
+  }
+  const size_t units = size_t(B) * H * ((W + 63) / 64);
+  const int nb = int((units + kWaves - 1) / kWaves);
+  hipLaunchKernelGGL(l0_fwd_kernel, dim3(nb > 0 ? nb : 1), dim3(kB), 0, s, x, w0, b0, a0, B, H, W,
                      iscale);
+  launch_srg_c32_fwd(a0, wf, b, out, B, H, W, s);
 }
 
 void launch_srg_l0_bwd_data(const uint16_t* dz, const uint16_t* w, float* dx, int B, int H,

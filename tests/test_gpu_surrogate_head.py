@@ -39,3 +39,11 @@ def test_first_two_layers_at_patch_edges(B, H, W):
         gw = s.get_param(layer, 2).reshape(grads[layer][0].shape)
         assert rel_l2(gw, grads[layer][0]) <= TOL_G, layer
         assert rel_l2(s.get_param(layer, 3), grads[layer][1]) <= TOL_G, layer
+
+
+@pytest.mark.parametrize("B,H,W", [(800, 3, 5), (257, 12, 63), (52, 62, 19), (1, 4, 49200),
+                                   (60, 61, 20), (100, 11, 130)])
+def test_first_two_layers_on_many_patches(B, H, W):
+    """Both sides of the line between one pass and a pass per layer, where a
+    work-group has more than a patch."""
+    test_first_two_layers_at_patch_edges(B, H, W)
