@@ -72,12 +72,24 @@ def read_traffic(kernel: str, L: int, path: str = None, srcs=None, per="step"):
     return int(v) if v is not None else None
 
 
-# time steps that one launch (or grid barrier) takes on a large lattice
-STEPS_PER_LAUNCH = 5
+# most steps between two grid barriers of the batched engine, by region width
+BATCH_STEPS = {64: 5, 128: 3, 256: 2}
 
 
-def bytes_per_site(elem: int, source_term: int = 1, nspecies: int = 2,
-                   steps: int = STEPS_PER_LAUNCH):
+def mean_steps(dp, info):
+    """Time steps a launch of a sweep over the tape's segments, on average: the
+    plan of the library, launch by launch."""
+    from paper_1908_03876_amd import abi
+    launches = 0
+    for n in range(0, dp.nsteps, info.ckpt_every):
+        left = min(info.ckpt_every, dp.nsteps - n)
+        while left > 0:
+            left -= abi.mrt_step_plan(dp.struct, info.ckpt_every, left).steps
+            launches += 1
+    return dp.nsteps / launches
+
+
+def bytes_per_site(elem: int, source_term: int = 1, nspecies: int = 2, steps: float = 1):
     """Algorithmic HBM bytes per fluid node and time step, `steps` of them in a
     launch.  Every step writes (forward) or reads (adjoint) its record: u, j_v;
     and j_w with three species.  A launch reads and writes once: 9 NS planes of
@@ -184,17 +196,29 @@ def bench_batched(args):
     t1 = time.perf_counter()
     ms = (t1 - t0) * 1e3 / args.steps
     # forward, recomputation with the record, adjoint
-    rec_b, adj_b, fwd_b = bytes_per_site(4)
+    per = K / -(-K // BATCH_STEPS[best["tile_w"]])
+    rec_b, adj_b, fwd_b = bytes_per_site(4, steps=per)
     bytes_it = sites * N * (fwd_b + rec_b + adj_b)
     out = {"metric": "batched coupled MRT+AMRT MLUPS (96 uneven instances)",
            "value": round(sites * N / (ms / 1e3) / 1e6, 1), "unit": "MLUPS",
            "ms_per_iteration": round(ms, 1), "iterations": args.steps,
            "instances": 96, "sites": sites, "nsteps": N, "ckpt_every": K,
-           "tiles": best, "steps_per_barrier": STEPS_PER_LAUNCH,
+           "tiles": best, "steps_per_barrier": round(per, 2),
            "algorithmic_GBps_per_iteration": round(bytes_it / (ms / 1e3) / 1e9, 1),
            "hbm_frac": round(bytes_it / (ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
            "J_sum_history": [round(x, 4) for x in js]}
     b.close()
+    # the streaming probe with the access mix of each part at one step a barrier:
+    # the iteration's ceiling is its bytes over the sum of each part's bytes at
+    # its own ceiling
+    ceil, t_ideal = {}, 0.0
+    for r, w, nb in ((19, 18, fwd_b), (19, 21, rec_b), (23, 20, adj_b)):
+        c = stream_ceiling(r, w, sites, torch.device("cuda:0"))
+        ceil[f"{r}+{w}"] = c["GBps"]
+        t_ideal += sites * N * nb / (c["GBps"] * 1e9)
+    out["stream_ceiling_GBps"] = ceil
+    out["iteration_stream_ceiling_GBps"] = round(bytes_it / t_ideal / 1e9, 1)
+    out["frac_of_stream_ceiling"] = round(t_ideal / (ms / 1e3), 4)
     print(json.dumps(out), flush=True)
 
 
@@ -246,7 +270,7 @@ def bench_autograd(args):
     f_ms, f_n = abi.mrt_timing_read(abi.TIMING_FORWARD)
     a_ms, a_n = abi.mrt_timing_read(abi.TIMING_ADJOINT)
     r_ms, r_n = abi.mrt_timing_read(abi.TIMING_RECOMPUTE)
-    b_fwd, b_adj, b_norec = bytes_per_site(4)
+    b_fwd, b_adj, b_norec = bytes_per_site(4, steps=mean_steps(s.dp, info))
     # forward without record, recomputation with record, adjoint
     bytes_it = N * n_fluid * (b_norec + b_fwd + b_adj)
     out = {"metric": "autograd MRT+AMRT MLUPS (forward + checkpointed backward)",
@@ -874,9 +898,7 @@ def main():
     value = n_fluid * dp.nsteps / (ms_step / 1e3) / 1e6
 
     elem = 4
-    # the explicit second-order source takes one step a launch unless the tape
-    # holds every step
-    per_launch = STEPS_PER_LAUNCH if args.source_term != 2 or info.mode == 1 else 1
+    per_launch = mean_steps(dp, info)
     b_fwd, b_adj, b_norec = bytes_per_site(elem, args.source_term, args.species, per_launch)
     # per-step algorithmic bytes: fluid nodes only
     step_bytes_adj = n_fluid * b_adj
@@ -893,7 +915,7 @@ def main():
                if args.source_term == 1 and args.species == 2 else None)
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": traffic, "kernel": dom, "steps_per_launch": per_launch,
+            "traffic": traffic, "kernel": dom, "steps_per_launch": round(per_launch, 2),
             "avg_step_ms": round(avg_ms, 5),
             "algorithmic_bytes_per_step": int(lbytes),
             "algorithmic_bytes_per_fluid_node": round(

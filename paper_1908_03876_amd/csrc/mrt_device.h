@@ -649,9 +649,7 @@ __device__ __forceinline__ void finalize_node(
 // of the kinetics this step stores for the next one.  With sigma = w . nu
 // per species, the adjoint of this step's kinetics is rho = 3/2 sigma + mu
 // (sigma + mu at step 0, where F_prev = F), and the new mu = -1/2 sigma.
-// FIRST (step N-1) reads no mu: nothing reads the last stored kinetics.
-// step0 marks step 0 (a run-time flag: LAST is set only when dJ/du0,
-// dJ/dv0 are requested).
+// Step N-1 reads no mu: nothing reads the last stored kinetics.
 //
 // kVarImplicit: the adjoint of g.  With A the relaxation (phi -> phi -
 // C (phi - w~ Theta)), a step maps g to g* = A g + (tau/2)(A w + w) Phi +
