@@ -167,10 +167,17 @@ __device__ __forceinline__ bool links(const Geometry& g, const NodeIdx& n, unsig
 // segments that it touches?  Every wavefront reads all of them (a lane per row
 // and side) and comes to the same answer without a barrier.  A region that wraps
 // around an end of its rows is not asked.
+//
+// The look stands before a region's loads and costs 5% where it finds nothing
+// (2048^2, AMRT step 53.2 -> 56.3 us), so only lattices of which a share of the
+// segments is all solid (kSolidAreas) have kernels that look (kAreas).  Forward
+// step in us without and with it, by the share of fluid in one square block:
+//            2%           10%           25%           50%           75%
+//   2048^2  45.3 12.9    48.5 24.1     48.6 31.3     55.4 46.2     58.6 56.0
+//   1024^2  11.8  5.7    12.1  7.9     12.6  9.5     13.1 11.7     13.9 13.9
 template <int RX, int RY>
 __device__ __forceinline__ bool solid_region(const Geometry& g, const TileGrid& tg) {
-  if (kRows<RY> || !g.solid_areas) return false;
-  static_assert(kRows<RY> || (RX <= 64 && 2 * RY <= 64), "two flags a row");
+  static_assert(RX <= 64 && 2 * RY <= 64, "two flags a row");
   const int lane = threadIdx.x & 63;
   const int t = xcd_tile(blockIdx.x, tg.ntiles), halo = tg.steps - 1;
   const int x0 = t % tg.ntx * (RX - 2 * halo) - halo;
@@ -180,6 +187,9 @@ __device__ __forceinline__ bool solid_region(const Geometry& g, const TileGrid& 
   const int x = x0 + (lane / RY & 1) * (RX - 1);
   return __builtin_amdgcn_ballot_w64(g.wflag[size_t(y) * g.nsx + (x >> 6)] != 2u) == 0ull;
 }
+
+// What a kernel meets: no walls, walls, walls with solid areas.
+constexpr int kOpen = 0, kWalls = 1, kAreas = 2;
 
 // Regions of 16 x 16 and of 32 x 32 nodes are taken only where a plane's offsets
 // fit 32 bits (plan_steps).
@@ -199,17 +209,19 @@ constexpr int kRegionWaves = (sizeof(T) == 4 ? 8 : 4) / (VAR == kVarThree ? 2 : 
                  amdgpu_waves_per_eu(kRegionWaves<T, VAR>)))
 
 // Forward steps n .. n + K - 1 (FIRST: n = 0, from the initial fields).
-template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
+template <typename T, int KIND, int VAR, int RX, int RY, bool FIRST>
 __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void forward_kernel(Geometry g, ModelCoef<T> m,
                                                                  FwdLaunch<T> a, TileGrid tg) {
   constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit;
+  constexpr bool WALLS = KIND != kOpen;
   constexpr Lanes A = lanes_of<RX, RY>;
   __shared__ Exchange<T, RX, RY, W3> lds;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
   if (kRows<RY> && !r.owner) return;
   NodeIdx n;
   make_node(g, r.x, r.y, n);
-  if (WALLS && solid_region<RX, RY>(g, tg)) return;
+  if constexpr (KIND == kAreas)
+    if (solid_region<RX, RY>(g, tg)) return;
   unsigned lm = 0;
   T fu[9], fv[9], fw[9], lag[2] = {T(0), T(0)}, c = T(0);
   if (WALLS && !links<kRows<RY>, A>(g, n, lm)) return;
@@ -327,10 +339,11 @@ __global__ __launch_bounds__(kBlock) void implicit_tlm_final_kernel(
 }
 
 // Adjoint steps n, n - 1, ..., n - K + 1.
-template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
+template <typename T, int KIND, int VAR, int RX, int RY, bool FIRST>
 __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, ModelCoef<T> m,
                                                             AdjLaunch<T> a, TileGrid tg) {
   constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit, IMPL = VAR == kVarImplicit;
+  constexpr bool WALLS = KIND != kOpen;
   __shared__ Exchange<T, RX, RY, W3> lds;
   constexpr Lanes A = lanes_of<RX, RY>;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
@@ -350,10 +363,11 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
   };
   if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) lm = 1u;
   if (kRows<RY> && WALLS && !FIRST && (lm & 1u)) return clear();
-  if (WALLS && solid_region<RX, RY>(g, tg)) {
-    if (r.owner) clear();
-    return;
-  }
+  if constexpr (KIND == kAreas)
+    if (solid_region<RX, RY>(g, tg)) {
+      if (r.owner) clear();
+      return;
+    }
   if (kRows<RY> && !a.dst && !a.adj_u0 && !a.adj_v0) {
     // step 0 of a sweep that asks for the gradient alone: its share needs no
     // record and no adjoint of u
@@ -390,17 +404,19 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void adjoint_kernel(Geometry g, Mod
 // Tangent-linear steps n .. n + K - 1: pull the perturbation (FIRST, step 0:
 // the equilibrium of (du0, dv0); the third species starts at zero),
 // linearised collision at the recorded (u, j_v), streaming as the forward.
-template <typename T, bool WALLS, int VAR, int RX, int RY, bool FIRST>
+template <typename T, int KIND, int VAR, int RX, int RY, bool FIRST>
 __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCoef<T> m,
                                                              TlmLaunch<T> a, TileGrid tg) {
   constexpr bool W3 = VAR == kVarThree, LAG = VAR == kVarExplicit;
+  constexpr bool WALLS = KIND != kOpen;
   constexpr Lanes A = lanes_of<RX, RY>;
   __shared__ Exchange<T, RX, RY, W3> lds;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
   if (kRows<RY> && !r.owner) return;
   NodeIdx n;
   make_node(g, r.x, r.y, n);
-  if (WALLS && solid_region<RX, RY>(g, tg)) return;
+  if constexpr (KIND == kAreas)
+    if (solid_region<RX, RY>(g, tg)) return;
   unsigned lm = 0;
   T fu[9], fv[9], fw[9], rec[5], lag[2] = {T(0), T(0)}, c = T(0);
   const T* in = a.rec;
@@ -453,12 +469,13 @@ __global__ MRT_REGION_BOUNDS(T, VAR, RX, RY) void tlm_kernel(Geometry g, ModelCo
 // Continuous-adjoint steps: pull the adjoint populations (or, at the first
 // reversed step, p = seed_u at equilibrium and q = 0) and collide with the
 // records of the forward steps n, n - 1, ... at those times.
-template <typename T, bool WALLS, int RX, int RY, bool FIRST>
+template <typename T, int KIND, int RX, int RY, bool FIRST>
 __global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, ModelCoef<T> m,
                                                          CadjCoef<T> cc, CadjLaunch<T> a,
                                                          TileGrid tg) {
-  __shared__ Exchange<T, RX, RY, false> lds;
+  constexpr bool WALLS = KIND != kOpen;
   constexpr Lanes A = lanes_of<RX, RY>;
+  __shared__ Exchange<T, RX, RY, false> lds;
   const RegionNode r = region_node<RX, RY>(g, tg, threadIdx.x);
   if (kRows<RY> && !r.owner) return;
   NodeIdx n;
@@ -467,10 +484,11 @@ __global__ MRT_REGION_BOUNDS(T, kVarFirst, RX, RY) void cadj_kernel(Geometry g, 
   T fp[9], fq[9], rec[5];
   double sum = 0.0;
   const T* in = a.rec;
-  if (WALLS && solid_region<RX, RY>(g, tg)) {
-    if (FIRST && r.owner) *own_at<A>(a.g, n) = 0.0;
-    return;
-  }
+  if constexpr (KIND == kAreas)
+    if (solid_region<RX, RY>(g, tg)) {
+      if (FIRST && r.owner) *own_at<A>(a.g, n) = 0.0;
+      return;
+    }
   if (WALLS && !links<kRows<RY> && !FIRST, A>(g, n, lm)) return;
   if (kRows<RY> && WALLS && !FIRST && (lm & 1u)) return;
   pull_species<A, FIRST>(g, n, m.u, a.src, a.seed_u, fp);
@@ -711,25 +729,33 @@ TileGrid region_grid(const Geometry& g, const StepPlan& p) {
   return t;
 }
 
-// Calls f(integral constants walls, region width, region height) for a
+// Calls f(integral constants kind of walls, region width, region height) for a
 // lattice and a plan.
 template <typename T, int VAR, typename F>
 void dispatch_region(const Geometry& g, const StepPlan& p, F f) {
   using std::integral_constant;
-  auto shape = [&](auto W) {
-    if (p.ry == 1) return f(W, integral_constant<int, 256>(), integral_constant<int, 1>());
-    if (p.rx == 16) return f(W, integral_constant<int, 16>(), integral_constant<int, 16>());
+  auto shape = [&](auto K) {
+    if (p.rx == 16) return f(K, integral_constant<int, 16>(), integral_constant<int, 16>());
     if constexpr (kWide<T, VAR>) {
-      f(W, integral_constant<int, 32>(), integral_constant<int, 16>());
+      f(K, integral_constant<int, 32>(), integral_constant<int, 16>());
     } else {
-      if (p.ry == 32) return f(W, integral_constant<int, 32>(), integral_constant<int, 32>());
-      f(W, integral_constant<int, 64>(), integral_constant<int, 16>());
+      if (p.ry == 32) return f(K, integral_constant<int, 32>(), integral_constant<int, 32>());
+      f(K, integral_constant<int, 64>(), integral_constant<int, 16>());
     }
   };
-  if (g.masked || !g.periodic)
-    shape(std::true_type());
+  auto rows = [&](auto K) {
+    f(K, integral_constant<int, 256>(), integral_constant<int, 1>());
+  };
+  const integral_constant<int, kOpen> open;
+  const integral_constant<int, kWalls> walls;
+  if (!g.masked && g.periodic)
+    p.ry == 1 ? rows(open) : shape(open);
+  else if (p.ry == 1)
+    rows(walls);
+  else if (g.solid_areas)
+    shape(integral_constant<int, kAreas>());
   else
-    shape(std::false_type());
+    shape(walls);
 }
 
 // Calls f(integral constant variant).
@@ -751,13 +777,15 @@ void dispatch_variant(int variant, F f) {
 // A launch costs about 5 us beside its steps (the gather, the stores and the
 // gap before it), every further step costs a ring of each region, and the time
 // of a small lattice goes up in whole rounds of regions: with up to 256 of them
-// each has a compute unit to itself, with up to 512 two share one.  So: the
-// most steps whose regions fit one round of 256, or else of 512, as long as the
-// rings leave enough of a region; and 5 for the large lattices, where memory
-// and the vector units come level.  Of the shapes, 16 x 16 spreads the smallest
-// lattices over the chip; 64 x 16, whose rows are scalar addresses, has the
-// shortest steps; 32 x 32 owns more of its nodes (with 5 steps 56% instead of
-// 44%).  Measured in us per forward step, FP32, steps per launch in brackets:
+// each has a compute unit to itself, with up to 512 two share one.  (The counts
+// are of a whole device; in a partition of fewer compute units the plan is as
+// right, its rounds only more.)  So: the most steps whose regions fit one round
+// of 256, or else of 512, as long as the rings leave enough of a region; and 5
+// for the large lattices, between memory (fewer) and the rings (more).
+// Of the shapes, 16 x 16 spreads the smallest lattices over the chip; 64 x 16,
+// whose rows are scalar addresses, has the shortest steps; 32 x 32 owns more of
+// its nodes (with 5 steps 56% instead of 44%).  Measured in us per forward step,
+// FP32, steps per launch in brackets:
 //            64 x 16                                      32 x 32
 //   2048^2   64.2 (3)  57.0 (4)  51.2 (5)  57.2 (6)       61.4 (4)  50.9 (5)  53.2 (6)
 //            54.7 (5) the AMRT step                       52.7 (5)

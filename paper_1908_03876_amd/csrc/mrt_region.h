@@ -28,12 +28,13 @@ namespace dev {
 // buffer for them it takes one step at a time.  A launch of one step goes over
 // rows of 256 nodes (kRows).
 //
-// What bounds it: with 5 steps a launch the state's traffic falls from 144 to
-// 29 B a node and step, and the vector units, of which the rings take 35%,
-// come level with memory.  Stores are ordinary ones: a region's rows begin
-// anywhere in a 64-byte chunk, and two regions' parts of a chunk merge in L2
-// (with non-temporal stores each part went to memory by itself: 65 us a step
-// at 2048^2 instead of 55).  Measured at 2048^2, masked, FP32, in us a step:
+// What bounds it: the vector units.  With 5 steps a launch the state's traffic
+// falls from 144 to 29 B a node and step, and at 2048^2 in FP32 vector
+// instructions take 88% (forward) and 90% (AMRT step) of the issue slots at 2.4
+// GHz, a third of them for the rings, beside 4.1 to 4.4 TB/s.  Stores are
+// ordinary ones: a region's rows begin anywhere in a 64-byte chunk, and two
+// regions' parts of a chunk merge in L2 (with non-temporal stores each part went
+// to memory by itself: 65 us a step at 2048^2 instead of 55).  Measured at 2048^2, masked, FP32, in us a step:
 // forward with record 122 -> 50.9, AMRT step 125 -> 52.7 (periodic: 49.6 and
 // 49.4); at 1024^2, periodic, 27 -> 11.8 and 36 -> 13.2; at 512^2, masked,
 // 9.7 -> 3.8 and 10.4 -> 4.0; at 128^2 4.4 -> 1.6.
