@@ -19,6 +19,7 @@ KINDS = {"periodic": (True, False), "masked": (False, True), "walls": (False, Fa
 SIZES = {(70, 45): (9, {"f32": (16, 16), "f64": (16, 16)}),
          (257, 7): (1, {"f32": (256, 1), "f64": (256, 1)}),
          (161, 160): (9, {"f32": (64, 16), "f64": (32, 16)}),
+         (20, 2100): (5, {"f32": (32, 32), "f64": (32, 16)}),  # single steps in regions too
          (32768, 2): (4, {"f32": (256, 1), "f64": (256, 1)}),
          (32768, 7): (6, {"f32": (64, 16), "f64": (32, 16)}),
          (386, 390): (11, {"f32": (32, 32), "f64": (32, 16)})}
